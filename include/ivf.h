@@ -29,8 +29,11 @@
  *     (v_mfma_i32_32x32x32_i8) on rows x - 128 against quantised centroids,
  *     whose integer scores are exact; the bound is the quantisation error
  *     alone. For D <= 128 one int8 plane rint(c - 128) screens first and
- *     settles most rows; the rows it leaves are screened on two int8 planes
- *     of the 16-bit fixed-point value rint(256 (c - 128)). A call whose
+ *     settles most rows; the few centroids that can be nearest to a row it
+ *     leaves are collected by a second pass over the plane and evaluated in
+ *     fp64. Where there are too many such rows or centroids the rows are
+ *     screened on two int8 planes of the 16-bit fixed-point value
+ *     rint(256 (c - 128)). A call whose
  *     centroids have a coordinate outside [0, 255.998] (which does not
  *     quantise) is screened on fp32 MFMA instead; the switch happens on the
  *     device, without a host synchronisation.
@@ -216,7 +219,7 @@ ivf_status ivf_build_lists(ivf_ctx *ctx, const int32_t *labels, int64_t N, int64
  *   out[4] route: centroids in the threshold sample
  *   out[5] assignment of uint8 rows: 1 when screened on int8 MFMA
  *   out[6] assignment of uint8 rows: rows the single-plane int8 screen left
- *          to the two-plane int8 screen
+ *          with more than two possible centroids
  *   out[7] reserved (0) */
 ivf_status ivf_last_stats(ivf_ctx *ctx, int64_t out[8]);
 
@@ -247,9 +250,11 @@ ivf_status ivf_last_stats(ivf_ctx *ctx, int64_t out[8]);
  *                           row goes on to the two-plane screen (results must
  *                           not change)
  *   IVF_OPT_RESCREEN_CAP    > 0: capacity of the single plane's list of rows
- *                           for the two-plane screen (default 4,096 + N / 16;
- *                           past it the two-plane screen takes every row);
- *                           speed only, never results
+ *                           for the two-plane screen, which then takes them
+ *                           (default 4,096 + N / 4, N / 16 from 2^26 rows on,
+ *                           with the rows' candidates collected; past it the
+ *                           two-plane screen takes every row); speed only,
+ *                           never results
  *   IVF_OPT_ASSIGN_SLICE    > 0: rows per assignment slice, below the
  *                           default 2^28 (each slice is screened with its own
  *                           worklists); speed only, never results

@@ -136,8 +136,9 @@ size_t layout_adc(void *base, int64_t B, int64_t P, int64_t k, AdcScratch *w)
 // the int8 screen, [3] the same for its single plane, [4] the single plane's
 // largest coordinate residual (float bits), [5] counter of the rows the
 // single plane leaves to the two planes, [6] the int8 routing gate, [7] the
-// single plane's largest residual norm (float bits), then (from word 16)
-// kNumStats uint64 counters.
+// single plane's largest residual norm (float bits), [8] counter of the rows
+// with two candidates, [9] counter of the rows with too many, then (from word
+// 16) kNumStats uint64 counters.
 struct Scalars {
     uint32_t *mc2_bits;
     uint32_t *wl_cnt;
@@ -273,9 +274,21 @@ RouteLayout layout_route(void *base, const RoutePlan &p, int64_t C)
 }
 
 int64_t worklist_cap(int64_t N) { return std::min<int64_t>(N, 4096 + N / 64); }
-// rows the single-plane int8 screen may list for the two-plane screen
-// before that screen takes every row
-int64_t rescreen_cap(int64_t N) { return std::min<int64_t>(N, 4096 + N / 16); }
+// Rows a one-pass screen may list before the next screen takes every row: a
+// quarter of a call of ordinary size (a 131,072 x 100 table of close centroids
+// lists 16 %; past a quarter a full second screen costs about as much as
+// collecting), a sixteenth of a call of more than 2^26 rows, where the lists'
+// 48 bytes per entry would grow into gigabytes.
+int64_t rescreen_cap(int64_t N)
+{
+    return std::min<int64_t>(N, 4096 + std::max<int64_t>(N / 16, std::min<int64_t>(N / 4, (int64_t)1 << 22)));
+}
+// two-candidate rows left to the resolving kernel (12 bytes each; more are
+// decided inside the screen)
+int64_t duel_cap(int64_t N)
+{
+    return std::min<int64_t>(N, 4096 + std::max<int64_t>(N / 8, std::min<int64_t>(N / 2, (int64_t)1 << 23)));
+}
 
 struct AssignLayout {
     Scalars sc;
@@ -298,6 +311,7 @@ struct AssignLayout {
     int32_t *pos1;
     int32_t *list;
     int64_t list_cap;
+    ResolveLists rs;
     int32_t *wl;
     int64_t wl_cap;
     double *fb_d;   // split fallback partial results
@@ -365,6 +379,15 @@ AssignLayout layout_assign(void *base, int64_t N, int64_t C, int qdp, bool need_
             l.pos1 = c.take<int32_t>(C);
             l.list_cap = rescreen_cap(std::min(N, kAssignSlice));
             l.list = c.take<int32_t>(l.list_cap);
+            l.rs.duel_cap = duel_cap(std::min(N, kAssignSlice));
+            l.rs.duel = c.take<uint2>(l.rs.duel_cap);
+            l.rs.duel2 = c.take<int32_t>(l.rs.duel_cap);
+            l.rs.list_thr = c.take<int32_t>(l.list_cap);
+            l.rs.cand_cnt = c.take<uint32_t>(l.list_cap);
+            l.rs.cand = c.take<int32_t>((size_t)l.list_cap * kResolveCand);
+            l.rs.list2 = c.take<int32_t>(l.list_cap);
+            l.rs.duel_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 8 : nullptr;
+            l.rs.list2_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 9 : nullptr;
         }
     }
     l.wl_cap = worklist_cap(std::min(N, kAssignSlice));
@@ -529,7 +552,10 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
         if (r0 > 0) {
             // the worklist and the single plane's list start empty for every slice
             TIMED("fill", launch_fill_u32(l.sc.wl_cnt, 1, 0u, s));
-            if (single) TIMED("fill", launch_fill_u32(list_cnt, 1, 0u, s));
+            if (single) {
+                TIMED("fill", launch_fill_u32(list_cnt, 1, 0u, s));
+                TIMED("fill", launch_fill_u32(l.rs.duel_cnt, 2, 0u, s));
+            }
         }
         ScreenArgs a{};
         a.rows = xr;
@@ -581,7 +607,27 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
                 q.hint = hint ? hint + r0 : nullptr;
                 q.ord1 = ord1;
                 q.pos1 = pos1;
+                // near ties: decided from collected candidates (a forced
+                // rescreen or a test's list capacity keeps the two-plane
+                // screen of the listed rows)
+                const bool collect = !q.force_rescreen && ctx->rescreen_cap == 0;
+                q.rs = l.rs;
+                if (!collect) q.rs.list_thr = nullptr;
                 TIMED("screen_top1_i8s", launch_screen_i8_single(DP, q, ctx->num_cus, s));
+                if (collect) TIMED("collect_i8", launch_collect_i8(DP, q, ctx->num_cus, s));
+                ResolveArgs ra{};
+                ra.rows = xr;
+                ra.nrows = n;
+                ra.D = D;
+                ra.cent = cent;
+                ra.C = C;
+                ra.ord = ord1;
+                ra.list = l.list;
+                ra.list_cnt = list_cnt;
+                ra.list_cap = q.list_cap;
+                ra.rs = q.rs;
+                ra.labels = lab;
+                TIMED("resolve", launch_resolve(rowtype, ra, ctx->num_cus, s));
             }
             TIMED("screen_top1_i8", launch_screen_i8(DP, q, ctx->num_cus, s));
             a.gate = q_bad;

@@ -25,7 +25,7 @@ enum StatSlot {
     kStatOverflow = 3,
     kStatSample = 4,
     kStatScreenI8 = 5,  // 1 when the uint8 rows were screened on int8 MFMA
-    kStatRescreen = 6,  // rows the single-plane int8 screen left to the two-plane screen
+    kStatRescreen = 6,  // rows the single-plane int8 screen left with more than two candidates
     kNumStats = 8
 };
 
@@ -70,6 +70,44 @@ struct ScreenArgs {
 hipError_t launch_screen(int mode, int rowtype, int DP, const ScreenArgs &a, int waves, int num_cus,
                          hipStream_t s);
 
+// ---- near ties the one-pass screens leave (resolve.hip) ----------------------
+// A one-pass screen (single int8 plane) settles the rows whose
+// best score stands clear of the others by its window. Rows with exactly two
+// centroids inside the window are "duels"; rows with more are listed with the
+// score a candidate must reach, collected by a second pass over the plane and
+// resolved here, both by the exact fp64 distances of the candidates.
+constexpr int kResolveCand = 8;       // candidates kept per listed row
+constexpr int kResolveScanRows = 512; // at most this many overflowed rows go to the fp64 scan directly
+struct ResolveLists {
+    // duels: (row, first centroid) and the second centroid
+    uint2 *duel;
+    int32_t *duel2;
+    uint32_t *duel_cnt;   // null: duels are decided by the screen itself
+    int64_t duel_cap;
+    // listed rows: threshold (int score or float bits), candidates met,
+    // their plane rows
+    int32_t *list_thr;    // null: listed rows go to the next screen
+    uint32_t *cand_cnt;
+    int32_t *cand;        // [list_cap][kResolveCand]
+    // rows with more candidates than kResolveCand (or none)
+    int32_t *list2;
+    uint32_t *list2_cnt;
+};
+struct ResolveArgs {
+    const void *rows;     // [nrows, D] fp32 or uint8
+    int64_t nrows;
+    int D;
+    const float *cent;
+    int64_t C;
+    const uint32_t *ord;  // plane row -> centroid id (null: the same)
+    const int32_t *list;
+    const uint32_t *list_cnt;
+    int64_t list_cap;
+    ResolveLists rs;
+    int32_t *labels;
+};
+hipError_t launch_resolve(int rowtype, const ResolveArgs &a, int num_cus, hipStream_t s);
+
 // ---- int8 screening of uint8 rows (screen_i8.hip) ---------------------------
 // Quantised centroids: qc [cpad][2 * DP] int8 (plane H, then plane Ls), negb
 // [cpad] int32 (-B); cpad = C rounded up to 64, the padding scores lowest.
@@ -112,6 +150,8 @@ struct ScreenI8Args {
     // centroid ord1[p], and centroid c sits at plane row pos1[c]
     const uint32_t *ord1;
     const int32_t *pos1;
+    // near ties of the single plane (all null: decided or listed as above)
+    ResolveLists rs;
 };
 int64_t quantized_pad(int64_t C);
 // the single plane (qc1, negb1) is padded to whole staged chunks of 256
@@ -138,6 +178,9 @@ int64_t order1_parts(int64_t C);
 hipError_t launch_order1_keys(const float *cent, int64_t C, int D, double *part, float *mean, int32_t *keys,
                               hipStream_t s);
 hipError_t launch_screen_i8_single(int DP, const ScreenI8Args &a, int num_cus, hipStream_t s);
+// The plane rows within the window of each listed row's best (rs.cand); one
+// workgroup of eight waves per CU over (rows, chunk) units.
+hipError_t launch_collect_i8(int DP, const ScreenI8Args &a, int num_cus, hipStream_t s);
 
 // ---- norms, selection, fallbacks (select.hip) -----------------------------
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);

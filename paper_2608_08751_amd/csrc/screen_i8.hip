@@ -712,6 +712,27 @@ __global__ __launch_bounds__(W * 64, 2) void screen_i8_kernel(ScreenI8Args a)
         if (c <= (uint64_t)a.list_cap) {
             ids = a.list;
             n = c;
+            if (a.rs.list_thr) {
+                // collected and resolved but for the rows with too many
+                // candidates. A tile's scan of the whole table takes as long
+                // for one row as for 512 (1.6 ms at 65,536 x 128), the split
+                // fp64 scan 0.1 ms for 30 rows and 1 ms for 500: few rows go
+                // straight to that
+                ids = a.rs.list2;
+                n = *a.rs.list2_cnt;
+                if (n <= kResolveScanRows) {
+                    if (blockIdx.x == 0) {
+                        for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
+                            const int32_t r = ids[i];
+                            a.labels[r] = -1;
+                            const uint32_t slot = atomicAdd(a.wl_cnt, 1u);
+                            if (slot < (uint64_t)a.wl_cap) a.wl[slot] = r;
+                        }
+                        if (threadIdx.x == 0 && n) atomicAdd(a.stats + kStatFallback, (unsigned long long)n);
+                    }
+                    return;
+                }
+            }
         }
     }
     constexpr int rows_per_tile = W * 32 * rows_blocks<DP>();
@@ -1233,6 +1254,38 @@ __device__ __forceinline__ void s1_tile_test(const i32x16 &p, int idp, Top3i &st
     }
 }
 
+// The collecting pass over listed rows: every plane row whose score is at
+// least the row's threshold (its best score minus the window, so the nearest
+// centroid is among them) is queued in LDS, at most kResolveCand per lane (a
+// lane that meets more has overflowed its row's list whatever the other lane
+// finds; the count goes on).
+struct CollectState {
+    int thr;     // keep scores >= thr (INT_MAX: no row)
+    int qn;      // scores met
+    int32_t *q;  // this thread's queue, entry e at q[e * stride]
+    int stride;
+};
+
+__device__ __forceinline__ void s1_tile_test(const i32x16 &p, int idp, CollectState &st)
+{
+    const int m = max(max(max3i(max3i(p[0], p[1], p[2]), max3i(p[3], p[4], p[5]), max3i(p[6], p[7], p[8])),
+                          max3i(max3i(p[9], p[10], p[11]), max3i(p[12], p[13], p[14]), p[15])),
+                      kNoScore);
+    if (__builtin_expect(__any(m >= st.thr), 0)) {
+        uint32_t hit = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) hit |= p[r] >= st.thr ? 1u << r : 0u;
+        while (__any(hit != 0)) {
+            if (hit != 0) {
+                const int r = __builtin_ctz(hit);
+                if (st.qn < kResolveCand) st.q[st.qn * st.stride] = idp + 8 * (r >> 2) + (r & 3);
+                ++st.qn;
+                hit &= hit - 1u;
+            }
+        }
+    }
+}
+
 // K-step at which the previous block's row block rb is tested: one step
 // after an even spread, so that the test does not read an accumulator whose
 // last MFMA was issued just before (no wait states for its result).
@@ -1242,8 +1295,8 @@ constexpr int s1_test_step()
     return rb * KS / RB + 1 < KS ? rb * KS / RB + 1 : KS - 1;
 }
 
-template <int RB, int T, int KS, int rb = 0>
-__device__ __forceinline__ void s1_tests_at(const i32x16 (&p)[RB], int idp, Top3i (&st)[RB])
+template <int RB, int T, int KS, int rb = 0, class S>
+__device__ __forceinline__ void s1_tests_at(const i32x16 (&p)[RB], int idp, S (&st)[RB])
 {
     if constexpr (rb < RB) {
         if constexpr (s1_test_step<RB, KS, rb>() == T) s1_tile_test(p[rb], idp, st[rb]);
@@ -1256,9 +1309,9 @@ __device__ __forceinline__ void s1_tests_at(const i32x16 (&p)[RB], int idp, Top3
 // at T = 0. The epilogue of the previous block (p; ids from idp) runs between
 // the K-steps, and each fragment register is refilled from the next block
 // (nA, nB) as soon as its last MFMA has been issued.
-template <int DP, int RB, int T = 0>
+template <int DP, int RB, int T = 0, class S>
 __device__ __forceinline__ void s1_block(Frags1<DP> &f, const i32x4 (&x)[RB][DP / 32], i32x16 &bias,
-                                         i32x16 (&c)[RB], const i32x16 (&p)[RB], int idp, Top3i (&st)[RB],
+                                         i32x16 (&c)[RB], const i32x16 (&p)[RB], int idp, S (&st)[RB],
                                          const char *nA, const int *nB)
 {
     constexpr int KS = DP / 32;
@@ -1282,14 +1335,40 @@ __device__ __forceinline__ void s1_block(Frags1<DP> &f, const i32x4 (&x)[RB][DP 
     }
 }
 
+// Counters of one tile's unsettled rows (LDS) and their places in the call's
+// lists. One atomic per tile and list: with one per wave and row block, 250K
+// atomics on four neighbouring words bound an assignment against few
+// centroids (2M x 128 rows, 256 centroids: 1.86 ms, 0.45 with these).
+struct S1Tile {
+    uint32_t cnt[2];   // duels, listed rows of this tile
+    uint32_t base[2];  // their first slots in the lists
+};
+
+// What a row's three best scores decide.
+struct S1Verdict {
+    int kind;      // -1: nothing to list, 0: duel of c1 and c2, 1: listed
+    int c1, c2;
+    int thr;       // listed: scores >= thr can belong to the nearest centroid
+    uint32_t at;   // place among the tile's rows of this kind
+};
+
 // Merges the two half-lanes of a row and certifies with the window T:
-// settled rows get their label (two-way near-ties decided in fp64), the
-// others are listed for the two-plane screen. The scan's ids are plane rows;
-// one is used only when it names a real centroid, through the visiting
-// order. Equal scores may rank in plane-row order, which never decides a
-// label: a gap above T excludes ties, and the fp64 decision breaks them by
-// centroid id.
-__device__ __forceinline__ void s1_finish(const ScreenI8Args &a, int64_t row, bool rvalid, int h, const Top3i &st)
+// settled rows get their label, rows with two candidates are left to the
+// resolving kernel (or decided here when the call has no list of them), the
+// others are listed. The scan's ids are plane rows; one is used only when it
+// names a real centroid, through the visiting order. Equal scores may rank in
+// plane-row order, which never decides a label: a gap above T excludes ties,
+// and the fp64 decision breaks them by centroid id.
+__device__ __forceinline__ int s1_duel_here(const ScreenI8Args &a, int64_t row, int c1, int c2)
+{
+    const uint8_t *x = a.rows + row * (int64_t)a.D;
+    const double d1 = exact_dist(x, a.cent + (int64_t)c1 * a.D, a.D);
+    const double d2 = exact_dist(x, a.cent + (int64_t)c2 * a.D, a.D);
+    return dist_lt(d2, c2, d1, c1) ? c2 : c1;
+}
+
+__device__ __forceinline__ S1Verdict s1_finish(const ScreenI8Args &a, int64_t row, bool rvalid, int h, const Top3i &st,
+                                               S1Tile &tl)
 {
     Top3i o;
     o.k1 = __shfl_xor(st.k1, 32);
@@ -1298,34 +1377,76 @@ __device__ __forceinline__ void s1_finish(const ScreenI8Args &a, int64_t row, bo
     o.i1 = __shfl_xor(st.i1, 32);
     o.i2 = __shfl_xor(st.i2, 32);
     const Top3i m = top3i_merge(st, o);
-    int label = -1;
-    bool refined = false;
+    S1Verdict v{-1, 0, 0, INT_MAX, 0};
     if (rvalid && h == 0) {
         const int64_t T = st.twoR;
         const bool ok1 = m.i1 >= 0 && m.i1 < a.ncent;
         const bool ok2 = m.i2 >= 0 && m.i2 < a.ncent;
+        // a row whose best is not a real centroid collects nothing and goes on
+        v.thr = ok1 ? m.k1 - st.twoR : INT_MAX;
+        v.kind = 1;
         if (!a.force_rescreen && ok1) {
-            const int c1 = a.ord1 ? (int)a.ord1[m.i1] : m.i1;
+            v.c1 = a.ord1 ? (int)a.ord1[m.i1] : m.i1;
             if ((int64_t)m.k1 - (int64_t)m.k2 > T) {
-                label = c1;
+                v.kind = -1;
+                a.labels[row] = v.c1;
             } else if ((int64_t)m.k1 - (int64_t)m.k3 > T && ok2) {
-                const int c2 = a.ord1 ? (int)a.ord1[m.i2] : m.i2;
-                const uint8_t *x = a.rows + row * (int64_t)a.D;
-                const double d1 = exact_dist(x, a.cent + (int64_t)c1 * a.D, a.D);
-                const double d2 = exact_dist(x, a.cent + (int64_t)c2 * a.D, a.D);
-                label = dist_lt(d2, c2, d1, c1) ? c2 : c1;
-                refined = true;
+                v.c2 = a.ord1 ? (int)a.ord1[m.i2] : m.i2;
+                v.kind = 0;
             }
         }
-        if (label >= 0) a.labels[row] = label;
     }
-    // statistics and list slots: one atomic per wave; past the list's
-    // capacity the two-plane screen takes every row
-    const bool listed = rvalid && h == 0 && label < 0;
-    wave_count(a.stats + kStatRefine2, refined);
-    wave_count(a.stats + kStatRescreen, listed);
-    const uint32_t slot = wave_append(const_cast<uint32_t *>(a.list_cnt), listed);
-    if (listed && slot < (uint64_t)a.list_cap) const_cast<int32_t *>(a.list)[slot] = (int32_t)row;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const uint32_t at = wave_append(&tl.cnt[k], v.kind == k);
+        v.at = v.kind == k ? at : v.at;
+    }
+    return v;
+}
+
+// After every row block of the tile has its verdicts: the workgroup reserves
+// the list slots of its rows and writes them.
+template <int RB>
+__device__ __forceinline__ void s1_list(const ScreenI8Args &a, const int64_t (&row)[RB], const S1Verdict (&v)[RB],
+                                        S1Tile &tl)
+{
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t nd = tl.cnt[0], nl = tl.cnt[1];
+        if (nd) {
+            if (a.rs.duel_cnt) tl.base[0] = atomicAdd(a.rs.duel_cnt, nd);
+            atomicAdd(a.stats + kStatRefine2, (unsigned long long)nd);
+        }
+        if (nl) {
+            tl.base[1] = atomicAdd(const_cast<uint32_t *>(a.list_cnt), nl);
+            atomicAdd(a.stats + kStatRescreen, (unsigned long long)nl);
+        }
+        tl.cnt[0] = 0;
+        tl.cnt[1] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        if (v[rb].kind == 0) {
+            const uint64_t slot = (uint64_t)tl.base[0] + v[rb].at;
+            if (a.rs.duel_cnt && slot < (uint64_t)a.rs.duel_cap) {
+                a.rs.duel[slot] = make_uint2((uint32_t)row[rb], (uint32_t)v[rb].c1);
+                a.rs.duel2[slot] = v[rb].c2;
+            } else {
+                a.labels[row[rb]] = s1_duel_here(a, row[rb], v[rb].c1, v[rb].c2);
+            }
+        } else if (v[rb].kind == 1) {
+            // past the list's capacity the two-plane screen takes every row
+            const uint64_t slot = (uint64_t)tl.base[1] + v[rb].at;
+            if (slot < (uint64_t)a.list_cap) {
+                const_cast<int32_t *>(a.list)[slot] = (int32_t)row[rb];
+                if (a.rs.list_thr) {
+                    a.rs.list_thr[slot] = v[rb].thr;
+                    a.rs.cand_cnt[slot] = 0;
+                }
+            }
+        }
+    }
 }
 
 // Row blocks of 32 rows per wave in the single-plane screen: three at
@@ -1353,7 +1474,7 @@ __device__ __forceinline__ void for_each_index(F &&f, std::integer_sequence<int,
 // (that block refills its fragments from it) and then chunk j + 2 is
 // fetched into chunk j's buffer, which no wave reads any more.
 template <int DP, int W>
-__device__ void screen1_tile(const ScreenI8Args &a, int64_t tile, char *__restrict__ lds)
+__device__ void screen1_tile(const ScreenI8Args &a, int64_t tile, char *__restrict__ lds, S1Tile &tl)
 {
     static_assert(DP <= 128, "the single-plane screen keeps several row blocks per wave");
     constexpr int RB = s1_row_blocks<DP>();
@@ -1478,11 +1599,143 @@ __device__ void screen1_tile(const ScreenI8Args &a, int64_t tile, char *__restri
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) s1_tile_test(sb[rb], idh + (nch - 1) * kS1Chunk + 32 * (NB - 1), st[rb]);
 
+    int64_t row[RB];
+    S1Verdict v[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        const int64_t row = row0 + (wave * RB + rb) * 32 + jl;
-        s1_finish(a, row, row < a.nrows, h, st[rb]);
+        row[rb] = row0 + (wave * RB + rb) * 32 + jl;
+        v[rb] = s1_finish(a, row[rb], row[rb] < a.nrows, h, st[rb], tl);
     }
+    s1_list<RB>(a, row, v, tl);
+}
+
+// Chunks [ch_lo, ch_hi) of the plane against one tile of listed rows, with
+// the collecting epilogue; staging and MFMA stream are those of screen1_tile.
+// The rows a plain second screen would take (a window full of near ties) fill
+// few tiles, and a tile's scan of a 65,536-centroid table takes 1.6 ms however
+// few rows it holds; here the chunks of a tile are spread over workgroups,
+// which only a collecting epilogue allows (nothing to merge but a list).
+template <int DP, int W>
+__device__ void collect1_range(const ScreenI8Args &a, int64_t tile, int64_t n, int ch_lo, int ch_hi,
+                               char *__restrict__ lds, int32_t *__restrict__ queue)
+{
+    constexpr int RB = s1_row_blocks<DP>();
+    constexpr int NT = W * 64;
+    using St = QStager<DP, NT, 1>;
+    constexpr int CS = (St::kBytes + 15) / 16 * 16;
+    constexpr int SB = kS1Sub * CS;
+    constexpr int NB = 2 * kS1Sub;
+    constexpr int BLK = 32 * St::kPitch;
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int h = lane >> 5;
+    const int jl = lane & 31;
+    const int64_t row0 = tile * (W * 32 * RB);
+
+    i32x4 xf[RB][DP / 32];
+    uint32_t l1[RB];
+    int64_t rowid[RB];
+    load_rows_ids<DP, RB>(a.rows, a.nrows, a.list, row0, n, a.D, wave, jl, h, xf, l1, rowid);
+    CollectState st[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        st[rb].thr = rowid[rb] >= 0 ? a.rs.list_thr[row0 + (wave * RB + rb) * 32 + jl] : INT_MAX;
+        st[rb].qn = 0;
+        st[rb].q = queue + rb * kResolveCand * NT + threadIdx.x;
+        st[rb].stride = NT;
+    }
+
+    const char *A0 = lds + jl * St::kPitch + 16 * h;
+    const char *B0 = lds + St::kBias + 16 * h;
+    const int nch = ch_hi - ch_lo;
+    const int idh = 4 * h + ch_lo * kS1Chunk;
+    auto abuf = [&](int jj, int b) { return A0 + (jj & 1) * SB + (b >> 1) * CS + (b & 1) * BLK; };
+    auto bbuf = [&](int jj, int b) {
+        return reinterpret_cast<const int *>(B0 + (jj & 1) * SB + (b >> 1) * CS) + 32 * (b & 1);
+    };
+    St q;
+    q.init();
+    auto fetch = [&](int jj) {
+        char *buf = lds + (jj & 1) * SB;
+#pragma unroll
+        for (int u = 0; u < kS1Sub; ++u)
+            q.fetch(a.qc1, a.negb1, (int64_t)(ch_lo + jj) * kS1Chunk + u * kQChunk, a.cpad, buf + u * CS);
+    };
+    fetch(0);
+    __syncthreads();
+    fetch(1);
+
+    // set B starts as a block of lowest scores: the first epilogue keeps nothing
+    i32x16 sa[RB], sb[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sb[rb][r] = kNoScore;
+    i32x16 bias = load_bias(bbuf(0, 0));
+    Frags1<DP> f;
+    load_frags1<DP>(abuf(0, 0), f);
+    auto block = [&](int jj, auto bc) {
+        constexpr int b = decltype(bc)::value;
+        const char *nA = b + 1 < NB ? abuf(jj, b + 1) : abuf(jj + 1, 0);
+        const int *nB = b + 1 < NB ? bbuf(jj, b + 1) : bbuf(jj + 1, 0);
+        const int idp = idh + jj * kS1Chunk + 32 * b - 32;
+        if constexpr (b % 2 == 0)
+            s1_block<DP, RB>(f, xf, bias, sa, sb, idp, st, nA, nB);
+        else
+            s1_block<DP, RB>(f, xf, bias, sb, sa, idp, st, nA, nB);
+    };
+    for (int j = 0;; ++j) {
+        for_each_index([&](auto bc) { block(j, bc); }, std::make_integer_sequence<int, NB - 1>{});
+        __syncthreads();
+        fetch(j + 2);
+        block(j, std::integral_constant<int, NB - 1>{});
+        if (j + 1 == nch) break;
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        s1_tile_test(sb[rb], idh + (nch - 1) * kS1Chunk + 32 * (NB - 1), st[rb]);
+        if (st[rb].qn > 0) {
+            // thr < INT_MAX: a listed row, so its slots exist
+            const int64_t pos = row0 + (wave * RB + rb) * 32 + jl;
+            const uint32_t slot = atomicAdd(a.rs.cand_cnt + pos, (uint32_t)st[rb].qn);
+            for (int i = 0; i < st[rb].qn && i < kResolveCand && slot + i < (uint32_t)kResolveCand; ++i)
+                a.rs.cand[pos * kResolveCand + slot + i] = st[rb].q[i * NT];
+        }
+    }
+}
+
+template <int DP, int W>
+__global__ __launch_bounds__(W * 64, 2) void collect1_kernel(ScreenI8Args a)
+{
+    using St = QStager<DP, W * 64, 1>;
+    constexpr int CS = (St::kBytes + 15) / 16 * 16;
+    constexpr int RB = s1_row_blocks<DP>();
+    __shared__ __attribute__((aligned(16))) char lds[2 * kS1Sub * CS];
+    __shared__ int32_t queue[RB * kResolveCand * W * 64];
+    if (*a.q_bad || *a.q_bad1) return;
+    const int64_t n = *a.list_cnt;
+    if (n > a.list_cap) return;  // the two-plane screen takes every row
+    constexpr int rows_per_tile = W * 32 * RB;
+    const int64_t ntiles = (n + rows_per_tile - 1) / rows_per_tile;
+    // a contiguous range of (tile, chunk) units in tile-major order
+    const int64_t units = ntiles * a.nchunks;
+    int64_t u = units * blockIdx.x / gridDim.x;
+    const int64_t u1 = units * (blockIdx.x + 1) / gridDim.x;
+    while (u < u1) {
+        const int64_t tile = u / a.nchunks;
+        const int64_t ch = u - tile * a.nchunks;
+        const int64_t ch_end = min(a.nchunks, ch + (u1 - u));
+        collect1_range<DP, W>(a, tile, n, (int)ch, (int)ch_end, lds, queue);
+        u += ch_end - ch;
+        __syncthreads();
+    }
+}
+
+template <int DP>
+hipError_t launch_c1(const ScreenI8Args &a, int num_cus, hipStream_t s)
+{
+    hipLaunchKernelGGL((collect1_kernel<DP, 8>), dim3(num_cus), dim3(8 * 64), 0, s, a);
+    return hipGetLastError();
 }
 
 template <int DP, int W>
@@ -1491,11 +1744,13 @@ __global__ __launch_bounds__(W * 64, 2) void screen1_kernel(ScreenI8Args a)
     using St = QStager<DP, W * 64, 1>;
     constexpr int CS = (St::kBytes + 15) / 16 * 16;
     __shared__ __attribute__((aligned(16))) char lds[2 * kS1Sub * CS];
+    __shared__ S1Tile tl;
     if (*a.q_bad || *a.q_bad1) return;  // another screen takes every row
+    if (threadIdx.x == 0) tl.cnt[0] = tl.cnt[1] = 0;  // (the tile's barriers come before their first use)
     constexpr int rows_per_tile = W * 32 * s1_row_blocks<DP>();
     const int64_t ntiles = (a.nrows + rows_per_tile - 1) / rows_per_tile;
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        screen1_tile<DP, W>(a, tile, lds);
+        screen1_tile<DP, W>(a, tile, lds, tl);
         __syncthreads();
     }
 }
@@ -1565,6 +1820,21 @@ hipError_t launch_screen_i8_single(int DP, const ScreenI8Args &a0, int num_cus, 
     case 64: return launch_s1<64>(a, num_cus, s);
     case 96: return launch_s1<96>(a, num_cus, s);
     case 128: return launch_s1<128>(a, num_cus, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_collect_i8(int DP, const ScreenI8Args &a0, int num_cus, hipStream_t s)
+{
+    if (a0.nrows <= 0 || !a0.rs.list_thr) return hipErrorInvalidValue;
+    ScreenI8Args a = a0;
+    a.cpad = quantized_pad1(a0.ncent);
+    a.nchunks = a.cpad / kS1Chunk;
+    switch (DP) {
+    case 32: return launch_c1<32>(a, num_cus, s);
+    case 64: return launch_c1<64>(a, num_cus, s);
+    case 96: return launch_c1<96>(a, num_cus, s);
+    case 128: return launch_c1<128>(a, num_cus, s);
     default: return hipErrorInvalidValue;
     }
 }
