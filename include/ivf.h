@@ -23,8 +23,13 @@
  * error bound decides which candidates are re-evaluated in fp64 and when a
  * query or row falls back to an exact fp64 scan of all centroids. Which
  * matrix unit screens depends on the data type:
- *   - fp32 queries and rows: fp32 MFMA (v_mfma_f32_32x32x2_f32); the bound is
- *     the fp32 dot-product rounding bound for any summation order;
+ *   - fp32 queries and rows: f16 MFMA (v_mfma_f32_32x32x16_f16) on rows and
+ *     centroids scaled by a power of two and rounded to f16; the bound is made
+ *     of the measured rounding residuals and the rounding of the fp32 sums.
+ *     What its window leaves undecided, and data f16 cannot hold, is screened
+ *     on fp32 MFMA (v_mfma_f32_32x32x2_f32; the bound is the fp32 dot-product
+ *     rounding bound for any summation order), as are routing tables of at
+ *     most 2,048 centroids;
  *   - uint8 rows (k-means and assignment): int8 MFMA
  *     (v_mfma_i32_32x32x32_i8) on rows x - 128 against quantised centroids,
  *     whose integer scores are exact; the bound is the quantisation error
@@ -41,9 +46,9 @@
  *     against more than 2,048 centroids: the threshold-sample keys and the
  *     candidate filter run on the two int8 planes (x - 128 against
  *     rint(256 (c - 128))), with a bound of (390 + ||x - 128||_1) / 2 in the
- *     planes' key units; any other value in the call, or a centroid that does
- *     not quantise, sends the call to the fp32 kernels (device flag, no host
- *     synchronisation). IVF_OPT_FP32_SCREEN forces the fp32 kernels.
+ *     planes' key units; any other value in the call sends it to the f16, a
+ *     centroid that does not quantise to the fp32 kernels (device flag, no
+ *     host synchronisation). IVF_OPT_FP32_SCREEN forces the fp32 kernels.
  * Either way the results are the exact ones above; the screen chosen changes
  * speed only.
  *
@@ -218,8 +223,8 @@ ivf_status ivf_build_lists(ivf_ctx *ctx, const int32_t *labels, int64_t N, int64
  *   out[3] route: queries whose candidate list overflowed
  *   out[4] route: centroids in the threshold sample
  *   out[5] assignment of uint8 rows: 1 when screened on int8 MFMA
- *   out[6] assignment of uint8 rows: rows the single-plane int8 screen left
- *          with more than two possible centroids
+ *   out[6] assignment: rows the first screen (one int8 plane, or f16 for
+ *          fp32 rows) left with more than two possible centroids
  *   out[7] reserved (0) */
 ivf_status ivf_last_stats(ivf_ctx *ctx, int64_t out[8]);
 
@@ -235,26 +240,27 @@ ivf_status ivf_last_stats(ivf_ctx *ctx, int64_t out[8]);
  *   IVF_OPT_SCREEN_WAVES    wave64s per workgroup of the fp32 distance-
  *                           screening kernel, 4 or 8 (D > 128 always uses 4);
  *                           speed only, never results
- *   IVF_OPT_FP32_SCREEN     1 = uint8 rows, and uint8-valued queries in
- *                           ivf_route, are screened on fp32 MFMA like fp32
- *                           data (default 0: int8 MFMA whenever every
- *                           centroid coordinate c has rint(256 (c - 128)) in
- *                           [-32768, 32767], i.e. c in [0, 255.998]);
- *                           speed only, never results
+ *   IVF_OPT_FP32_SCREEN     1 = every row and query is screened on fp32 MFMA
+ *                           (default 0: int8 MFMA for uint8 rows and
+ *                           uint8-valued queries whenever every centroid
+ *                           coordinate c has rint(256 (c - 128)) in
+ *                           [-32768, 32767], i.e. c in [0, 255.998], f16 MFMA
+ *                           for fp32 rows and queries); speed only, never
+ *                           results
  *   IVF_OPT_I8_TWO_PLANE_ONLY  1 = no single-plane int8 pre-screen (default 0:
  *                           for D <= 128, uint8 rows are first screened on one
  *                           int8 plane rint(c - 128), which settles most rows
  *                           with half the MFMA work, when every coordinate has
  *                           rint(c - 128) in [-128, 127]); speed only
- *   IVF_OPT_FORCE_RESCREEN  1 = the single-plane screen settles no row: every
- *                           row goes on to the two-plane screen (results must
- *                           not change)
- *   IVF_OPT_RESCREEN_CAP    > 0: capacity of the single plane's list of rows
- *                           for the two-plane screen, which then takes them
+ *   IVF_OPT_FORCE_RESCREEN  1 = the first screen settles no row: every row
+ *                           goes on to the next one (two int8 planes, or fp32
+ *                           for fp32 rows; results must not change)
+ *   IVF_OPT_RESCREEN_CAP    > 0: capacity of the first screen's list of rows
+ *                           for the next one, which then takes them
  *                           (default 4,096 + N / 4, N / 16 from 2^26 rows on,
  *                           with the rows' candidates collected; past it the
- *                           two-plane screen takes every row); speed only,
- *                           never results
+ *                           next screen takes every row); speed only, never
+ *                           results
  *   IVF_OPT_ASSIGN_SLICE    > 0: rows per assignment slice, below the
  *                           default 2^28 (each slice is screened with its own
  *                           worklists); speed only, never results

@@ -4,6 +4,7 @@
 // synchronises with the host except ivf_sync and ivf_last_stats.
 #include <hip/hip_runtime.h>
 
+#include <math.h>
 #include <stdarg.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -135,10 +136,11 @@ size_t layout_adc(void *base, int64_t B, int64_t P, int64_t k, AdcScratch *w)
 // [1] worklist counter, [2] nonzero when some centroid does not quantise for
 // the int8 screen, [3] the same for its single plane, [4] the single plane's
 // largest coordinate residual (float bits), [5] counter of the rows the
-// single plane leaves to the two planes, [6] the int8 routing gate, [7] the
+// single plane leaves to the two planes, [6] nonzero when
+// the int8 planes do not take a routing call, [7] the
 // single plane's largest residual norm (float bits), [8] counter of the rows
-// with two candidates, [9] counter of the rows with too many, then (from word
-// 16) kNumStats uint64 counters.
+// with two candidates, [9] counter of the rows with too many, [10] and [11] see
+// ScalarWord, then (from word 16) kNumStats uint64 counters.
 struct Scalars {
     uint32_t *mc2_bits;
     uint32_t *wl_cnt;
@@ -191,7 +193,8 @@ struct RoutePlan {
     int64_t Ss;   // the sample: chunks j * Ss of kChunk centroids, j < Cs / kChunk
     int L;        // candidate capacity per query
     int rank_j;
-    int qdp;      // padded dimension of the int8 route planes; 0 = fp32 kernels only
+    int qdp;      // padded dimension of the int8 and f16 route planes; 0 = fp32 kernels only
+    int rank_safe, rank_max;  // f16 plane: see RouteArgs
 };
 
 RoutePlan plan_route(int64_t Q, int64_t C, int k, int rank_override, int D)
@@ -204,6 +207,7 @@ RoutePlan plan_route(int64_t Q, int64_t C, int k, int rank_override, int D)
         p.Ss = 1;
         p.L = pow2_ceil(std::max<int64_t>(C, k));
         p.rank_j = 0;
+        p.rank_safe = p.rank_max = 0;
         return p;
     }
     // sizes depend only on (Q, C, k); a rank override (a test knob) moves the
@@ -227,6 +231,13 @@ RoutePlan plan_route(int64_t Q, int64_t C, int k, int rank_override, int D)
     int L = pow2_ceil((int64_t)(2.5 * expected) + 1);
     L = std::max(L, std::max(512, pow2_ceil(k)));
     p.L = std::min(L, 4096);
+    // the k-th smallest key has sample rank k Cs / C on average: five standard
+    // deviations above that are safe; up to three quarters of a candidate list
+    // are expected below the last minimum the f16 window may reach
+    const double rk = (double)k * (double)Cs / (double)C;
+    p.rank_safe = (int)std::min<double>(r - 1, ceil(rk + 5.0 * sqrt(rk) + 3.0));
+    p.rank_max = (int)std::min<double>(64, floor(0.75 * p.L * (double)Cs / (double)C));
+    p.rank_max = std::max(p.rank_max, r);
     return p;
 }
 
@@ -265,8 +276,9 @@ RouteLayout layout_route(void *base, const RoutePlan &p, int64_t C)
     l.negb = nullptr;
     l.qbound = nullptr;
     if (p.qdp > 0) {
-        l.qc = c.take<int8_t>((size_t)quantized_pad(C) * 2 * p.qdp);
-        l.negb = c.take<int32_t>(quantized_pad(C));
+        // the two int8 planes or the f16 plane: one call uses one of them
+        l.qc = c.take<int8_t>((size_t)quantized_pad1(C) * 2 * p.qdp);
+        l.negb = c.take<int32_t>(quantized_pad1(C));
         l.qbound = c.take<float>(p.QB);
     }
     l.bytes = c.off + kAlign;
@@ -364,8 +376,9 @@ AssignLayout layout_assign(void *base, int64_t N, int64_t C, int qdp, bool need_
     l.sc = take_scalars(c);
     l.cnorm = c.take<float>(C);
     if (qdp > 0) {
-        l.qc = c.take<int8_t>((size_t)quantized_pad(C) * 2 * qdp);
-        l.negb = c.take<int32_t>(quantized_pad(C));
+        // the two int8 planes (uint8 rows) or the f16 plane (fp32 rows)
+        l.qc = c.take<int8_t>((size_t)quantized_pad1(C) * 2 * qdp);
+        l.negb = c.take<int32_t>(quantized_pad1(C));
         if (qdp <= 128) {
             l.qc1 = c.take<int8_t>((size_t)quantized_pad1(C) * qdp);
             l.negb1 = c.take<int32_t>(quantized_pad1(C));
@@ -377,18 +390,18 @@ AssignLayout layout_assign(void *base, int64_t N, int64_t C, int qdp, bool need_
             l.ooffsets = c.take<int64_t>(kOrder1Keys + 1);
             l.ord1 = c.take<uint32_t>(C);
             l.pos1 = c.take<int32_t>(C);
-            l.list_cap = rescreen_cap(std::min(N, kAssignSlice));
-            l.list = c.take<int32_t>(l.list_cap);
-            l.rs.duel_cap = duel_cap(std::min(N, kAssignSlice));
-            l.rs.duel = c.take<uint2>(l.rs.duel_cap);
-            l.rs.duel2 = c.take<int32_t>(l.rs.duel_cap);
-            l.rs.list_thr = c.take<int32_t>(l.list_cap);
-            l.rs.cand_cnt = c.take<uint32_t>(l.list_cap);
-            l.rs.cand = c.take<int32_t>((size_t)l.list_cap * kResolveCand);
-            l.rs.list2 = c.take<int32_t>(l.list_cap);
-            l.rs.duel_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 8 : nullptr;
-            l.rs.list2_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 9 : nullptr;
         }
+        l.list_cap = rescreen_cap(std::min(N, kAssignSlice));
+        l.list = c.take<int32_t>(l.list_cap);
+        l.rs.duel_cap = duel_cap(std::min(N, kAssignSlice));
+        l.rs.duel = c.take<uint2>(l.rs.duel_cap);
+        l.rs.duel2 = c.take<int32_t>(l.rs.duel_cap);
+        l.rs.list_thr = c.take<int32_t>(l.list_cap);
+        l.rs.cand_cnt = c.take<uint32_t>(l.list_cap);
+        l.rs.cand = c.take<int32_t>((size_t)l.list_cap * kResolveCand);
+        l.rs.list2 = c.take<int32_t>(l.list_cap);
+        l.rs.duel_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 8 : nullptr;
+        l.rs.list2_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 9 : nullptr;
     }
     l.wl_cap = worklist_cap(std::min(N, kAssignSlice));
     l.wl = c.take<int32_t>(l.wl_cap);
@@ -515,12 +528,14 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
     TIMED("fill", launch_fill_u32(l.sc.mc2_bits, 64, 0u, s));
     TIMED("centroid_norms", launch_centroid_norms(cent, C, D, l.cnorm, l.sc.mc2_bits, s));
     const bool int8 = rowtype == kRowU8 && !ctx->fp32_screen;
+    const bool f16 = rowtype == kRowF32 && !ctx->fp32_screen && l.list;
     const bool single = int8 && l.qc1 && !ctx->two_plane_only;
     uint32_t *q_bad = l.sc.mc2_bits + 2;
     uint32_t *q_bad1 = l.sc.mc2_bits + 3;
     uint32_t *e_bits = l.sc.mc2_bits + 4;
     uint32_t *list_cnt = l.sc.mc2_bits + 5;
     uint32_t *r2_bits = l.sc.mc2_bits + 7;
+    uint32_t *rc_bits = l.sc.mc2_bits + kWordF16Rc;
     const uint32_t *ord1 = nullptr;
     const int32_t *pos1 = nullptr;
     if (int8) {
@@ -545,6 +560,9 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
             pos1 = ordered ? l.pos1 : nullptr;
         }
     }
+    uint16_t *plane16 = (uint16_t *)l.qc;
+    float *bias16 = (float *)l.negb;
+    if (f16) TIMED("quantize_f16", launch_quantize_f16(cent, C, D, DP, l.sc.mc2_bits, plane16, bias16, rc_bits, s));
     for (int64_t r0 = 0; r0 < N; r0 += slice) {
         const int64_t n = std::min(slice, N - r0);
         const void *xr = (const char *)rows + (size_t)r0 * rb;
@@ -552,7 +570,7 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
         if (r0 > 0) {
             // the worklist and the single plane's list start empty for every slice
             TIMED("fill", launch_fill_u32(l.sc.wl_cnt, 1, 0u, s));
-            if (single) {
+            if (single || f16) {
                 TIMED("fill", launch_fill_u32(list_cnt, 1, 0u, s));
                 TIMED("fill", launch_fill_u32(l.rs.duel_cnt, 2, 0u, s));
             }
@@ -574,6 +592,52 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
         a.wl_cap = l.wl_cap;
         a.stats = l.sc.stats;
         a.force_fallback = ctx->force_fallback;
+        auto resolve_args = [&](const ResolveLists &rs, int64_t cap, const uint32_t *ord) {
+            ResolveArgs ra{};
+            ra.rows = xr;
+            ra.nrows = n;
+            ra.D = D;
+            ra.cent = cent;
+            ra.C = C;
+            ra.ord = ord;
+            ra.list = l.list;
+            ra.list_cnt = list_cnt;
+            ra.list_cap = cap;
+            ra.rs = rs;
+            ra.labels = lab;
+            return ra;
+        };
+        if (f16) {
+            ScreenF16Args q{};
+            q.rows = (const float *)xr;
+            q.nrows = n;
+            q.D = D;
+            q.cent = cent;
+            q.plane = plane16;
+            q.nbias = bias16;
+            q.mc2_bits = l.sc.mc2_bits;
+            q.rc_bits = rc_bits;
+            q.acc_coef = f16_acc_coef(DP);
+            q.ncent = C;
+            q.cpad = quantized_pad1(C);
+            q.labels = lab;
+            q.stats = l.sc.stats;
+            q.list = l.list;
+            q.list_cnt = list_cnt;
+            q.list_cap = ctx->rescreen_cap > 0 ? std::min<int64_t>(ctx->rescreen_cap, l.list_cap) : l.list_cap;
+            q.rs = l.rs;
+            // a forced fallback passes every row on to the fp32 screen, which sends it on
+            q.force_list = ctx->force_rescreen || ctx->force_fallback;
+            const bool collect = !q.force_list && ctx->rescreen_cap == 0;
+            if (!collect) q.rs.list_thr = nullptr;
+            TIMED("screen_top1_f16", launch_screen_f16(DP, q, ctx->num_cus, s));
+            if (collect) TIMED("collect_f16", launch_collect_f16(DP, q, ctx->num_cus, s));
+            TIMED("resolve", launch_resolve(rowtype, resolve_args(q.rs, q.list_cap, nullptr), ctx->num_cus, s));
+            a.list = l.list;
+            a.list_cnt = list_cnt;
+            a.list_cap = q.list_cap;
+            a.rs = q.rs;
+        }
         if (int8) {
             ScreenI8Args q{};
             q.rows = (const uint8_t *)xr;
@@ -615,19 +679,7 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
                 if (!collect) q.rs.list_thr = nullptr;
                 TIMED("screen_top1_i8s", launch_screen_i8_single(DP, q, ctx->num_cus, s));
                 if (collect) TIMED("collect_i8", launch_collect_i8(DP, q, ctx->num_cus, s));
-                ResolveArgs ra{};
-                ra.rows = xr;
-                ra.nrows = n;
-                ra.D = D;
-                ra.cent = cent;
-                ra.C = C;
-                ra.ord = ord1;
-                ra.list = l.list;
-                ra.list_cnt = list_cnt;
-                ra.list_cap = q.list_cap;
-                ra.rs = q.rs;
-                ra.labels = lab;
-                TIMED("resolve", launch_resolve(rowtype, ra, ctx->num_cus, s));
+                TIMED("resolve", launch_resolve(rowtype, resolve_args(q.rs, q.list_cap, ord1), ctx->num_cus, s));
             }
             TIMED("screen_top1_i8", launch_screen_i8(DP, q, ctx->num_cus, s));
             a.gate = q_bad;
@@ -926,30 +978,32 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
     const int DP = padded_dim(D);
     TIMED("fill", launch_fill_u32(l.sc.mc2_bits, 64, 0u, s));
     TIMED("centroid_norms", launch_centroid_norms(centroids, C, D, l.cnorm, l.sc.mc2_bits, s));
-    // uint8-valued queries are routed on the two int8 planes; the fp32
-    // kernels run instead (device flag, no host synchronisation) when a query
-    // or a centroid does not fit them. Tables small enough to be candidates
-    // whole (no threshold sample) stay on the fp32 kernels: there the screen
-    // only copies every centroid into the candidate list.
-    const bool i8 = p.qdp > 0 && p.Cs > 0 && !ctx->fp32_screen;
-    uint32_t *q_bad = l.sc.mc2_bits + 2;
-    uint32_t *i8_off = l.sc.mc2_bits + 6;
-    if (i8) {
-        TIMED("route_i8_check", launch_route_i8_check(queries, Q, D, i8_off, s));
-        TIMED("quantize", launch_quantize_centroids(centroids, C, D, p.qdp, l.qc, l.negb, q_bad, s, i8_off));
+    // uint8-valued queries are routed on the two int8 planes, other queries on
+    // the f16 plane; the fp32 kernels run instead (device words, no host
+    // synchronisation) when a centroid does not fit the int8 planes or the f16
+    // window is too wide. Tables small enough to be candidates whole (no
+    // threshold sample) stay on the fp32 kernels: there the screen only copies
+    // every centroid into the candidate list.
+    const bool planes = p.qdp > 0 && p.Cs > 0 && !ctx->fp32_screen;
+    uint32_t *w = l.sc.mc2_bits;
+    if (planes) {
+        TIMED("route_i8_check", launch_route_i8_check(queries, Q, D, w + kWordNotI8, s));
+        TIMED("quantize", launch_quantize_centroids(centroids, C, D, p.qdp, l.qc, l.negb, w + kWordQBad, s,
+                                                    w + kWordNotI8, w));
     }
     for (int64_t q0 = 0; q0 < Q; q0 += p.QB) {
         const int64_t nb = std::min(p.QB, Q - q0);
         const float *qrows = queries + q0 * D;
-        TIMED("fill", launch_fill_u32(l.sc.wl_cnt, 1, 0u, s));
-        TIMED("row_norms", launch_row_norms(qrows, nb, D, l.qn2, s));
+        TIMED("route_bound", launch_route_i8_bound(qrows, nb, D, planes ? w + kWordQBad : nullptr,
+                                                   planes ? w + kWordNotI8 : nullptr, planes ? l.qbound : nullptr, s,
+                                                   w, f16_acc_coef(DP), l.qn2));
         ScreenArgs a{};
         a.rows = qrows;
         a.nrows = nb;
         a.D = D;
         a.cent = centroids;
         a.cnorm = l.cnorm;
-        a.gate = i8 ? i8_off : nullptr;
+        a.route_w = planes ? w : nullptr;
         RouteI8Args ra{};
         ra.queries = qrows;
         ra.nq = nb;
@@ -957,26 +1011,17 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
         ra.qc = l.qc;
         ra.negb = l.negb;
         ra.cpad = quantized_pad(C);
-        ra.off = i8_off;
+        ra.off = w + kWordNotI8;
         ra.stats = l.sc.stats;
-        if (i8) TIMED("route_i8_bound", launch_route_i8_bound(qrows, nb, D, q_bad, i8_off, l.qbound, s));
-        if (p.Cs > 0) {
-            a.c_begin = 0;
-            a.c_end = C;
-            a.nchunks = p.Cs / kChunk;
-            a.cstride = p.Ss;
-            a.keys = l.keys;
-            a.kmin = l.kmin;
-            if (i8) {
-                ra.c_begin = 0;
-                ra.c_end = p.Cs;
-                ra.nchunks = p.Cs / kQuantChunk;
-                ra.cstride = p.Ss;
-                ra.keys = l.keys;
-                TIMED("route_i8_keys", launch_route_i8(kRouteKeys, p.qdp, ra, ctx->num_cus, s));
-            }
-            TIMED("screen_keys", launch_screen(kModeKeys, kRowF32, DP, a, ctx->screen_waves, ctx->num_cus, s));
-        }
+        RouteF16Args rf{};
+        rf.queries = qrows;
+        rf.nq = nb;
+        rf.D = D;
+        rf.plane = (const uint16_t *)l.qc;
+        rf.nbias = (const float *)l.negb;
+        rf.mc2_bits = l.sc.mc2_bits;
+        rf.w = w;
+        rf.cpad = quantized_pad1(C);
         RouteArgs r{};
         r.queries = qrows;
         r.nq = nb;
@@ -988,6 +1033,8 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
         r.Cs = p.Cs;
         r.sstride = p.Ss;
         r.rank_j = p.rank_j;
+        r.rank_safe = p.rank_safe;
+        r.rank_max = p.rank_max;
         r.keys = l.keys;
         r.kmin = l.kmin;
         r.tau = l.tau;
@@ -1002,8 +1049,49 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
         r.wl = l.wl;
         r.wl_cnt = l.sc.wl_cnt;
         r.stats = l.sc.stats;
-        r.i8_off = i8 ? i8_off : nullptr;
+        r.w = planes ? w : nullptr;
         r.qbound = l.qbound;
+        if (planes) {
+            // the planes' sample minima (in the keys buffer), threshold and
+            // filter over every centroid
+            ra.c_begin = 0;
+            ra.c_end = p.Cs;
+            ra.nchunks = p.Cs / kQuantChunk;
+            ra.cstride = p.Ss;
+            ra.keys = l.keys;
+            TIMED("route_i8_keys", launch_route_i8(kRouteKeys, p.qdp, ra, ctx->num_cus, s));
+            rf.nsub = p.Cs / kQuantChunk;
+            rf.cstride = p.Ss;
+            rf.kmin = l.keys;
+            TIMED("route_f16_keys", launch_route_f16(kRouteKeys, p.qdp, rf, ctx->num_cus, s));
+            TIMED("route_threshold_min", launch_route_threshold_min(r, s));
+            ra.c_end = C;
+            ra.nchunks = (C + kQuantChunk - 1) / kQuantChunk;
+            ra.cstride = 1;
+            ra.keys = nullptr;
+            ra.tau = l.tau;
+            ra.cand_cnt = l.cand_cnt;
+            ra.cand = l.cand;
+            ra.L = p.L;
+            TIMED("route_i8_filter", launch_route_i8(kRouteFilter, p.qdp, ra, ctx->num_cus, s));
+            rf.nsub = rf.cpad / kQuantChunk;
+            rf.cstride = 1;
+            rf.kmin = nullptr;
+            rf.tau = l.tau;
+            rf.cand_cnt = l.cand_cnt;
+            rf.cand = l.cand;
+            rf.L = p.L;
+            TIMED("route_f16_filter", launch_route_f16(kRouteFilter, p.qdp, rf, ctx->num_cus, s));
+        }
+        if (p.Cs > 0) {
+            a.c_begin = 0;
+            a.c_end = C;
+            a.nchunks = p.Cs / kChunk;
+            a.cstride = p.Ss;
+            a.keys = l.keys;
+            a.kmin = l.kmin;
+            TIMED("screen_keys", launch_screen(kModeKeys, kRowF32, DP, a, ctx->screen_waves, ctx->num_cus, s));
+        }
         TIMED("route_threshold", launch_route_threshold(r, s));
         if (p.Cs < C) {
             // every chunk the sample left
@@ -1018,19 +1106,6 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
             a.cand_cnt = l.cand_cnt;
             a.cand = l.cand;
             a.L = p.L;
-            if (i8) {
-                // the int8 threshold emits no sample candidates: the filter covers every centroid
-                ra.c_begin = 0;
-                ra.c_end = C;
-                ra.nchunks = (C + kQuantChunk - 1) / kQuantChunk;
-                ra.cstride = 1;
-                ra.keys = nullptr;
-                ra.tau = l.tau;
-                ra.cand_cnt = l.cand_cnt;
-                ra.cand = l.cand;
-                ra.L = p.L;
-                TIMED("route_i8_filter", launch_route_i8(kRouteFilter, p.qdp, ra, ctx->num_cus, s));
-            }
             TIMED("screen_filter", launch_screen(kModeFilter, kRowF32, DP, a, ctx->screen_waves, ctx->num_cus, s));
         }
         TIMED("route_select", launch_route_select(r, s));
@@ -1087,7 +1162,9 @@ ivf_status ivf_route_noalloc(ivf_ctx *ctx, const float *queries, int64_t Q, cons
         return fail(ctx, IVF_EUNSUPPORTED,
                     "route_noalloc: C = %lld, nprobe = %d need %zu bytes of scratch for one query; the static "
                     "scratch holds %zu", (long long)C, nprobe, one, kStaticScratchBytes);
-    const size_t per_query = layout_route(nullptr, RoutePlan{2, p.Cs, p.L, p.rank_j, p.qdp}, C).bytes - one;
+    RoutePlan two = p;
+    two.QB = 2;
+    const size_t per_query = layout_route(nullptr, two, C).bytes - one;
     const int64_t fit = 1 + (int64_t)((kStaticScratchBytes - one) / std::max<size_t>(per_query, 1));
     if (p.QB > fit) p.QB = fit >= 64 ? fit / 32 * 32 : fit;
     while (p.QB > 1 && layout_route(nullptr, p, C).bytes > kStaticScratchBytes) --p.QB;

@@ -14,6 +14,22 @@ namespace ivf {
 // workgroups run per CU (two waves per SIMD).
 constexpr int kChunk = 64;
 
+// Words of the workspace's scalar area that more than one kernel uses.
+enum ScalarWord {
+    kWordMc2 = 0,       // max_j fl32(||c_j||^2) as float bits
+    kWordWorklist = 1,  // fallback worklist counter
+    kWordQBad = 2,      // some centroid does not fit the two int8 planes
+    kWordNotI8 = 6,     // routing: the int8 planes do not take the call
+    kWordF16Rc = 10,    // largest residual norm of the f16 plane (float bits)
+    kWordF16Off = 11,   // routing: the f16 window is too wide for some query of the batch
+};
+// Which kernels screen a routing batch that has planes.
+enum RouteMode { kModeI8 = 0, kModeF16 = 1, kModeF32 = 2 };
+__device__ __forceinline__ int route_mode(const uint32_t *w)
+{
+    return w[kWordNotI8] == 0u ? kModeI8 : w[kWordF16Off] == 0u ? kModeF16 : kModeF32;
+}
+
 enum ScreenMode { kModeKeys = 0, kModeFilter = 1, kModeTop1 = 2 };
 enum RowType { kRowF32 = 0, kRowU8 = 1 };
 
@@ -29,6 +45,29 @@ enum StatSlot {
     kNumStats = 8
 };
 
+// ---- near ties the one-pass screens leave (resolve.hip) ----------------------
+// A one-pass screen (the single int8 plane, the f16 plane) settles the rows
+// whose best score stands clear of the others by its window. Rows with exactly two
+// centroids inside the window are "duels"; rows with more are listed with the
+// score a candidate must reach, collected by a second pass over the plane and
+// resolved here, both by the exact fp64 distances of the candidates.
+constexpr int kResolveCand = 8;       // candidates kept per listed row
+constexpr int kResolveScanRows = 512; // at most this many overflowed rows go to the fp64 scan directly
+struct ResolveLists {
+    // duels: (row, first centroid) and the second centroid
+    uint2 *duel;
+    int32_t *duel2;
+    uint32_t *duel_cnt;   // null: duels are decided by the screen itself
+    int64_t duel_cap;
+    // listed rows: threshold (int score or float bits), candidates met,
+    // their plane rows
+    int32_t *list_thr;    // null: listed rows go to the next screen
+    uint32_t *cand_cnt;
+    int32_t *cand;        // [list_cap][kResolveCand]
+    // rows with more candidates than kResolveCand (or none)
+    int32_t *list2;
+    uint32_t *list2_cnt;
+};
 struct ScreenArgs {
     const void *rows;       // [nrows, D] fp32 or u8
     int64_t nrows;
@@ -64,35 +103,20 @@ struct ScreenArgs {
     // when non-null and *gate == 0, the int8 screen has taken the call and
     // this kernel returns at once
     const uint32_t *gate;
+    // routing: when non-null, this kernel runs only while route_mode(route_w)
+    // is kModeF32
+    const uint32_t *route_w;
+    // top-1: rows left by a one-pass screen (null: every row); see pick_rows
+    const int32_t *list;
+    const uint32_t *list_cnt;
+    int64_t list_cap;
+    ResolveLists rs;
 };
 
 // waves: 4 or 8 per workgroup; the grid fills every CU with two waves per SIMD.
 hipError_t launch_screen(int mode, int rowtype, int DP, const ScreenArgs &a, int waves, int num_cus,
                          hipStream_t s);
 
-// ---- near ties the one-pass screens leave (resolve.hip) ----------------------
-// A one-pass screen (single int8 plane) settles the rows whose
-// best score stands clear of the others by its window. Rows with exactly two
-// centroids inside the window are "duels"; rows with more are listed with the
-// score a candidate must reach, collected by a second pass over the plane and
-// resolved here, both by the exact fp64 distances of the candidates.
-constexpr int kResolveCand = 8;       // candidates kept per listed row
-constexpr int kResolveScanRows = 512; // at most this many overflowed rows go to the fp64 scan directly
-struct ResolveLists {
-    // duels: (row, first centroid) and the second centroid
-    uint2 *duel;
-    int32_t *duel2;
-    uint32_t *duel_cnt;   // null: duels are decided by the screen itself
-    int64_t duel_cap;
-    // listed rows: threshold (int score or float bits), candidates met,
-    // their plane rows
-    int32_t *list_thr;    // null: listed rows go to the next screen
-    uint32_t *cand_cnt;
-    int32_t *cand;        // [list_cap][kResolveCand]
-    // rows with more candidates than kResolveCand (or none)
-    int32_t *list2;
-    uint32_t *list2_cnt;
-};
 struct ResolveArgs {
     const void *rows;     // [nrows, D] fp32 or uint8
     int64_t nrows;
@@ -156,9 +180,12 @@ struct ScreenI8Args {
 int64_t quantized_pad(int64_t C);
 // the single plane (qc1, negb1) is padded to whole staged chunks of 256
 int64_t quantized_pad1(int64_t C);
-// skip (may be null): when *skip is nonzero the kernel does nothing
+// skip (may be null): when *skip is nonzero the kernel does nothing, or, with
+// the scalar words w, builds the f16 plane in the same memory (then of
+// quantized_pad1(C) rows)
 hipError_t launch_quantize_centroids(const float *cent, int64_t C, int D, int DP, int8_t *qc, int32_t *negb,
-                                     uint32_t *q_bad, hipStream_t s, const uint32_t *skip = nullptr);
+                                     uint32_t *q_bad, hipStream_t s, const uint32_t *skip = nullptr,
+                                     uint32_t *w = nullptr);
 // Eight waves per workgroup (two per SIMD), one workgroup per CU.
 hipError_t launch_screen_i8(int DP, const ScreenI8Args &a, int num_cus, hipStream_t s);
 // Single-plane int8 screen (DP <= 128): plane rint(c - 128) [quantized_pad1(C)][DP],
@@ -186,7 +213,6 @@ hipError_t launch_collect_i8(int DP, const ScreenI8Args &a, int num_cus, hipStre
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_centroid_norms(const float *cent, int64_t C, int D, float *cnorm,
                                  uint32_t *mc2_bits, hipStream_t s);
-hipError_t launch_row_norms(const float *rows, int64_t n, int D, double *out, hipStream_t s);
 
 struct RouteArgs {
     const float *queries;  // [nq, D] (already offset to the batch)
@@ -213,18 +239,24 @@ struct RouteArgs {
     int32_t *wl;            // [nq]
     uint32_t *wl_cnt;
     unsigned long long *stats;
-    // keys from the int8 route kernels while *i8_off == 0 (null: fp32 only):
-    // their per-query bound qbound replaces the fp32 key bound
-    const uint32_t *i8_off;
+    // scalar words (null: fp32 kernels only): while route_mode(w) is not
+    // kModeF32 the keys come from a plane and their per-query bound qbound
+    // replaces the fp32 key bound
+    uint32_t *w;
     const float *qbound;    // [nq]
+    // f16 plane: the threshold covers the window above the rank_safe-th
+    // smallest group minimum, and the batch goes to the fp32 kernels when that
+    // lies above the rank_max-th
+    int rank_safe, rank_max;
 };
 
 hipError_t launch_route_threshold(const RouteArgs &a, hipStream_t s);
+hipError_t launch_route_threshold_min(const RouteArgs &a, hipStream_t s);  // a.w set
 // Int8 routing of uint8-valued queries on the two quantised planes
 // (screen_i8.hip): keys of the threshold sample and the candidate filter,
 // run only while *off == 0; route_i8_check raises *off when some query value
-// is not an integer in [0, 255], route_i8_bound when *q_bad is set, and
-// writes the per-query bound of the int8 keys.
+// is not an integer in [0, 255], route_i8_bound when *q_bad is set; the latter
+// writes the per-query bound of the planes' keys.
 constexpr int kQuantChunk = 64;  // centroids per staged chunk of the two-plane kernels
 constexpr int kRouteKeys = 0;
 constexpr int kRouteFilter = 1;
@@ -247,12 +279,61 @@ struct RouteI8Args {
     unsigned long long *stats;  // [kStatScreenI8] = 1 when the int8 filter ran
 };
 hipError_t launch_route_i8_check(const float *queries, int64_t nq, int D, uint32_t *off, hipStream_t s);
+// q_bad and off null: no int8 planes; qbound null: no planes at all; w: the
+// scalar words of a library call (acc = f16_acc_coef), qn2: ||q||^2
 hipError_t launch_route_i8_bound(const float *queries, int64_t nq, int D, const uint32_t *q_bad, uint32_t *off,
-                                 float *qbound, hipStream_t s);
+                                 float *qbound, hipStream_t s, uint32_t *w = nullptr, double acc = 0.0,
+                                 double *qn2 = nullptr);
 hipError_t launch_route_i8(int mode, int DP, const RouteI8Args &a, int num_cus, hipStream_t s);
 hipError_t launch_route_select(const RouteArgs &a, hipStream_t s);
 hipError_t launch_route_fallback(const RouteArgs &a, int grid, hipStream_t s);
 
+// ---- f16 screening of fp32 rows and queries (screen_f16.hip) -----------------
+// The f16 plane [quantized_pad1(C)][DP] and its biases; *rc_bits zeroed by the
+// caller.
+hipError_t launch_quantize_f16(const float *cent, int64_t C, int D, int DP, const uint32_t *mc2_bits, uint16_t *plane,
+                               float *nbias, uint32_t *rc_bits, hipStream_t s);
+double f16_acc_coef(int DP);  // accumulation term of the bound
+struct ScreenF16Args {
+    const float *rows;      // [nrows, D]
+    int64_t nrows;
+    int D;
+    const float *cent;      // [C, D] (exact re-evaluation)
+    const uint16_t *plane;
+    const float *nbias;
+    const uint32_t *mc2_bits, *rc_bits;
+    double acc_coef;
+    int64_t cpad, ncent;    // cpad = quantized_pad1(ncent)
+    int32_t *labels;
+    unsigned long long *stats;
+    // rows left over; past list_cap entries the fp32 screen takes every row
+    const int32_t *list;
+    const uint32_t *list_cnt;
+    int64_t list_cap;
+    ResolveLists rs;
+    int force_list;         // 1: settle no row
+};
+// Eight waves per workgroup (two per SIMD), one workgroup per CU.
+hipError_t launch_screen_f16(int DP, const ScreenF16Args &a, int num_cus, hipStream_t s);
+hipError_t launch_collect_f16(int DP, const ScreenF16Args &a, int num_cus, hipStream_t s);
+struct RouteF16Args {
+    const float *queries;   // [nq, D]
+    int64_t nq;
+    int D;
+    const uint16_t *plane;
+    const float *nbias;
+    const uint32_t *mc2_bits;
+    const uint32_t *w;      // runs while route_mode(w) is kModeF16
+    int64_t cpad;
+    int64_t nsub;           // sub-chunks of 64 centroids visited
+    int64_t cstride;        // keys: sub-chunk k of the visit is k * cstride (at least 1)
+    float *kmin;            // keys: group minima [nq, 4 nsub]
+    const float *tau;       // filter (every sub-chunk): [nq], lists [nq, L]
+    uint32_t *cand_cnt;
+    uint2 *cand;
+    int L;
+};
+hipError_t launch_route_f16(int mode, int DP, const RouteF16Args &a, int num_cus, hipStream_t s);
 // Exact fp64 scan of the rows on the assignment worklist (labels -1). The
 // first kFbSplitWindows windows of 8 rows are split into kFbSeg centroid
 // segments over the whole grid; split_d / split_i hold their partial

@@ -20,6 +20,7 @@
 // holds centroid 8*(r/4) + 4*(l/32) + r%4 of the block.
 #include "ivf_internal.h"
 #include "exact.h"
+#include "tile_lists.h"
 #include "wave_ops.h"
 
 #include <math.h>
@@ -373,8 +374,8 @@ __device__ __forceinline__ void top1_finish(const ScreenArgs &a, int64_t row, bo
 }
 
 template <int DP, int W, typename XT>
-__device__ void screen_top1(const ScreenArgs &a, int64_t tile, float *__restrict__ lds_c,
-                            float *__restrict__ lds_n)
+__device__ void screen_top1(const ScreenArgs &a, int64_t tile, const int32_t *ids, int64_t nrows,
+                            float *__restrict__ lds_c, float *__restrict__ lds_n)
 {
     constexpr int NT = W * 64;
     constexpr int KH = DP / 2;
@@ -383,8 +384,9 @@ __device__ void screen_top1(const ScreenArgs &a, int64_t tile, float *__restrict
     const int wave = threadIdx.x >> 6;
     const int h = lane >> 5;
     const int jl = lane & 31;
-    const int64_t row = tile * (32 * W) + wave * 32 + jl;
-    const bool rvalid = row < a.nrows;
+    const int64_t pos = tile * (32 * W) + wave * 32 + jl;
+    const int64_t row = pos < nrows ? (ids ? (int64_t)ids[pos] : pos) : a.nrows;
+    const bool rvalid = row >= 0 && row < a.nrows;
 
     float b[KH];
     load_row<DP>(reinterpret_cast<const XT *>(a.rows), row, rvalid, a.D, h, b);
@@ -798,14 +800,19 @@ __global__ __launch_bounds__(W * 64, waves_per_simd<DP>()) void screen_kernel(Sc
 {
     __shared__ __attribute__((aligned(16))) float lds_c[2 * kChunk * (DP + 4)];
     __shared__ __attribute__((aligned(16))) float lds_n[2 * kChunk];
-    const int64_t ntiles = (a.nrows + 32 * W - 1) / (32 * W);
     if (a.gate && *a.gate == 0u) return;  // screened on int8 MFMA instead
     if constexpr (MODE == kModeTop1) {
+        const int32_t *ids = nullptr;
+        int64_t n = a.nrows;
+        if (a.list && !pick_rows(a, ids, n)) return;
+        const int64_t ntiles = (n + 32 * W - 1) / (32 * W);
         for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-            screen_top1<DP, W, XT>(a, tile, lds_c, lds_n);
+            screen_top1<DP, W, XT>(a, tile, ids, n, lds_c, lds_n);
             __syncthreads();
         }
     } else {
+        if (a.route_w && route_mode(a.route_w) != kModeF32) return;  // a plane takes the batch
+        const int64_t ntiles = (a.nrows + 32 * W - 1) / (32 * W);
         // a contiguous range of (tile, chunk) units in tile-major order
         const int64_t units = ntiles * a.nchunks;
         int64_t u = units * blockIdx.x / gridDim.x;

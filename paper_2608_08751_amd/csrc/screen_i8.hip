@@ -32,7 +32,10 @@
 // centroid 8 (r / 4) + 4 (l / 32) + r % 4 of the block for row l % 32.
 #include "exact.h"
 #include "wave_ops.h"
+#include "f16_bound.h"
 #include "ivf_internal.h"
+#include "qstage.h"
+#include "tile_lists.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -44,7 +47,6 @@ namespace {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kQChunk = kQuantChunk;  // centroids per staged chunk (sub-chunk of the single plane)
 constexpr int kS1Sub = 4;            // 64-centroid sub-chunks per staged chunk of the single plane
 constexpr int kS1Chunk = kS1Sub * kQChunk;
 constexpr int kOrder1PartRows = 32;  // centroids per column-sum block of the visiting order
@@ -67,9 +69,15 @@ constexpr int rows_blocks()
 __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__ cent, int64_t C, int D,
                                                        int DP, int64_t Cpad, int8_t *__restrict__ qc,
                                                        int32_t *__restrict__ negb, uint32_t *__restrict__ q_bad,
-                                                       const uint32_t *__restrict__ skip)
+                                                       const uint32_t *__restrict__ skip, float *nbias16,
+                                                       const uint32_t *__restrict__ mc2_bits,
+                                                       uint32_t *__restrict__ rc_bits, int64_t Cpad16)
 {
-    if (skip && *skip) return;  // no int8 screen reads the planes in this call
+    if (skip && *skip) {  // no int8 screen reads the planes in this call: the same memory takes the f16 plane
+        if (nbias16)
+            quantize_f16_rows(cent, C, D, DP, Cpad16, mc2_bits, reinterpret_cast<uint16_t *>(qc), nbias16, rc_bits);
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int64_t w0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -101,76 +109,6 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__
         if (lane == 0) negb[j] = j < C ? -(int32_t)llrint(0.5 * n2) : kNoBias;
     }
 }
-
-// ------------------------------------------------------------ staging
-// A chunk of kQChunk quantised centroids (both planes) and their biases is
-// copied from the padded global arrays straight into LDS by buffer loads with
-// an LDS destination (16 bytes per lane, a wave writes 1 KiB of consecutive
-// LDS per instruction): no register staging and no LDS stores by the vector
-// unit. LDS layout of a chunk: centroid rows of PL planes with a pitch of
-// PL DP + 16 bytes (the 16 spread the rows over the banks), then the 64
-// biases. Slot s (16 bytes) of the row area holds unit s % (PL DP / 16 + 1)
-// of row s / (PL DP / 16 + 1); the pad unit and the bias instruction's lanes past the
-// biases read beyond the buffer range and receive zeros. Loads go through
-// buffer resources over the chunk's valid rows, so a ragged last chunk and
-// the chunk after the last one read zeros and every load is unconditional.
-// The loads of a chunk are complete (and visible to every wave) after the
-// next workgroup barrier, which waits for all outstanding vector memory
-// operations.
-template <int DP, int NT, int PL = 2>
-struct QStager {
-    static constexpr int kRowB = PL * DP;                // bytes per centroid
-    static constexpr int kRowU = kRowB / 16;             // 16-byte units per centroid
-    static constexpr int kPitch = kRowB + 16;
-    static constexpr int kRowInst = kRowU + 1;           // 64 rows x (kRowU + 1) slots / 64 lanes
-    static constexpr int kInst = kRowInst + 1;           // plus one for the biases
-    static constexpr int kBias = kQChunk * kPitch;       // byte offset of the biases (= kRowInst KiB)
-    static constexpr int kBytes = kInst * 1024;
-    static constexpr int kW = NT / 64;
-    static constexpr int kIPW = (kInst + kW - 1) / kW;   // load instructions per wave
-    int voff[kIPW];
-    int wave;  // wave-uniform
-
-    __device__ __forceinline__ void init()
-    {
-        const int lane = threadIdx.x & 63;
-        wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-#pragma unroll
-        for (int i = 0; i < kIPW; ++i) {
-            const int inst = wave + i * kW;
-            int off = 1 << 30;  // beyond any buffer range: reads zero
-            if (inst < kRowInst) {
-                const int slot = 64 * inst + lane;
-                const int r = slot / (kRowU + 1), u = slot % (kRowU + 1);
-                if (u < kRowU) off = r * kRowB + 16 * u;
-            } else if (inst == kRowInst && lane < kQChunk / 4) {
-                off = 16 * lane;
-            }
-            voff[i] = off;
-        }
-    }
-
-    // Enqueues the loads of the chunk starting at centroid cbase into the LDS
-    // buffer buf.
-    __device__ __forceinline__ void fetch(const int8_t *__restrict__ qc, const int32_t *__restrict__ negb,
-                                          int64_t cbase, int64_t cpad, char *buf) const
-    {
-        const int64_t left = cpad - cbase;
-        const int valid = (int)(left < 0 ? 0 : left < kQChunk ? left : kQChunk);
-        const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<int8_t *>(qc + cbase * kRowB), (short)0, valid * kRowB, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<int32_t *>(negb + cbase), (short)0, valid * 4, 0x00020000);
-#pragma unroll
-        for (int i = 0; i < kIPW; ++i) {
-            const int inst = wave + i * kW;
-            if (inst < kInst)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(inst < kRowInst ? rq : rb,
-                                                         (__attribute__((address_space(3))) void *)(buf + inst * 1024),
-                                                         16, voff[i], 0, 0, 0);
-        }
-    }
-};
 
 // ------------------------------------------------------------ rows
 // Row block rb of this wave: K-step k of row (wave * RB + rb) * 32 + l % 32
@@ -707,34 +645,7 @@ __global__ __launch_bounds__(W * 64, 2) void screen_i8_kernel(ScreenI8Args a)
     // every row when the list overflowed or the single plane did not apply
     const int32_t *ids = nullptr;
     int64_t n = a.nrows;
-    if (a.list && *a.q_bad1 == 0) {
-        const uint32_t c = *a.list_cnt;
-        if (c <= (uint64_t)a.list_cap) {
-            ids = a.list;
-            n = c;
-            if (a.rs.list_thr) {
-                // collected and resolved but for the rows with too many
-                // candidates. A tile's scan of the whole table takes as long
-                // for one row as for 512 (1.6 ms at 65,536 x 128), the split
-                // fp64 scan 0.1 ms for 30 rows and 1 ms for 500: few rows go
-                // straight to that
-                ids = a.rs.list2;
-                n = *a.rs.list2_cnt;
-                if (n <= kResolveScanRows) {
-                    if (blockIdx.x == 0) {
-                        for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-                            const int32_t r = ids[i];
-                            a.labels[r] = -1;
-                            const uint32_t slot = atomicAdd(a.wl_cnt, 1u);
-                            if (slot < (uint64_t)a.wl_cap) a.wl[slot] = r;
-                        }
-                        if (threadIdx.x == 0 && n) atomicAdd(a.stats + kStatFallback, (unsigned long long)n);
-                    }
-                    return;
-                }
-            }
-        }
-    }
+    if (a.list && *a.q_bad1 == 0 && !pick_rows(a, ids, n)) return;
     constexpr int rows_per_tile = W * 32 * rows_blocks<DP>();
     const int64_t ntiles = (n + rows_per_tile - 1) / rows_per_tile;
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
@@ -779,7 +690,7 @@ hipError_t launch_i8_w(int DP, const ScreenI8Args &a, int num_cus, hipStream_t s
 // route_i8_check checks every query value before the centroids are
 // quantised, route_i8_bound writes B per query; when some value is not an
 // integer in [0, 255] or some centroid does not quantise (*q_bad), *off is
-// raised and the fp32 kernels, which check the same flag, take the call.
+// raised and the f16 and fp32 kernels, which check the same flag, take the call.
 
 // Raises *off when some value of the nq queries is not an integer in
 // [0, 255] (one wave per query, grid-stride).
@@ -799,28 +710,56 @@ __global__ __launch_bounds__(256) void route_i8_check_kernel(const float *__rest
     if (__syncthreads_or(bad) && threadIdx.x == 0) atomicOr(off, 1u);  // one atomic per workgroup
 }
 
-// Per query of a batch (one wave each): qbound[q] = B = (390 + ||x'||_1) / 2;
-// raises *off when *q_bad (a centroid outside the two planes' range) is set.
+// Per query of a batch (one wave each): the bound of its plane keys, B =
+// (390 + ||x'||_1) / 2 on the int8 planes, the f16 plane's bound once another
+// plane takes the call, and ||q||^2 in fp64 for the fp32 kernels (qn2, may be
+// null). Raises *off when *q_bad (a centroid outside the two planes' range) is
+// set (the f16 plane was not built then: the fp32 kernels take the call). In a
+// library call, w are the scalar words: the batch's worklist counter and f16
+// flag start here.
 __global__ __launch_bounds__(256) void route_i8_bound_kernel(const float *__restrict__ Q, int64_t nq, int D,
                                                              const uint32_t *__restrict__ q_bad,
-                                                             uint32_t *__restrict__ off, float *__restrict__ qbound)
+                                                             uint32_t *__restrict__ off, float *__restrict__ qbound,
+                                                             uint32_t *__restrict__ w, double acc,
+                                                             double *__restrict__ qn2)
 {
-    // (the bounds are written whatever *off says: a wave must not read the
-    // flag this kernel itself raises to decide whether to take part)
     const int lane = threadIdx.x & 63;
     const int64_t w0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    if (w0 == 0 && lane == 0 && *q_bad) atomicOr(off, 1u);
+    // (whichever of the two is seen first: *off is raised here only when *q_bad is set)
+    const bool i8 = !off || (*off == 0u && *q_bad == 0u);
+    if (w0 == 0 && lane == 0) {
+        if (off && *q_bad) atomicOr(off, 1u);
+        if (w) {
+            w[kWordWorklist] = 0u;
+            w[kWordF16Off] = off && *q_bad ? 1u : 0u;
+        }
+    }
+    const uint32_t mc2 = w ? w[kWordMc2] : 0u, rc = w ? w[kWordF16Rc] : 0u;
+    const float sc = f16_scale(mc2);
     for (int64_t q = w0; q < nq; q += nw) {
+        double s = 0.0;
         uint32_t l1 = 0;
+        RowAcc f;
         for (int d = lane; d < D; d += 64) {
-            const float v = Q[q * D + d];  // (a value outside [0, 255] has raised *off already)
+            const float v = Q[q * D + d];
+            s = fma((double)v, (double)v, s);
             const int x = v >= 0.0f && v <= 255.0f ? (int)v - 128 : 0;
             l1 += (uint32_t)(x < 0 ? -x : x);
+            f.add(v * sc);
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) l1 += __shfl_xor(l1, o);
-        if (lane == 0) qbound[q] = 0.5f * (float)(390u + l1);
+        for (int o = 32; o > 0; o >>= 1) {
+            s += __shfl_xor(s, o);
+            l1 += __shfl_xor(l1, o);
+            f.r2 += __shfl_xor(f.r2, o);
+            f.n2 += __shfl_xor(f.n2, o);
+        }
+        f.over = __any(f.over);
+        if (lane == 0) {
+            if (qn2) qn2[q] = s;
+            if (qbound) qbound[q] = i8 ? 0.5f * (float)(390u + l1) : __double2float_ru(f16_bound(f.norms(), mc2, rc, acc));
+        }
     }
 }
 
@@ -1009,7 +948,7 @@ __global__ __launch_bounds__(W * 64, 2) void route_i8_kernel(RouteI8Args a)
     constexpr int CS = (St::kBytes + 15) / 16 * 16;
     __shared__ __attribute__((aligned(16))) char lds[2 * CS];
     __shared__ uint2 queue[MODE == kRouteFilter ? rows_blocks<DP>() * kRouteQueue * W * 64 : 1];
-    if (*a.off) return;  // the fp32 kernels take this call
+    if (*a.off) return;  // the f16 or fp32 kernels take this call
     if (MODE == kRouteFilter && blockIdx.x == 0 && threadIdx.x == 0 && a.stats) a.stats[kStatScreenI8] = 1ull;
     constexpr int rows_per_tile = W * 32 * rows_blocks<DP>();
     const int64_t ntiles = (a.nq + rows_per_tile - 1) / rows_per_tile;
@@ -1335,23 +1274,6 @@ __device__ __forceinline__ void s1_block(Frags1<DP> &f, const i32x4 (&x)[RB][DP 
     }
 }
 
-// Counters of one tile's unsettled rows (LDS) and their places in the call's
-// lists. One atomic per tile and list: with one per wave and row block, 250K
-// atomics on four neighbouring words bound an assignment against few
-// centroids (2M x 128 rows, 256 centroids: 1.86 ms, 0.45 with these).
-struct S1Tile {
-    uint32_t cnt[2];   // duels, listed rows of this tile
-    uint32_t base[2];  // their first slots in the lists
-};
-
-// What a row's three best scores decide.
-struct S1Verdict {
-    int kind;      // -1: nothing to list, 0: duel of c1 and c2, 1: listed
-    int c1, c2;
-    int thr;       // listed: scores >= thr can belong to the nearest centroid
-    uint32_t at;   // place among the tile's rows of this kind
-};
-
 // Merges the two half-lanes of a row and certifies with the window T:
 // settled rows get their label, rows with two candidates are left to the
 // resolving kernel (or decided here when the call has no list of them), the
@@ -1359,16 +1281,8 @@ struct S1Verdict {
 // names a real centroid, through the visiting order. Equal scores may rank in
 // plane-row order, which never decides a label: a gap above T excludes ties,
 // and the fp64 decision breaks them by centroid id.
-__device__ __forceinline__ int s1_duel_here(const ScreenI8Args &a, int64_t row, int c1, int c2)
-{
-    const uint8_t *x = a.rows + row * (int64_t)a.D;
-    const double d1 = exact_dist(x, a.cent + (int64_t)c1 * a.D, a.D);
-    const double d2 = exact_dist(x, a.cent + (int64_t)c2 * a.D, a.D);
-    return dist_lt(d2, c2, d1, c1) ? c2 : c1;
-}
-
-__device__ __forceinline__ S1Verdict s1_finish(const ScreenI8Args &a, int64_t row, bool rvalid, int h, const Top3i &st,
-                                               S1Tile &tl)
+__device__ __forceinline__ RowVerdict s1_finish(const ScreenI8Args &a, int64_t row, bool rvalid, int h, const Top3i &st,
+                                               TileLists &tl)
 {
     Top3i o;
     o.k1 = __shfl_xor(st.k1, 32);
@@ -1377,7 +1291,7 @@ __device__ __forceinline__ S1Verdict s1_finish(const ScreenI8Args &a, int64_t ro
     o.i1 = __shfl_xor(st.i1, 32);
     o.i2 = __shfl_xor(st.i2, 32);
     const Top3i m = top3i_merge(st, o);
-    S1Verdict v{-1, 0, 0, INT_MAX, 0};
+    RowVerdict v{-1, 0, 0, INT_MAX, 0};
     if (rvalid && h == 0) {
         const int64_t T = st.twoR;
         const bool ok1 = m.i1 >= 0 && m.i1 < a.ncent;
@@ -1402,51 +1316,6 @@ __device__ __forceinline__ S1Verdict s1_finish(const ScreenI8Args &a, int64_t ro
         v.at = v.kind == k ? at : v.at;
     }
     return v;
-}
-
-// After every row block of the tile has its verdicts: the workgroup reserves
-// the list slots of its rows and writes them.
-template <int RB>
-__device__ __forceinline__ void s1_list(const ScreenI8Args &a, const int64_t (&row)[RB], const S1Verdict (&v)[RB],
-                                        S1Tile &tl)
-{
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t nd = tl.cnt[0], nl = tl.cnt[1];
-        if (nd) {
-            if (a.rs.duel_cnt) tl.base[0] = atomicAdd(a.rs.duel_cnt, nd);
-            atomicAdd(a.stats + kStatRefine2, (unsigned long long)nd);
-        }
-        if (nl) {
-            tl.base[1] = atomicAdd(const_cast<uint32_t *>(a.list_cnt), nl);
-            atomicAdd(a.stats + kStatRescreen, (unsigned long long)nl);
-        }
-        tl.cnt[0] = 0;
-        tl.cnt[1] = 0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        if (v[rb].kind == 0) {
-            const uint64_t slot = (uint64_t)tl.base[0] + v[rb].at;
-            if (a.rs.duel_cnt && slot < (uint64_t)a.rs.duel_cap) {
-                a.rs.duel[slot] = make_uint2((uint32_t)row[rb], (uint32_t)v[rb].c1);
-                a.rs.duel2[slot] = v[rb].c2;
-            } else {
-                a.labels[row[rb]] = s1_duel_here(a, row[rb], v[rb].c1, v[rb].c2);
-            }
-        } else if (v[rb].kind == 1) {
-            // past the list's capacity the two-plane screen takes every row
-            const uint64_t slot = (uint64_t)tl.base[1] + v[rb].at;
-            if (slot < (uint64_t)a.list_cap) {
-                const_cast<int32_t *>(a.list)[slot] = (int32_t)row[rb];
-                if (a.rs.list_thr) {
-                    a.rs.list_thr[slot] = v[rb].thr;
-                    a.rs.cand_cnt[slot] = 0;
-                }
-            }
-        }
-    }
 }
 
 // Row blocks of 32 rows per wave in the single-plane screen: three at
@@ -1474,7 +1343,7 @@ __device__ __forceinline__ void for_each_index(F &&f, std::integer_sequence<int,
 // (that block refills its fragments from it) and then chunk j + 2 is
 // fetched into chunk j's buffer, which no wave reads any more.
 template <int DP, int W>
-__device__ void screen1_tile(const ScreenI8Args &a, int64_t tile, char *__restrict__ lds, S1Tile &tl)
+__device__ void screen1_tile(const ScreenI8Args &a, int64_t tile, char *__restrict__ lds, TileLists &tl)
 {
     static_assert(DP <= 128, "the single-plane screen keeps several row blocks per wave");
     constexpr int RB = s1_row_blocks<DP>();
@@ -1600,13 +1469,13 @@ __device__ void screen1_tile(const ScreenI8Args &a, int64_t tile, char *__restri
     for (int rb = 0; rb < RB; ++rb) s1_tile_test(sb[rb], idh + (nch - 1) * kS1Chunk + 32 * (NB - 1), st[rb]);
 
     int64_t row[RB];
-    S1Verdict v[RB];
+    RowVerdict v[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         row[rb] = row0 + (wave * RB + rb) * 32 + jl;
         v[rb] = s1_finish(a, row[rb], row[rb] < a.nrows, h, st[rb], tl);
     }
-    s1_list<RB>(a, row, v, tl);
+    list_tile<uint8_t, RB>(a, row, v, tl);
 }
 
 // Chunks [ch_lo, ch_hi) of the plane against one tile of listed rows, with
@@ -1744,7 +1613,7 @@ __global__ __launch_bounds__(W * 64, 2) void screen1_kernel(ScreenI8Args a)
     using St = QStager<DP, W * 64, 1>;
     constexpr int CS = (St::kBytes + 15) / 16 * 16;
     __shared__ __attribute__((aligned(16))) char lds[2 * kS1Sub * CS];
-    __shared__ S1Tile tl;
+    __shared__ TileLists tl;
     if (*a.q_bad || *a.q_bad1) return;  // another screen takes every row
     if (threadIdx.x == 0) tl.cnt[0] = tl.cnt[1] = 0;  // (the tile's barriers come before their first use)
     constexpr int rows_per_tile = W * 32 * s1_row_blocks<DP>();
@@ -1773,12 +1642,13 @@ int64_t quantized_pad(int64_t C) { return (C + kQChunk - 1) / kQChunk * kQChunk;
 int64_t quantized_pad1(int64_t C) { return (C + kS1Chunk - 1) / kS1Chunk * kS1Chunk; }
 
 hipError_t launch_quantize_centroids(const float *cent, int64_t C, int D, int DP, int8_t *qc, int32_t *negb,
-                                     uint32_t *q_bad, hipStream_t s, const uint32_t *skip)
+                                     uint32_t *q_bad, hipStream_t s, const uint32_t *skip, uint32_t *w)
 {
     const int64_t cpad = quantized_pad(C);
     const int64_t blocks = std::min<int64_t>((cpad + 3) / 4, 8192);
     hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)blocks), dim3(256), 0, s, cent, C, D, DP, cpad, qc, negb,
-                       q_bad, skip);
+                       q_bad, skip, w ? reinterpret_cast<float *>(negb) : nullptr, w ? w + kWordMc2 : nullptr,
+                       w ? w + kWordF16Rc : nullptr, quantized_pad1(C));
     return hipGetLastError();
 }
 
@@ -1854,12 +1724,12 @@ hipError_t launch_route_i8_check(const float *queries, int64_t nq, int D, uint32
 }
 
 hipError_t launch_route_i8_bound(const float *queries, int64_t nq, int D, const uint32_t *q_bad, uint32_t *off,
-                                 float *qbound, hipStream_t s)
+                                 float *qbound, hipStream_t s, uint32_t *w, double acc, double *qn2)
 {
     if (nq <= 0) return hipSuccess;
-    const int64_t blocks = std::min<int64_t>((nq + 3) / 4, 65536);
+    const int64_t blocks = std::min<int64_t>((nq + 3) / 4, 4096);
     hipLaunchKernelGGL(route_i8_bound_kernel, dim3((unsigned)blocks), dim3(256), 0, s, queries, nq, D, q_bad, off,
-                       qbound);
+                       qbound, w, acc, qn2);
     return hipGetLastError();
 }
 

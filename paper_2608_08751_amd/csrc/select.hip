@@ -112,22 +112,6 @@ __global__ __launch_bounds__(256) void centroid_norms_kernel(const float *__rest
     }
 }
 
-__global__ __launch_bounds__(256) void row_norms_kernel(const float *__restrict__ rows, int64_t n,
-                                                        int D, double *__restrict__ out)
-{
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < n; r += (int64_t)gridDim.x * 4) {
-        double s = 0.0;
-        for (int d = lane; d < D; d += 64) {
-            const double v = (double)rows[r * D + d];
-            s = fma(v, v, s);
-        }
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-        if (lane == 0) out[r] = s;
-    }
-}
-
 // Order-preserving map between non-NaN floats and uint32 keys.
 __device__ __forceinline__ uint32_t f2o(float f)
 {
@@ -194,8 +178,8 @@ __device__ uint32_t block_select(const uint32_t (&v)[V], int nv, int k, uint32_t
 constexpr int kMaxGroups = 4096;
 constexpr int kGroupsPerThread = kMaxGroups / 256;
 
-// true when the int8 route kernels produce this call's keys (group minima)
-__device__ __forceinline__ bool int8_keys(const RouteArgs &a) { return a.i8_off && *a.i8_off == 0u; }
+// true when a plane's route kernels produce this batch's keys (group minima)
+__device__ __forceinline__ bool plane_keys(const RouteArgs &a) { return a.w && route_mode(a.w) != kModeF32; }
 
 // Centroid id of sample key s: the sample is the chunks j * sstride of kChunk
 // centroids, its keys in that order.
@@ -207,7 +191,7 @@ __device__ __forceinline__ uint32_t sample_id(const RouteArgs &a, int64_t s)
 
 __global__ __launch_bounds__(256) void route_threshold_kernel(RouteArgs a)
 {
-    if (int8_keys(a)) return;
+    if (plane_keys(a)) return;
     const int64_t q = blockIdx.x;
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sh[2];
@@ -268,7 +252,7 @@ __global__ __launch_bounds__(256) void route_threshold_kernel(RouteArgs a)
 template <int GPT>
 __global__ __launch_bounds__(256) void route_threshold_reg_kernel(RouteArgs a)
 {
-    if (int8_keys(a)) return;
+    if (plane_keys(a)) return;
     const int64_t q = blockIdx.x;
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sh[2];
@@ -327,7 +311,7 @@ __global__ __launch_bounds__(256) void route_threshold_reg_kernel(RouteArgs a)
 // candidates (a group whose minimum exceeds tau holds none).
 __global__ __launch_bounds__(256) void route_threshold_gmin_kernel(RouteArgs a)
 {
-    if (int8_keys(a)) return;
+    if (plane_keys(a)) return;
     const int64_t q = blockIdx.x;
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sh[2];
@@ -375,16 +359,27 @@ __global__ __launch_bounds__(256) void route_threshold_gmin_kernel(RouteArgs a)
     }
 }
 
-// The threshold when the int8 route kernels ran: the keys buffer holds the
+// The threshold when a plane's route kernels ran: the keys buffer holds the
 // sample's group minima [nq, Cs / 16] directly, tau = the rank_j-th smallest,
 // and the sample's centroids are left to the filter, which then covers every
-// centroid (the candidate list starts empty).
+// centroid (the candidate list starts empty). The f16 plane's window 2 B is
+// part of the spacing of the minima, so tau is at least the window above the
+// rank_safe-th minimum (the k-th smallest key lies below that minimum but for
+// a five-sigma draw of the sample); a query for which that lies above the
+// rank_max-th minimum would keep too many candidates, and its batch goes to
+// the fp32 kernels.
+constexpr int kRankMax = 64;
+
 __global__ __launch_bounds__(256) void route_threshold_min_kernel(RouteArgs a)
 {
-    if (!int8_keys(a)) return;
+    // (kWordF16Off, zero before this kernel, is raised by it and not read)
+    const bool i8 = a.w[kWordNotI8] == 0u;
     const int64_t q = blockIdx.x;
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sh[2];
+    __shared__ uint32_t s_n;
+    __shared__ uint32_t s_v[2 * kRankMax];
+    __shared__ float s_rank[2];
     const int G = (int)(a.Cs / 16);
     const float *kr = a.keys + q * G;
     uint32_t v[kGroupsPerThread];
@@ -398,10 +393,46 @@ __global__ __launch_bounds__(256) void route_threshold_min_kernel(RouteArgs a)
             nv = e + 1;
         }
     }
-    const float th = o2f(block_select(v, nv, min(a.rank_j, G), hist, sh));
+    const int rank = min(a.rank_j, G);
+    if (i8) {
+        const float th = o2f(block_select(v, nv, rank, hist, sh));
+        if (threadIdx.x == 0) {
+            a.tau[q] = th;
+            a.cand_cnt[q] = 0;
+        }
+        return;
+    }
+    // the rank_max smallest minima, then two ranks among them
+    if (threadIdx.x == 0) s_n = 0;
+    const int rmax = min(a.rank_max, G);
+    const uint32_t top = block_select(v, nv, rmax, hist, sh);
+#pragma unroll
+    for (int e = 0; e < kGroupsPerThread; ++e) {
+        if (e < nv && v[e] <= top) {
+            const uint32_t at = atomicAdd(&s_n, 1u);
+            if (at < 2 * kRankMax) s_v[at] = v[e];
+        }
+    }
+    __syncthreads();
+    const int n = min((int)s_n, 2 * kRankMax);  // rmax but for equal minima
+    if ((int)threadIdx.x < n) {
+        const uint32_t m = s_v[threadIdx.x];
+        int less = 0, same = 0;
+        for (int i = 0; i < n; ++i) {
+            less += s_v[i] < m ? 1 : 0;
+            same += s_v[i] == m ? 1 : 0;
+        }
+        if (less < rank && rank <= less + same) s_rank[0] = o2f(m);
+        const int rs = min(a.rank_safe, rmax);
+        if (less < rs && rs <= less + same) s_rank[1] = o2f(m);
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        a.tau[q] = th;
+        const float cover = __double2float_ru((double)s_rank[1] + 2.0 * (double)a.qbound[q]);
+        const bool wide = !(cover <= o2f(top));
+        a.tau[q] = fmaxf(s_rank[0], cover);
         a.cand_cnt[q] = 0;
+        if (wide) a.w[kWordF16Off] = 1u;
     }
 }
 
@@ -458,8 +489,8 @@ __global__ __launch_bounds__(256) void route_select_kernel(RouteArgs a)
     for (int d = threadIdx.x; d < a.D; d += blockDim.x) qrow[d] = a.queries[q * a.D + d];
     if (threadIdx.x == 0) s_nr = 0;
     const double kth = (double)o2f(block_select(v, nv, a.k, hist, sh));
-    const double B2 = a.i8_off && *a.i8_off == 0u ? 2.0 * (double)a.qbound[q]
-                                                  : 2.0 * key_bound(a.bound_coef, *a.mc2_bits, a.qn2[q]);
+    const double B2 = plane_keys(a) ? 2.0 * (double)a.qbound[q]
+                                    : 2.0 * key_bound(a.bound_coef, *a.mc2_bits, a.qn2[q]);
     if (!((double)a.tau[q] >= kth + B2)) {
         if (threadIdx.x == 0) push_fallback(a, q, false);
         return;
@@ -582,17 +613,9 @@ hipError_t launch_centroid_norms(const float *cent, int64_t C, int D, float *cno
     return hipGetLastError();
 }
 
-hipError_t launch_row_norms(const float *rows, int64_t n, int D, double *out, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(row_norms_kernel, dim3(grid_for(n, 4, 4096)), dim3(256), 0, s, rows, n, D, out);
-    return hipGetLastError();
-}
-
 hipError_t launch_route_threshold(const RouteArgs &a, hipStream_t s)
 {
     const int64_t G = a.Cs / 16;
-    if (a.i8_off && a.Cs > 0) hipLaunchKernelGGL(route_threshold_min_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a);
     if (a.Cs > 0 && a.kmin && G <= kMaxGroups)
         hipLaunchKernelGGL(route_threshold_gmin_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a);
     else if (a.Cs > 0 && G <= 256)
@@ -603,6 +626,12 @@ hipError_t launch_route_threshold(const RouteArgs &a, hipStream_t s)
         hipLaunchKernelGGL(route_threshold_reg_kernel<4>, dim3((unsigned)a.nq), dim3(256), 0, s, a);
     else
         hipLaunchKernelGGL(route_threshold_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_route_threshold_min(const RouteArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL(route_threshold_min_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

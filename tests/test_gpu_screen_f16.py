@@ -1,0 +1,96 @@
+"""The f16 screen of fp32 rows and queries: labels, ids and distances equal the
+oracle's on ordinary data, among near ties (two candidates, a few, more than
+the collecting pass keeps), and where f16 cannot decide: data far from the
+origin (its window covers every centroid), values beyond its range or below
+its smallest normal number, and a zero table. IVF_OPT_FP32_SCREEN gives the
+same."""
+import numpy as np
+import pytest
+
+from test_gpu_screen_i8 import ivf_ctx, to_dev  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def data(kind, N, C, D, seed):
+    r = np.random.default_rng(seed)
+    c = r.normal(size=(C, D)).astype(np.float32)
+    c /= np.linalg.norm(c, axis=1, keepdims=True)
+    x = (c[r.integers(0, C, N)] + 0.3 / np.sqrt(D) * r.normal(size=(N, D))).astype(np.float32)
+    if kind == "ties":  # groups of 1, 2, 3, 8 and 12 almost equal centroids
+        size = np.resize([1, 2, 3, 8, 12], C)
+        head = np.repeat(np.arange(C), size)[:C]
+        c = (c[head] * (1.0 + 1e-6 * r.normal(size=(C, D)))).astype(np.float32)
+    elif kind == "offset":
+        c, x = c * np.float32(0.01) + np.float32(50.0), x * np.float32(0.01) + np.float32(50.0)
+    elif kind == "range":  # some rows 1e4 times longer than any centroid, some 1e-6 times as long
+        x[::7] *= np.float32(1e4)
+        x[3::11] *= np.float32(1e-6)
+    elif kind == "tiny":
+        c, x = c * np.float32(1e-17), x * np.float32(1e-17)
+    elif kind == "huge":
+        c, x = c * np.float32(1e17), x * np.float32(1e17)
+    elif kind == "zero":
+        c[:] = 0
+    return np.ascontiguousarray(x), np.ascontiguousarray(c)
+
+
+@pytest.mark.parametrize("kind,N,C,D", [
+    ("plain", 513, 257, 96), ("plain", 1, 1, 4), ("plain", 3000, 1000, 128), ("plain", 700, 65, 36),
+    ("plain", 900, 130, 256), ("plain", 600, 300, 160), ("plain", 520, 700, 64),
+    ("ties", 4000, 900, 100), ("ties", 2500, 600, 200), ("offset", 2000, 500, 96), ("range", 1500, 400, 128),
+    ("tiny", 800, 200, 96), ("huge", 800, 200, 96), ("zero", 100, 70, 32),
+])
+def test_assign_equals_the_oracle(ivf_ctx, oracle_mod, kind, N, C, D):  # noqa: F811
+    import torch
+
+    import paper_2608_08751_amd as ivf
+
+    x, c = data(kind, N, C, D, seed=N + D)
+    olab = oracle_mod.assign(x, c)
+    for fp32 in (0, 1):
+        ivf_ctx.set_option(ivf.IVF_OPT_FP32_SCREEN, fp32)
+        try:
+            lab = ivf.ivf_assign_build(ivf_ctx, to_dev(x), to_dev(c))[0]
+            torch.cuda.synchronize()
+            print(kind, N, C, D, "fp32" if fp32 else "f16", ivf_ctx.last_stats(), flush=True)
+        finally:
+            ivf_ctx.set_option(ivf.IVF_OPT_FP32_SCREEN, 0)
+        bad = np.nonzero(lab.cpu().numpy() != olab)[0]
+        assert bad.size == 0, "labels differ at rows %s" % bad[:10]
+
+
+@pytest.mark.parametrize("kind,Q,C,D,k", [
+    ("plain", 513, 4096, 96, 16), ("plain", 1, 3000, 128, 5), ("plain", 40, 9001, 4, 128), ("plain", 300, 2049, 256, 64),
+    ("plain", 65, 5000, 100, 1000), ("plain", 200, 2113, 160, 1), ("ties", 500, 4100, 64, 40),
+    ("offset", 64, 3000, 96, 32), ("range", 100, 3000, 128, 16), ("tiny", 50, 2500, 96, 8), ("huge", 50, 2500, 96, 8),
+])
+def test_route_equals_the_oracle(ivf_ctx, oracle_mod, kind, Q, C, D, k):  # noqa: F811
+    import torch
+
+    import paper_2608_08751_amd as ivf
+
+    q, c = data(kind, Q, C, D, seed=Q + D)
+    if kind != "huge" and D >= 64:
+        q[0] = c[C // 3]  # a planted query
+    oids, odist = oracle_mod.route(q, c, k)
+    ids, dist = ivf.ivf_route(ivf_ctx, to_dev(q), to_dev(c), k)
+    torch.cuda.synchronize()
+    print(kind, Q, C, D, k, ivf_ctx.last_stats(), flush=True)
+    assert (ids.cpu().numpy() == oids).all() and (dist.cpu().numpy() == odist).all()
+
+
+def test_route_batches_and_odd_queries(ivf_ctx, oracle_mod):  # noqa: F811
+    """Two internal batches: one query of the second has no f16 bound, so that
+    batch alone goes to the fp32 kernels."""
+    import torch
+
+    import paper_2608_08751_amd as ivf
+
+    q, c = data("plain", 16384 + 700, 2300, 32, seed=9)
+    q[16384 + 5] *= np.float32(1e6)
+    ids, dist = ivf.ivf_route(ivf_ctx, to_dev(q), to_dev(c), 8)
+    torch.cuda.synchronize()
+    pick = np.r_[0:64, 16384 - 8:16384 + 64, 16384 + 636:16384 + 700]
+    oids, odist = oracle_mod.route(q[pick], c, 8)
+    assert (ids.cpu().numpy()[pick] == oids).all() and (dist.cpu().numpy()[pick] == odist).all()
