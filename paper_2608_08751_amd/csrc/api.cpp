@@ -1499,7 +1499,7 @@ ivf_status ivf_pq_encode(ivf_ctx *ctx, const float *x, int64_t n, int32_t D, int
         return fail(ctx, IVF_EINVAL, "outputs overlap inputs");
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(ctx, IVF_EDEVICE, "no usable device (context device %d)", ctx->device);
-    TIMED("pq_assign", launch_pq_assign(x, n, D, dsub, 0, M, codebooks, out_codes, M, nullptr, ctx->stream));
+    TIMED("pq_assign", launch_pq_assign(x, n, D, dsub, M, codebooks, out_codes, nullptr, ctx->num_cus, ctx->stream));
     ctx->last_stats = nullptr;
     return IVF_OK;
 }
@@ -1537,7 +1537,7 @@ ivf_status ivf_pq_train_step(ivf_ctx *ctx, const float *x, int64_t n, int32_t D,
     int64_t *counts = out_counts ? out_counts : l.counts;
     // every subspace's labels, then each subspace's lists, then one update
     // launch over all M x 256 codewords (group m = subspace m, seed + m)
-    TIMED("pq_assign", launch_pq_assign(x, n, D, dsub, 0, M, codebooks, nullptr, M, l.labels, ctx->stream));
+    TIMED("pq_assign", launch_pq_assign(x, n, D, dsub, M, codebooks, nullptr, l.labels, ctx->num_cus, ctx->stream));
     for (int m = 0; m < M; ++m)
         if ((st = enqueue_build(ctx, n, kPqK, l.labels + (int64_t)m * n, l.radix, counts + (int64_t)m * kPqK,
                                 l.offsets + (int64_t)m * (kPqK + 1), l.perm + (int64_t)m * n)) != IVF_OK)

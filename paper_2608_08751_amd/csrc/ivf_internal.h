@@ -411,11 +411,10 @@ hipError_t launch_list_major(const void *base, int rowtype, int64_t N, const flo
 // ---- product quantisation (pq.hip) ------------------------------------------
 constexpr int kPqK = 256;         // codewords per subspace (8-bit codes)
 constexpr int kPqMaxSubDims = 16; // dims per subspace
-// Nearest codeword of every row in subspaces [m0, m1): codes [n, M] uint8
-// and/or labels [m1 - m0][n] int32.
-hipError_t launch_pq_assign(const float *X, int64_t n, int D, int dsub, int m0, int m1,
-                            const float *codebooks, uint8_t *codes, int M, int32_t *labels,
-                            hipStream_t s);
+// Nearest codeword of every row in each of the M subspaces: codes [n, M] uint8
+// and/or labels [M][n] int32.
+hipError_t launch_pq_assign(const float *X, int64_t n, int D, int dsub, int M, const float *codebooks, uint8_t *codes,
+                            int32_t *labels, int num_cus, hipStream_t s);
 
 // ---- candidate-restricted assignment (assign_graph.hip) ---------------------
 constexpr int kMaxGraphDegree = 64;
