@@ -338,12 +338,12 @@ struct AssignLayout {
 };
 
 // Product-quantisation training step over M subspaces: labels [M][n], the
-// list build of each subspace's labels (256 lists; one radix scratch reused),
+// list build of all subspaces' labels (256 lists each; block counts),
 // counts [M][256], offsets [M][257], permutations [M][n] and the update's
 // objective parts [M][256].
 struct PqLayout {
     int32_t *labels;
-    void *radix;
+    uint32_t *cnt;
     int64_t *counts;
     int64_t *offsets;
     uint32_t *perm;
@@ -356,7 +356,7 @@ PqLayout layout_pq(void *base, int64_t n, int M, int num_cus)
     Carver c(base);
     PqLayout l{};
     l.labels = c.take<int32_t>((size_t)n * M);
-    l.radix = c.take<unsigned char>(radix_scratch_bytes(plan_radix(n, kPqK, num_cus)));
+    l.cnt = c.take<uint32_t>(single_scratch_bytes(plan_single(n, kPqK, M, num_cus)) / 4);
     l.counts = c.take<int64_t>((size_t)kPqK * M);
     l.offsets = c.take<int64_t>((size_t)(kPqK + 1) * M);
     l.perm = c.take<uint32_t>((size_t)n * M);
@@ -408,7 +408,9 @@ AssignLayout layout_assign(void *base, int64_t N, int64_t C, int qdp, bool need_
     l.fb_d = c.take<double>(kFbSplitEntries);
     l.fb_i = c.take<int32_t>(kFbSplitEntries);
     if (need_build) {
-        if (C <= kRadixMaxLists)
+        if (C <= kSingleMaxLists)
+            l.cntmat = c.take<uint32_t>(single_scratch_bytes(plan_single(N, C, 1, num_cus)) / 4);
+        else if (C <= kRadixMaxLists)
             l.cntmat = (uint32_t *)c.take<unsigned char>(radix_scratch_bytes(plan_radix(N, C, num_cus)));
         else
             l.cntmat = c.take<uint32_t>(build_scratch_bytes(plan_build(N, C, num_cus)) / 4);
@@ -693,20 +695,25 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
     return IVF_OK;
 }
 
-// List build: the two-level radix partition for C <= 65,536 lists, the
-// single-pass per-block build otherwise. `scratch` is the build area of the
+// List build: one partition by the label for C <= 256 lists, the two-level
+// radix partition for C <= 65,536, the single-pass per-block build otherwise. `scratch` is the build area of the
 // workspace.
 ivf_status enqueue_build(ivf_ctx *ctx, int64_t N, int64_t C, const int32_t *labels, void *scratch,
                          int64_t *counts, int64_t *offsets, uint32_t *perm)
 {
     if (C <= kRadixMaxLists) {
-        const RadixPlan rp = plan_radix(N, C, ctx->num_cus);
-        const RadixScratch rs = carve_radix(rp, scratch);
         if (N == 0) {
             TIMED("fill", launch_fill_u32((uint32_t *)counts, 2 * C, 0u, ctx->stream));
             TIMED("build_offsets", launch_offsets(counts, C, offsets, ctx->stream));
             return IVF_OK;
         }
+        if (C <= kSingleMaxLists) {
+            TIMED("build_single", launch_single_build(plan_single(N, C, 1, ctx->num_cus), labels, (uint32_t *)scratch,
+                                                      counts, offsets, perm, ctx->stream));
+            return IVF_OK;
+        }
+        const RadixPlan rp = plan_radix(N, C, ctx->num_cus);
+        const RadixScratch rs = carve_radix(rp, scratch);
         TIMED("build_level0", launch_radix_level0(rp, labels, rs, ctx->stream));
         TIMED("build_level1_counts", launch_radix_level1_counts(rp, rs, counts, ctx->stream));
         TIMED("build_offsets", launch_offsets(counts, C, offsets, ctx->stream));
@@ -1535,13 +1542,11 @@ ivf_status ivf_pq_train_step(ivf_ctx *ctx, const float *x, int64_t n, int32_t D,
     if (!g.ok) return fail(ctx, IVF_EDEVICE, "no usable device (context device %d)", ctx->device);
     const PqLayout l = layout_pq(ctx->ws, n, M, ctx->num_cus);
     int64_t *counts = out_counts ? out_counts : l.counts;
-    // every subspace's labels, then each subspace's lists, then one update
+    // every subspace's labels, then all subspaces' lists, then one update
     // launch over all M x 256 codewords (group m = subspace m, seed + m)
     TIMED("pq_assign", launch_pq_assign(x, n, D, dsub, M, codebooks, nullptr, l.labels, ctx->num_cus, ctx->stream));
-    for (int m = 0; m < M; ++m)
-        if ((st = enqueue_build(ctx, n, kPqK, l.labels + (int64_t)m * n, l.radix, counts + (int64_t)m * kPqK,
-                                l.offsets + (int64_t)m * (kPqK + 1), l.perm + (int64_t)m * n)) != IVF_OK)
-            return st;
+    TIMED("build_single", launch_single_build(plan_single(n, kPqK, M, ctx->num_cus), l.labels, l.cnt, counts, l.offsets,
+                                              l.perm, ctx->stream));
     TIMED("pq_update", launch_kmeans_update(x, kRowF32, n, dsub, D, codebooks, kPqK, counts, l.offsets, l.perm,
                                             seed, iter, out_codebooks, l.jpart, out_objective, ctx->stream, M,
                                             dsub));

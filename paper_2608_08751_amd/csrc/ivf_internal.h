@@ -391,6 +391,20 @@ hipError_t launch_radix_level1_counts(const RadixPlan &p, const RadixScratch &s,
 hipError_t launch_radix_level1_scatter(const RadixPlan &p, const RadixScratch &s, const int64_t *offsets,
                                        uint32_t *perm, hipStream_t st);
 hipError_t launch_offsets(const int64_t *counts, int64_t C, int64_t *offsets, hipStream_t st);
+// At most 256 lists: one partition by the label, `groups` independent label
+// arrays [groups][N] at once (counts [groups][C], offsets [groups][C + 1],
+// perm [groups][N]).
+constexpr int64_t kSingleMaxLists = 256;
+struct SinglePlan {
+    int64_t N, C;
+    int groups;
+    int64_t R;     // rows per block
+    int nblocks;   // per group
+};
+SinglePlan plan_single(int64_t N, int64_t C, int groups, int num_cus);
+size_t single_scratch_bytes(const SinglePlan &p);
+hipError_t launch_single_build(const SinglePlan &p, const int32_t *labels, uint32_t *cnt, int64_t *counts,
+                               int64_t *offsets, uint32_t *perm, hipStream_t st);
 
 // ---- k-means update (kmeans.hip) --------------------------------------------
 // `groups` independent problems in one launch (product-quantisation
