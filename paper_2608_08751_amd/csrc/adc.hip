@@ -15,21 +15,31 @@
 // codes (the last one partial); the chunks of a list are taken in runs of
 // G_b (the group size of query b, max(kAdcMinGroup, ceil(chunks_b / P))), so a
 // short list is one group and a long one is spread over several groups, and a
-// query has at most 2P groups (the workspace holds 2P * k handoff keys per
-// query).
+// query has at most 2P groups. The groups of a query are dealt to S parts
+// (part s takes groups s, s + S, ...): one part per query when the batch fills
+// the chip, several when it does not.
 //   adc_setup_kernel   one workgroup per query: the chunk counts of its
 //                      probed lists, G_b, the groups of every list and their
 //                      exclusive scan over the probes (each group's slot),
 //                      and one descriptor per group (list, code range);
-//   adc_group_kernel   one workgroup per group slot (slots past the query's
-//                      group count return at once): builds the list's LUT,
-//                      scans the group's chunks and keeps the k smallest keys
-//                      in an LDS pool (an exact MSD radix select trims it
-//                      whenever it holds more than k), then hands over those k
-//                      keys: the chunk scan and the first merge are one
-//                      kernel, chunk-level candidates never leave LDS;
-//   adc_merge_kernel   one workgroup per query merges its groups' keys into
-//                      the k smallest and sorts them.
+//   adc_scan_kernel    one workgroup of 16 waves per part: a few groups at a
+//                      time it builds their lists' LUTs in LDS, scans their
+//                      codes and keeps the k smallest keys of the part in an
+//                      LDS pool (an exact radix select trims it when the next
+//                      codes might not fit; later codes enter only below the
+//                      k-th key of the last trim). The part of a whole query
+//                      sorts its keys into the results, the others hand over
+//                      their k keys;
+//   adc_merge_kernel   one workgroup per query merges its parts' keys the same
+//                      way and sorts them.
+// What bounds it is the LUT arithmetic: 256 D fp64 subtractions and fmas per
+// probed list, whatever its length. With one workgroup per group every group
+// read the 1,024 D bytes of codebooks from L2 and converted them, and handed
+// all its codes to the merge; here a thread holds its codewords of the usual
+// subspaces (D <= 160) in registers in fp64 for all the groups of its part, and
+// one threshold serves a whole query. 2,048 queries x 96 probed lists of 152
+// codes, M = 16, k = 512: 1.96 -> 1.21 ms (0.23 of it per workgroup, 9.9 us per
+// list of all queries); 8 queries x 64 lists: 158 -> 58 us.
 // Ids are unique within a query (lists are disjoint), so "the k smallest
 // keys" is exact whatever the grouping.
 #include "ivf_internal.h"
@@ -39,12 +49,17 @@
 namespace ivf {
 namespace {
 
-constexpr int kAdcThreads = 256;
-constexpr int kAdcChunk = 1024;                          // codes per chunk (appended per round)
-constexpr int kAdcMinGroup = 8;                          // chunks per group at least
-constexpr int kAdcPool = kAdcMaxK + kAdcChunk;            // LDS pool capacity (keys)
-constexpr int kAdcKeysPerThread = kAdcPool / kAdcThreads;
+constexpr int kSetupThreads = 256;
+constexpr int kAdcThreads = 1024;
+constexpr int kAdcWaves = kAdcThreads / 64;
+constexpr int kAdcChunk = 1024;      // codes per chunk
+constexpr int kAdcMinGroup = 8;      // chunks per group at least
+constexpr int kAdcPool = 4096;       // LDS pool capacity (keys): trimmed when fewer than kAdcThreads places are left
+constexpr int kAdcMaxLists = 8;      // lists whose LUTs are built at a time, as many as fit
+constexpr int kAdcLutBytes = 73728;  // LUTs
+constexpr int kAdcBins = 2048;       // 11-bit digits
 constexpr uint64_t kNoKey = ~0ull;
+static_assert(kAdcMaxK + kAdcThreads <= kAdcPool, "a trimmed pool takes another round of keys");
 
 __device__ __forceinline__ uint32_t f2o(float f)
 {
@@ -59,82 +74,136 @@ __device__ __forceinline__ float o2f(uint32_t u)
 
 struct PoolLds {
     uint64_t key[kAdcPool];
-    uint64_t thr;  // the k-th smallest key at the last trim (keys >= thr cannot enter)
-    uint32_t hist[256];
-    uint32_t sel_digit, sel_below;
-    uint32_t n;  // keys in the pool
+    uint32_t hist[kAdcBins];
+    uint32_t wsum[kAdcWaves];
+    uint64_t thr;  // keys above it are not among the k smallest seen
+    uint32_t digit, below, count;  // the selected bin of a pass
+    uint32_t n;    // keys in the pool
 };
 
-// Leaves exactly the k smallest of the pool's n (> k) unique keys in it.
+__device__ __forceinline__ void pool_init(PoolLds &P)
+{
+    if (threadIdx.x == 0) {
+        P.n = 0;
+        P.thr = kNoKey;
+    }
+}
+
+// Appends this thread's key (every thread of the workgroup calls it).
+__device__ __forceinline__ void pool_add(PoolLds &P, uint64_t key, bool have, uint64_t thr)
+{
+    const int lane = threadIdx.x & 63;
+    const bool keep = have && key <= thr;
+    const uint64_t want = __ballot(keep);
+    if (want != 0) {
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&P.n, (uint32_t)__popcll(want));
+        base = __shfl(base, 0);
+        if (keep) P.key[base + __popcll(want & ((1ull << lane) - 1))] = key;
+    }
+}
+
+// Leaves exactly the k smallest of the pool's n (> k) unique keys in it. The
+// select takes 11 bits a pass and stops as soon as the bin of the k-th key ends
+// at rank k (usually after the second or third pass).
 __device__ void pool_trim(PoolLds &P, int k)
 {
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int n = (int)P.n;
-    uint64_t prefix = 0, mask = 0;
-    uint32_t kk = (uint32_t)k;  // rank of the target inside the current prefix
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        P.hist[t] = 0;
-        __syncthreads();
-        for (int i = t; i < n; i += kAdcThreads) {
-            const uint64_t v = P.key[i];
-            if ((v & mask) == prefix) atomicAdd(&P.hist[(v >> shift) & 255u], 1u);
-        }
-        __syncthreads();
-        if (t < 64) {  // one wave: the digit whose cumulative count reaches kk
-            const uint32_t h0 = P.hist[4 * t], h1 = P.hist[4 * t + 1], h2 = P.hist[4 * t + 2],
-                           h3 = P.hist[4 * t + 3];
-            const uint32_t own = h0 + h1 + h2 + h3;
-            uint32_t incl = own;
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t up = __shfl_up(incl, o);
-                if (t >= o) incl += up;
-            }
-            uint32_t before = incl - own;
-            if (before < kk && kk <= incl) {
-                int dgt = 4 * t;
-                uint32_t b = before;
-                if (b + h0 < kk) {
-                    b += h0;
-                    ++dgt;
-                    if (b + h1 < kk) {
-                        b += h1;
-                        ++dgt;
-                        if (b + h2 < kk) {
-                            b += h2;
-                            ++dgt;
-                        }
-                    }
-                }
-                P.sel_digit = (uint32_t)dgt;
-                P.sel_below = b;
-            }
-        }
-        __syncthreads();
-        prefix |= (uint64_t)P.sel_digit << shift;
-        mask |= 255ull << shift;
-        kk -= P.sel_below;
-        __syncthreads();
-    }
-    // prefix is now the k-th smallest key: keep the keys <= prefix
-    uint64_t mine[kAdcKeysPerThread];
+    uint64_t mine[kAdcPool / kAdcThreads];
 #pragma unroll
-    for (int e = 0; e < kAdcKeysPerThread; ++e) {
+    for (int e = 0; e < kAdcPool / kAdcThreads; ++e) {
         const int i = t + e * kAdcThreads;
         mine[e] = i < n ? P.key[i] : kNoKey;
     }
+    uint64_t prefix = 0, mask = 0;
+    uint32_t kk = (uint32_t)k;  // rank of the target inside the current prefix
+    for (int top = 64; top > 0;) {
+        const int width = min(top, 11), shift = top - width;
+        top = shift;
+        P.hist[t] = 0;
+        P.hist[t + kAdcThreads] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kAdcPool / kAdcThreads; ++e)
+            if (t + e * kAdcThreads < n && (mine[e] & mask) == prefix)
+                atomicAdd(&P.hist[(mine[e] >> shift) & ((1u << width) - 1u)], 1u);
+        __syncthreads();
+        const uint32_t h0 = P.hist[2 * t], h1 = P.hist[2 * t + 1];
+        uint32_t incl = h0 + h1;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t up = __shfl_up(incl, o);
+            if (lane >= o) incl += up;
+        }
+        if (lane == 63) P.wsum[wave] = incl;
+        __syncthreads();
+        uint32_t before = incl - h0 - h1;
+        for (int w = 0; w < wave; ++w) before += P.wsum[w];
+        if (before < kk && kk <= before + h0 + h1) {
+            const bool second = before + h0 < kk;
+            P.digit = 2 * t + (second ? 1 : 0);
+            P.below = before + (second ? h0 : 0u);
+            P.count = second ? h1 : h0;
+        }
+        __syncthreads();
+        prefix |= (uint64_t)P.digit << shift;
+        mask |= ((1ull << width) - 1ull) << shift;
+        kk -= P.below;
+        if (P.count == kk) break;  // (uniform) the whole bin belongs to the k smallest
+    }
     if (t == 0) {
         P.n = 0;
-        P.thr = prefix;
+        P.thr = prefix | ~mask;
     }
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < kAdcKeysPerThread; ++e)
-        if (mine[e] <= prefix && mine[e] != kNoKey) P.key[atomicAdd(&P.n, 1u)] = mine[e];
+    for (int e = 0; e < kAdcPool / kAdcThreads; ++e)
+        pool_add(P, mine[e], t + e * kAdcThreads < n && (mine[e] & mask) <= prefix, kNoKey);
     __syncthreads();
     // with unique keys exactly k remain; repeated ids (not a valid list
     // layout) must not let the pool outgrow its capacity
     if (t == 0 && P.n > (uint32_t)k) P.n = (uint32_t)k;
     __syncthreads();
+}
+
+// Room for one more round of keys, after every thread's last append.
+__device__ __forceinline__ void pool_room(PoolLds &P, int k)
+{
+    __syncthreads();
+    const int n = (int)P.n;
+    __syncthreads();  // every thread has read n before anyone appends again
+    if (n > kAdcPool - kAdcThreads) pool_trim(P, k);
+}
+
+// The pool's k smallest keys, ascending, into the results of query b: one key
+// per thread, exchanged by shuffles inside a wave and through LDS across.
+__device__ void pool_finish(PoolLds &P, int k, int64_t b, uint32_t *__restrict__ ids, float *__restrict__ dist)
+{
+    const int t = threadIdx.x;
+    const int n = (int)P.n;  // <= k <= kAdcThreads
+    int np = 64;
+    while (np < n) np <<= 1;
+    uint64_t v = t < n ? P.key[t] : kNoKey;
+    for (int size = 2; size <= np; size <<= 1) {
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            uint64_t o;
+            if (stride < 64) {
+                o = (uint64_t)__shfl_xor((unsigned long long)v, stride);
+            } else {
+                __syncthreads();
+                P.key[t] = v;
+                __syncthreads();
+                o = P.key[t ^ stride];
+            }
+            const bool up = (t & size) == 0, low = (t & stride) == 0;
+            v = (up == low) == (o < v) ? o : v;
+        }
+    }
+    if (t < k) {
+        const bool have = t < n;
+        ids[b * k + t] = have ? (uint32_t)v : 0xFFFFFFFFu;
+        dist[b * k + t] = have ? o2f((uint32_t)(v >> 32)) : __builtin_huge_valf();
+    }
 }
 
 // Positions [o0, o1) of list l, kept inside [0, N) whatever the offsets hold;
@@ -153,18 +222,18 @@ __device__ __forceinline__ void list_range(const int64_t *__restrict__ offsets, 
 // Task setup of query b: the group size, the groups of each probed list
 // (prefix over the probes gives each group's slot j < 2P), and for every
 // group its list and code range: dl[b][j], dpos[b][j] = (first, end).
-__global__ __launch_bounds__(kAdcThreads) void adc_setup_kernel(const int32_t *__restrict__ probes, int P,
+__global__ __launch_bounds__(kSetupThreads) void adc_setup_kernel(const int32_t *__restrict__ probes, int P,
                                                                 const int64_t *__restrict__ offsets, int64_t C,
                                                                 int64_t N, int32_t *__restrict__ gcnt,
                                                                 int32_t *__restrict__ dl,
                                                                 longlong2 *__restrict__ dpos)
 {
-    __shared__ int32_t wsum[kAdcThreads / 64];
+    __shared__ int32_t wsum[kSetupThreads / 64];
     __shared__ int32_t s_g;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int64_t b = blockIdx.x;
     // thread t takes the contiguous probes [t * per, (t + 1) * per)
-    const int per = (P + kAdcThreads - 1) / kAdcThreads;  // <= 16
+    const int per = (P + kSetupThreads - 1) / kSetupThreads;  // <= 16
     int32_t nch[16];
     int64_t o0s[16], o1s[16];
     int32_t tot = 0;
@@ -186,7 +255,7 @@ __global__ __launch_bounds__(kAdcThreads) void adc_setup_kernel(const int32_t *_
     __syncthreads();
     if (t == 0) {
         int32_t n = 0;
-        for (int w = 0; w < kAdcThreads / 64; ++w) n += wsum[w];
+        for (int w = 0; w < kSetupThreads / 64; ++w) n += wsum[w];
         s_g = max(kAdcMinGroup, (n + P - 1) / P);
     }
     __syncthreads();
@@ -215,164 +284,311 @@ __global__ __launch_bounds__(kAdcThreads) void adc_setup_kernel(const int32_t *_
             dpos[base + j] = make_longlong2(f, min(o1s[e], f + (int64_t)G * kAdcChunk));
         }
     }
-    if (t == kAdcThreads - 1) gcnt[b] = j;  // the last thread ends past every group
+    if (t == kSetupThreads - 1) gcnt[b] = j;  // the last thread ends past every group
 }
 
-// Group slot (b, j) of every query (grid B * 2P).
-__global__ __launch_bounds__(kAdcThreads) void adc_group_kernel(
+struct Desc {
+    int64_t from, end;  // code positions
+    int32_t list;       // -1: none
+};
+
+// Part s of query b (grid B * S): its groups s, s + S, ..., `lists` of them at a
+// time. DS, SL: dims of a subspace and codeword slices per wave held in
+// registers (slice 4 m + q is codewords 64 q .. 64 q + 63 of subspace m, one per
+// lane; wave w holds slices SL w .. SL w + SL - 1); SL = 0: codewords of any
+// width are read from memory.
+template <int DS, int SL>
+__global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     const float *__restrict__ Q, int D, const float *__restrict__ cent, int P, const uint32_t *__restrict__ perm,
-    const uint8_t *__restrict__ codes, int M, const float *__restrict__ codebooks, int k,
+    const uint8_t *__restrict__ codes, int M, const float *__restrict__ codebooks, int k, int S, int lists,
     const int32_t *__restrict__ gcnt, const int32_t *__restrict__ dl, const longlong2 *__restrict__ dpos,
-    uint64_t *__restrict__ handoff, int32_t *__restrict__ hcnt)
+    uint64_t *__restrict__ handoff, int32_t *__restrict__ hcnt, uint32_t *__restrict__ ids, float *__restrict__ dist)
 {
-    extern __shared__ double dyn[];  // r [D] (fp64) then LUT [M][256] (fp32)
+    __shared__ __attribute__((aligned(16))) float lut[kAdcLutBytes / 4];  // [lists][M][256]
     __shared__ PoolLds pool;
-    double *r = dyn;
-    float *lut = reinterpret_cast<float *>(dyn + D);
-    const int t = threadIdx.x;
-    const int64_t b = blockIdx.x / (2 * P);
-    const int j = (int)(blockIdx.x - b * 2 * P);
-    if (j >= gcnt[b]) return;  // no such group
-    const int64_t slot = b * 2 * (int64_t)P + j;
-    const int32_t l = dl[slot];
-    const longlong2 range = dpos[slot];
-    const int dsub = D / M;
-    // the residual in fp32 (as defined), held in fp64 for the table's sums
-    for (int d = t; d < D; d += kAdcThreads) r[d] = (double)(Q[b * D + d] - cent[(int64_t)l * D + d]);
-    if (t == 0) {
-        pool.n = 0;
-        pool.thr = kNoKey;
-    }
-    __syncthreads();
-    if (dsub == 8) {
-        // the common 8-dimension subspace: two 16-byte codebook loads per entry
-        for (int e = t; e < M * kPqK; e += kAdcThreads) {
-            const float4 *wr = reinterpret_cast<const float4 *>(codebooks + (int64_t)e * 8);
-            const float4 w0 = wr[0], w1 = wr[1];
-            const float w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-            const double *rm = r + (e >> 8) * 8;
-            double acc = 0.0;
+    __shared__ Desc ring[4][kAdcMaxLists];  // descriptors of the steps around the current one
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t b = blockIdx.x / S;
+    const int part = (int)(blockIdx.x - b * S);
+    const int ng = (gcnt[b] - part + S - 1) / S;  // groups of this part
+    const int steps = (ng + lists - 1) / lists;
+    const int64_t g_first = b * 2 * (int64_t)P + part;
+    const float *qb = Q + b * D;
+    constexpr int NS = SL > 0 ? SL : 1;
+    // dims of the subspaces a wave's slices lie in, from dim wd on (subspaces of
+    // SL consecutive slices: one or two, three for SL = 10); lane W u + d holds
+    // dim d of list u of a step
+    constexpr bool WHOLE = SL == 1 || SL == 2 || SL == 4 || SL == 8;
+    constexpr int W = SL == 10 ? 16 : (SL == 8 || !WHOLE ? 2 : 1) * DS;
+    const int m_lo = wave * NS >> 2;
+    const int wd = m_lo * DS + lane % W;
+    double w[NS][DS];
+    if constexpr (SL > 0) {
 #pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                const double v = rm[d] - (double)w[d];
-                acc = fma(v, v, acc);
-            }
-            lut[e] = (float)acc;
-        }
-    } else {
-        for (int e = t; e < M * kPqK; e += kAdcThreads) {
-            const float *wr = codebooks + (int64_t)e * dsub;
-            const double *rm = r + (e >> 8) * dsub;
-            double acc = 0.0;
-            for (int d = 0; d < dsub; ++d) {
-                const double v = rm[d] - (double)wr[d];
-                acc = fma(v, v, acc);
-            }
-            lut[e] = (float)acc;
+        for (int i = 0; i < SL; ++i) {
+            const int sl = wave * SL + i;
+#pragma unroll
+            for (int d = 0; d < DS; ++d)
+                w[i][d] = sl < 4 * M ? (double)codebooks[((int64_t)(sl >> 2) * kPqK + 64 * (sl & 3) + lane) * DS + d] : 0.0;
         }
     }
+    const float ql = wd < D ? qb[wd] : 0.0f;
+    pool_init(pool);
+    auto load_desc = [&](int step) __attribute__((always_inline)) {
+        Desc v{0, 0, -1};
+        if (t < lists && step * lists + t < ng) {
+            const int64_t slot = g_first + (int64_t)(step * lists + t) * S;
+            const longlong2 rg = dpos[slot];
+            v = Desc{rg.x, rg.y, dl[slot]};
+        }
+        return v;
+    };
+    // this lane's centroid dim of a step's list (its descriptors are in the ring)
+    auto load_cent = [&](int step) __attribute__((always_inline)) {
+        float c = 0.0f;
+        if constexpr (SL > 0) {
+            const int u = lane / W;
+            const int32_t l = u < lists ? ring[step & 3][u].list : -1;
+            if (l >= 0 && wd < D) c = cent[(int64_t)l * D + wd];
+        }
+        return c;
+    };
+    // The tables of one step from its lanes' centroid dims. The residual r = q -
+    // c (fp32, as defined) is the same for every lane: it is formed once per
+    // list and dim, in the lane that holds the dim, and read from there into
+    // scalar registers (LDS broadcasts of it took the whole LDS bandwidth).
+    auto build = [&](int step, float cl, float *buf) __attribute__((always_inline)) {
+        const int nl = min(lists, ng - step * lists);
+        const double rl = (double)(ql - cl);
+        const int rlo = (int)(uint32_t)__double_as_longlong(rl), rhi = (int)(uint32_t)(__double_as_longlong(rl) >> 32);
+        for (int u = 0; u < nl; ++u) {
+            float *lt = buf + (size_t)u * M * kPqK;
+            if constexpr (SL > 0) {
+                double r[DS];
+                int m_of = -1;
+#pragma unroll
+                for (int i = 0; i < SL; ++i) {
+                    const int sl = wave * SL + i;
+                    if (sl < 4 * M) {
+                        const int m = (sl >> 2) - m_lo;
+                        if (WHOLE ? i % 4 == 0 : m != m_of) {  // (uniform) the slice's subspace
+                            m_of = m;
+#pragma unroll
+                            for (int d = 0; d < DS; ++d) {
+                                const int from = W * u + m * DS + d;
+                                r[d] = __hiloint2double(__builtin_amdgcn_readlane(rhi, from),
+                                                        __builtin_amdgcn_readlane(rlo, from));
+                            }
+                        }
+                        double acc = 0.0;
+#pragma unroll
+                        for (int d = 0; d < DS; ++d) {
+                            const double v = r[d] - w[i][d];
+                            acc = fma(v, v, acc);
+                        }
+                        lt[sl * 64 + lane] = (float)acc;
+                    }
+                }
+            } else {
+                const float *c = cent + (int64_t)__builtin_amdgcn_readfirstlane(ring[step & 3][u].list) * D;
+                const int dsub = D / M;
+                for (int sl = wave; sl < 4 * M; sl += kAdcWaves) {
+                    const float *wr = codebooks + ((int64_t)sl * 64 + lane) * dsub;
+                    const int d0 = (sl >> 2) * dsub;
+                    double acc = 0.0;
+                    for (int d = 0; d < dsub; ++d) {
+                        const double v = (double)(qb[d0 + d] - c[d0 + d]) - (double)wr[d];
+                        acc = fma(v, v, acc);
+                    }
+                    lt[sl * 64 + lane] = (float)acc;
+                }
+            }
+        }
+    };
+    const bool words = SL > 0 && M == 4 * SL;  // a code is SL words
+    // Loads are issued a table build ahead of their use: a step's descriptors
+    // three steps, its centroid dims one step, its codes one build. (Two table
+    // buffers of half as many lists, a build beside the scan before it, were
+    // slower: 1.31 against 1.20 ms.)
+    for (int i = 0; i < 3; ++i) {
+        const Desc v = load_desc(i);
+        if (t < lists) ring[i][t] = v;
+    }
+    Desc ahead = load_desc(3);
     __syncthreads();
-    // Keys are unique (distance bits, then the row id), so once a trim has
-    // left the k smallest, a key at or above the k-th of them cannot enter:
-    // only smaller keys are appended (a wave reserves its slots with one LDS
-    // atomic), and the pool is trimmed when the next chunk might not fit.
-    const int lane = t & 63;
-    for (int64_t c0 = range.x; c0 < range.y; c0 += kAdcChunk) {
-        const int len = (int)min((int64_t)kAdcChunk, range.y - c0);
-        const uint64_t thr = pool.thr;
-        for (int i0 = 0; i0 < len; i0 += kAdcThreads) {
-            const int i = i0 + t;
+    float cl = load_cent(0);
+    int room = kAdcPool;  // places the pool has at least
+    for (int step = 0; step < steps; ++step) {
+        const Desc *ds = ring[step & 3];
+        const int nl = min(lists, ng - step * lists);
+        if (t < lists) ring[(step + 3) & 3][t] = ahead;  // (read from the next barrier on)
+        ahead = load_desc(step + 4);
+        // code i of the step's groups laid end to end: list u, position
+        int64_t total = 0;
+        for (int u = 0; u < nl; ++u) total += ds[u].end - ds[u].from;
+        auto locate = [&](int64_t i, int &u) __attribute__((always_inline)) {
+            for (u = 0;; ++u) {
+                const int64_t from = ds[u].from, len = ds[u].end - from;
+                if (i < len) return from + i;
+                i -= len;
+            }
+        };
+        int cu = 0;
+        uint32_t cw[NS], id = 0;
+        if (t < total) {
+            const int64_t pos = locate(t, cu);
+            id = perm[pos];
+            // (the number of words is known at compile time: a branch per word
+            // would wait for each load before the next)
+            const uint32_t *a = reinterpret_cast<const uint32_t *>(codes + pos * M);
+            if (words) {
+#pragma unroll
+                for (int e = 0; e < SL; ++e) cw[e] = a[e];
+            }
+        }
+        const float cc = cl;
+        cl = load_cent(step + 1);
+        build(step, cc, lut);
+        __syncthreads();
+        for (int64_t c0 = 0; c0 < total; c0 += kAdcThreads) {
+            if (room < kAdcThreads) {  // (uniform)
+                pool_room(pool, k);
+                room = kAdcPool - (int)pool.n;
+                __syncthreads();  // every thread has read n before anyone appends
+            }
+            room -= (int)min((int64_t)kAdcThreads, total - c0);
             uint64_t key = kNoKey;
-            if (i < len) {
-                const int64_t pos = c0 + i;
-                const uint8_t *a = codes + pos * M;
+            const bool have = c0 + t < total;
+            if (have) {
+                const float *lt;
                 float acc = 0.0f;
-                if ((M & 3) == 0) {
-                    for (int m = 0; m < M; m += 4) {
-                        const uint32_t w = *reinterpret_cast<const uint32_t *>(a + m);
-                        acc = acc + lut[(m + 0) * kPqK + (w & 0xFFu)];
-                        acc = acc + lut[(m + 1) * kPqK + ((w >> 8) & 0xFFu)];
-                        acc = acc + lut[(m + 2) * kPqK + ((w >> 16) & 0xFFu)];
-                        acc = acc + lut[(m + 3) * kPqK + (w >> 24)];
+                if (words) {
+                    if (c0 > 0) {
+                        const int64_t pos = locate(c0 + t, cu);
+                        const uint32_t *a = reinterpret_cast<const uint32_t *>(codes + pos * M);
+                        id = perm[pos];
+#pragma unroll
+                        for (int e = 0; e < SL; ++e) cw[e] = a[e];
+                    }
+                    lt = lut + (size_t)cu * M * kPqK;
+#pragma unroll
+                    for (int e = 0; e < SL; ++e) {
+                        const float *l4 = lt + 4 * e * kPqK;
+                        acc = acc + l4[0 * kPqK + (cw[e] & 0xFFu)];
+                        acc = acc + l4[1 * kPqK + ((cw[e] >> 8) & 0xFFu)];
+                        acc = acc + l4[2 * kPqK + ((cw[e] >> 16) & 0xFFu)];
+                        acc = acc + l4[3 * kPqK + (cw[e] >> 24)];
                     }
                 } else {
-                    for (int m = 0; m < M; ++m) acc = acc + lut[m * kPqK + a[m]];
+                    const int64_t pos = locate(c0 + t, cu);
+                    lt = lut + (size_t)cu * M * kPqK;
+                    const uint8_t *a = codes + pos * M;
+                    if (c0 > 0) id = perm[pos];
+                    int m = 0;
+                    if ((M & 3) == 0) {
+                        for (; m < M; m += 4) {
+                            const uint32_t x = *reinterpret_cast<const uint32_t *>(a + m);
+                            acc = acc + lt[(m + 0) * kPqK + (x & 0xFFu)];
+                            acc = acc + lt[(m + 1) * kPqK + ((x >> 8) & 0xFFu)];
+                            acc = acc + lt[(m + 2) * kPqK + ((x >> 16) & 0xFFu)];
+                            acc = acc + lt[(m + 3) * kPqK + (x >> 24)];
+                        }
+                    }
+                    for (; m < M; ++m) acc = acc + lt[m * kPqK + a[m]];
                 }
-                key = ((uint64_t)f2o(acc) << 32) | perm[pos];
+                key = ((uint64_t)f2o(acc) << 32) | id;
             }
-            const bool keep = i < len && key < thr;
-            const uint64_t want = __ballot(keep);
-            if (want != 0) {
-                uint32_t wbase = 0;
-                if (lane == 0) wbase = atomicAdd(&pool.n, (uint32_t)__popcll(want));
-                wbase = __shfl(wbase, 0);
-                if (keep) pool.key[wbase + __popcll(want & ((1ull << lane) - 1))] = key;
-            }
+            pool_add(pool, key, have, pool.thr);
         }
         __syncthreads();
-        if ((int)pool.n > kAdcPool - kAdcChunk) pool_trim(pool, k);
     }
-    if ((int)pool.n > k) pool_trim(pool, k);
-    // the group's keys (at most k) and their count
-    uint64_t *out = handoff + slot * k;
     const int n = (int)pool.n;
-    for (int i = t; i < n; i += kAdcThreads) out[i] = pool.key[i];
-    if (t == 0) hcnt[slot] = n;
+    __syncthreads();
+    if (n > k) pool_trim(pool, k);
+    if (S == 1) {
+        pool_finish(pool, k, b, ids, dist);
+        return;
+    }
+    const int64_t slot = b * S + part;
+    const int m = min(n, k);
+    if (t < m) handoff[slot * k + t] = pool.key[t];
+    if (t == 0) hcnt[slot] = m;
 }
 
+// Query b's parts, 16 at a time: wave w takes the keys of part p0 + w.
 __global__ __launch_bounds__(kAdcThreads) void adc_merge_kernel(const uint64_t *__restrict__ handoff,
-                                                               const int32_t *__restrict__ hcnt, int P, int k,
-                                                               const int32_t *__restrict__ gcnt,
+                                                               const int32_t *__restrict__ hcnt, int S, int k,
                                                                uint32_t *__restrict__ ids, float *__restrict__ dist)
 {
     __shared__ PoolLds pool;
-    const int t = threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t b = blockIdx.x;
-    const uint64_t *in = handoff + b * 2 * (int64_t)P * k;
-    const int32_t *hc = hcnt + b * 2 * (int64_t)P;
-    const int G = gcnt[b];  // the query's groups
-    if (t == 0) pool.n = 0;
-    __syncthreads();
-    // append the groups' keys (n <= k each) while they fit the pool; trim it
-    // to the k smallest only when the next group would not fit
-    for (int g = 0; g < G; ++g) {
-        const int n = hc[g];
-        if ((int)pool.n + n > kAdcPool) pool_trim(pool, k);  // then pool.n = k, and k + n <= kAdcPool
-        const int base = (int)pool.n;
-        for (int i = t; i < n; i += kAdcThreads) pool.key[base + i] = in[(int64_t)g * k + i];
-        __syncthreads();
-        if (t == 0) pool.n = (uint32_t)(base + n);
-        __syncthreads();
-    }
-    if ((int)pool.n > k) pool_trim(pool, k);
-    // bitonic sort of the pool (at most k <= kAdcMaxK keys) ascending
-    const int n = (int)pool.n;
-    int np = 1;
-    while (np < n) np <<= 1;
-    for (int i = n + t; i < np; i += kAdcThreads) pool.key[i] = kNoKey;
-    __syncthreads();
-    for (int size = 2; size <= np; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = t; i < np; i += kAdcThreads) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    const bool up = (i & size) == 0;
-                    const uint64_t a = pool.key[i], c = pool.key[j];
-                    if ((a > c) == up) {
-                        pool.key[i] = c;
-                        pool.key[j] = a;
-                    }
-                }
-            }
-            __syncthreads();
+    pool_init(pool);
+    for (int p0 = 0; p0 < S; p0 += kAdcWaves) {
+        int most = 0;
+        for (int p = p0; p < min(S, p0 + kAdcWaves); ++p) most = max(most, hcnt[b * S + p]);
+        const int p = p0 + wave;
+        const int n = p < S ? hcnt[b * S + p] : 0;
+        const uint64_t *in = handoff + (b * S + min(p, S - 1)) * (int64_t)k;
+        for (int i0 = 0; i0 < most; i0 += 64) {
+            const int i = i0 + lane;
+            const uint64_t key = i < n ? in[i] : kNoKey;
+            pool_room(pool, k);
+            pool_add(pool, key, i < n, pool.thr);
         }
     }
-    for (int i = t; i < k; i += kAdcThreads) {
-        const bool have = i < n;
-        const uint64_t v = have ? pool.key[i] : kNoKey;
-        ids[b * k + i] = have ? (uint32_t)v : 0xFFFFFFFFu;
-        dist[b * k + i] = have ? o2f((uint32_t)(v >> 32)) : __builtin_huge_valf();
+    __syncthreads();
+    const int n = (int)pool.n;
+    __syncthreads();
+    if (n > k) pool_trim(pool, k);
+    pool_finish(pool, k, b, ids, dist);
+}
+
+using ScanKernel = decltype(&adc_scan_kernel<8, 4>);
+
+// The kernel that holds the codebooks in registers for the usual subspaces:
+// slices per wave = ceil(M / 4), at most 40 doubles a thread.
+ScanKernel scan_kernel(int dsub, int M)
+{
+    const int sl = (M + 3) / 4;
+    if (dsub == 8) {
+        switch (sl) {
+        case 1: return adc_scan_kernel<8, 1>;
+        case 2: return adc_scan_kernel<8, 2>;
+        case 3: return adc_scan_kernel<8, 3>;
+        case 4: return adc_scan_kernel<8, 4>;
+        case 5: return adc_scan_kernel<8, 5>;
+        }
+    } else if (dsub == 4) {
+        switch (sl) {
+        case 2: return adc_scan_kernel<4, 2>;
+        case 4: return adc_scan_kernel<4, 4>;
+        case 6: return adc_scan_kernel<4, 6>;
+        case 8: return adc_scan_kernel<4, 8>;
+        case 10: return adc_scan_kernel<4, 10>;
+        }
+    } else if (dsub == 16) {
+        switch (sl) {
+        case 1: return adc_scan_kernel<16, 1>;
+        case 2: return adc_scan_kernel<16, 2>;
+        }
     }
+    return adc_scan_kernel<1, 0>;
+}
+
+// Parts per query: one when the queries alone fill the chip several times over
+// (each part loads the codebooks and trims its own pool), else enough for four
+// rounds of workgroups, or for one when the batch is tiny (8 queries x 64
+// lists: 32 parts of two lists).
+int adc_parts(int64_t B, int P, int num_cus)
+{
+    int64_t s = 1;
+    if (B <= num_cus / 4)
+        s = (num_cus + B - 1) / std::max<int64_t>(B, 1);
+    else if (B < 4 * (int64_t)num_cus)
+        s = (4 * (int64_t)num_cus + B - 1) / B;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(s, P));
 }
 
 }  // namespace
@@ -380,19 +596,22 @@ __global__ __launch_bounds__(kAdcThreads) void adc_merge_kernel(const uint64_t *
 hipError_t launch_adc_scan(const float *Q, int64_t B, int D, const float *cent, int64_t C,
                            const int32_t *probes, int P, const int64_t *offsets, const uint32_t *perm,
                            int64_t N, const uint8_t *codes, int M, const float *codebooks, int k,
-                           const AdcScratch &w, uint32_t *ids, float *dist, hipStream_t s)
+                           const AdcScratch &w, uint32_t *ids, float *dist, int num_cus, hipStream_t s)
 {
     if (B <= 0) return hipSuccess;
-    hipLaunchKernelGGL(adc_setup_kernel, dim3((unsigned)B), dim3(kAdcThreads), 0, s, probes, P, offsets, C, N,
+    hipLaunchKernelGGL(adc_setup_kernel, dim3((unsigned)B), dim3(kSetupThreads), 0, s, probes, P, offsets, C, N,
                        w.gcnt, w.dl, w.dpos);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t lds = (size_t)D * sizeof(double) + (size_t)M * kPqK * sizeof(float);
-    hipLaunchKernelGGL(adc_group_kernel, dim3((unsigned)(B * 2 * P)), dim3(kAdcThreads), lds, s, Q, D, cent, P,
-                       perm, codes, M, codebooks, k, w.gcnt, w.dl, w.dpos, w.handoff, w.hcnt);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(adc_merge_kernel, dim3((unsigned)B), dim3(kAdcThreads), 0, s, w.handoff, w.hcnt, P, k,
-                       w.gcnt, ids, dist);
+    const int S = adc_parts(B, P, num_cus);
+    // lists whose tables are built at a time
+    // (and four at most for subspaces of 16 dims: 64 lanes hold a step's residuals)
+    const int lists = std::max(1, std::min(D / M == 16 ? 4 : kAdcMaxLists, kAdcLutBytes / (M * kPqK * 4)));
+    if ((size_t)lists * M * kPqK * 4 > (size_t)kAdcLutBytes) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(scan_kernel(D / M, M), dim3((unsigned)(B * S)), dim3(kAdcThreads), 0, s, Q, D, cent, P, perm,
+                       codes, M, codebooks, k, S, lists, w.gcnt, w.dl, w.dpos, w.handoff, w.hcnt, ids, dist);
+    if ((e = hipGetLastError()) != hipSuccess || S == 1) return e;
+    hipLaunchKernelGGL(adc_merge_kernel, dim3((unsigned)B), dim3(kAdcThreads), 0, s, w.handoff, w.hcnt, S, k, ids, dist);
     return hipGetLastError();
 }
 

@@ -1471,7 +1471,7 @@ ivf_status ivf_adc_scan(ivf_ctx *ctx, const float *queries, int64_t B, int32_t D
     AdcScratch w;
     layout_adc(ctx->ws, B, P, k, &w);
     TIMED("adc_scan", launch_adc_scan(queries, B, D, centroids, C, probes, P, offsets, perm, N, codes, M,
-                                      codebooks, k, w, out_ids, out_dist, ctx->stream));
+                                      codebooks, k, w, out_ids, out_dist, ctx->num_cus, ctx->stream));
     ctx->last_stats = nullptr;
     return IVF_OK;
 }

@@ -448,11 +448,12 @@ hipError_t launch_assign_cells(const void *rows, int rowtype, int64_t N, const f
 constexpr int kAdcMaxK = 1024;   // handoff per query (N_rerank)
 constexpr int kAdcMaxM = 60;     // subspaces (LUT of M x 256 floats in LDS, < 64 KiB)
 constexpr int kMaxAdcProbes = 4096;
-// Workspace of the scan: at most 2P groups per query, each with a handoff of
-// k keys and a descriptor (list id, code range), and each query's group count.
+// Workspace of the scan: at most 2P groups per query, each with a descriptor
+// (list id, code range), each query's group count, and, when a query is cut
+// into several parts (at most P), a handoff of k keys per part.
 struct AdcScratch {
-    uint64_t *handoff;  // [B * 2P * k]
-    int32_t *hcnt;      // [B * 2P] keys the group handed over (<= k)
+    uint64_t *handoff;  // [B * 2P * k], used up to B * parts * k
+    int32_t *hcnt;      // [B * 2P] keys the part handed over (<= k)
     int32_t *dl;        // [B * 2P] list of the group
     longlong2 *dpos;    // [B * 2P] first and end code position of the group
     int32_t *gcnt;      // [B] groups of the query
@@ -461,7 +462,7 @@ struct AdcScratch {
 hipError_t launch_adc_scan(const float *Q, int64_t B, int D, const float *cent, int64_t C,
                            const int32_t *probes, int P, const int64_t *offsets, const uint32_t *perm,
                            int64_t N, const uint8_t *codes, int M, const float *codebooks, int k,
-                           const AdcScratch &w, uint32_t *ids, float *dist, hipStream_t s);
+                           const AdcScratch &w, uint32_t *ids, float *dist, int num_cus, hipStream_t s);
 
 // ---- fp32 MFMA throughput probe (probe.hip) ---------------------------------
 // Enqueues the probe kernel for `iters` rounds; *flops = the work it does.

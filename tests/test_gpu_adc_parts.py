@@ -1,0 +1,36 @@
+"""The ADC scan's branches: every register layout of the codebooks (subspaces of
+4, 8 and 16 dims, whole and straddling waves) and the memory one, codes of one
+to sixty bytes, batches cut into many parts, a few and one, lists of one code
+and of many rounds, ties (equal codes, ids decide), and k from 1 to 1,024.
+Bit for bit the oracle's."""
+import numpy as np
+import pytest
+
+from test_gpu_adc import gpu_adc, ivf_ctx, setup  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,C,D,M,N,P,k", [
+    (1, 64, 128, 16, 9000, 64, 512), (3, 9, 32, 4, 30000, 9, 1024), (70, 40, 64, 8, 4000, 7, 33),
+    (300, 30, 96, 12, 3000, 5, 100), (1100, 20, 128, 16, 2000, 4, 50), (9, 30, 160, 20, 9000, 11, 300),
+    (5, 20, 32, 8, 5000, 6, 64), (5, 20, 64, 16, 5000, 6, 64), (5, 20, 96, 24, 5000, 6, 64),
+    (5, 20, 128, 32, 5000, 6, 64), (5, 20, 160, 40, 5000, 6, 64), (5, 20, 64, 4, 5000, 6, 64),
+    (5, 20, 128, 8, 5000, 6, 64), (4, 20, 240, 60, 4000, 6, 64), (4, 20, 256, 32, 4000, 6, 64),
+    (4, 20, 120, 15, 4000, 6, 64), (4, 20, 12, 3, 4000, 6, 1), (4, 300, 64, 8, 300, 256, 1000),
+])
+def test_branches_equal_the_oracle(ivf_ctx, oracle_mod, B, C, D, M, N, P, k):  # noqa: F811
+    q, c, probes, off, perm, codes, cb = setup(B + C + D + M, B, C, D, M, N, P, 0.6)
+    ids, dist = gpu_adc(ivf_ctx, q, c, probes, off, perm, codes, cb, k)
+    oids, odist = oracle_mod.adc_scan(q, c, probes, off, perm, codes, cb, k)
+    assert (ids == oids).all() and (dist.view(np.uint32) == odist.view(np.uint32)).all()
+
+
+@pytest.mark.parametrize("B", [2, 1100])
+def test_equal_codes_rank_by_id(ivf_ctx, oracle_mod, B):  # noqa: F811
+    q, c, probes, off, perm, codes, cb = setup(3, B, 6, 64, 8, 20000, 3)
+    codes[:] = codes[:1]
+    ids, dist = gpu_adc(ivf_ctx, q, c, probes, off, perm, codes, cb, 700)
+    n = min(B, 4)
+    oids, odist = oracle_mod.adc_scan(q[:n], c, probes[:n], off, perm, codes, cb, 700)
+    assert (ids[:n] == oids).all() and (dist[:n].view(np.uint32) == odist.view(np.uint32)).all()
