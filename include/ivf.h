@@ -49,6 +49,9 @@
  *     planes' key units; any other value in the call sends it to the f16, a
  *     centroid that does not quantise to the fp32 kernels (device flag, no
  *     host synchronisation). IVF_OPT_FP32_SCREEN forces the fp32 kernels.
+ *   - tables of at most 2,048 centroids, and batches of at most
+ *     min(32, padded D / 2) queries with nprobe <= 512 on tables of at most
+ *     65,536, are routed from the whole fp32 key matrix in two launches.
  * Either way the results are the exact ones above; the screen chosen changes
  * speed only.
  *
@@ -219,7 +222,8 @@ ivf_status ivf_build_lists(ivf_ctx *ctx, const int32_t *labels, int64_t N, int64
  * the workspace (waits on the stream):
  *   out[0] queries / rows that went to the full fp64 fallback scan
  *   out[1] rows whose top-1 was settled by fp64 re-evaluation of 2 candidates
- *   out[2] route: sum over queries of screened candidates kept
+ *   out[2] route: sum over queries of screened candidates kept (every centroid
+ *          where the whole key matrix is kept)
  *   out[3] route: queries whose candidate list overflowed
  *   out[4] route: centroids in the threshold sample
  *   out[5] assignment of uint8 rows: 1 when screened on int8 MFMA

@@ -250,6 +250,31 @@ struct RouteArgs {
     int rank_safe, rank_max;
 };
 
+// Direct route: every key of the batch kept, then one workgroup per query
+// selects from its row.
+constexpr int64_t kDirectMaxC = 65536;
+struct DirectArgs {
+    const float *queries;  // [nq, D] (already offset to the batch)
+    int64_t nq;
+    const float *cent;
+    int64_t C;             // <= kDirectMaxC
+    int D;
+    int k;
+    float *keys;           // [nq, stride]; stride = a multiple of 4 >= C, or 2 with C == 1
+    int64_t stride;
+    float *mc2_part;       // [ceil(C / 32)] largest norms
+    uint32_t *zero;        // 64 scalar words to set (null: not the first batch): zero but for
+    int total_word;        // the 64-bit candidate total at this word
+    uint32_t total_lo, total_hi;
+    double bound_coef;
+    int force_fallback;
+    int32_t *out_ids;      // [nq, k]
+    float *out_dist;       // [nq, k] or null
+    unsigned long long *stats;
+};
+hipError_t launch_direct_keys(int DP, const DirectArgs &a, hipStream_t s);
+hipError_t launch_direct_select(const DirectArgs &a, hipStream_t s);
+
 hipError_t launch_route_threshold(const RouteArgs &a, hipStream_t s);
 hipError_t launch_route_threshold_min(const RouteArgs &a, hipStream_t s);  // a.w set
 // Int8 routing of uint8-valued queries on the two quantised planes

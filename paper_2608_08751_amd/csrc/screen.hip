@@ -869,7 +869,96 @@ hipError_t launch_w(int mode, int rowtype, int DP, const ScreenArgs &a, int num_
     }
 }
 
+// ------------------------------------------------------------- direct route
+//
+// Keys of every centroid for a call whose keys all fit in scratch (see
+// direct_route): one launch in place of norms, bounds, sample and filter. A
+// wave takes 32 centroids, keeps their fragments and norms in registers and
+// walks tiles of 32 queries, with no LDS and no barrier: the small calls are
+// bound by launches and by the latency of one pass over the operands (a
+// table of 65,536 x 128 for 8 queries: 11-15 us, of which its 32 MB are 7).
+// Workgroup (i, 0) leaves its largest norm in mc2_part[i]; workgroup (0, 0)
+// sets the call's scalar words.
+template <int DP>
+__global__ __launch_bounds__(64) void direct_keys_kernel(DirectArgs a)
+{
+    constexpr int KH = DP / 2;
+    __shared__ float nh[32];  // -||c||^2 / 2
+    const int lane = threadIdx.x, col = lane & 31, h = lane >> 5;
+    if (a.zero && blockIdx.x == 0 && blockIdx.y == 0)
+        a.zero[lane] = lane == a.total_word ? a.total_lo : lane == a.total_word + 1 ? a.total_hi : 0u;
+    const int64_t c0 = (int64_t)blockIdx.x * 32;
+    float af[KH];
+    load_row<DP>(a.cent, c0 + col, c0 + col < a.C, a.D, h, af);
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+#pragma unroll
+    for (int t = 0; t < KH; t += 4) {
+        s0 = fma((double)af[t], (double)af[t], s0);
+        s1 = fma((double)af[t + 1], (double)af[t + 1], s1);
+        s2 = fma((double)af[t + 2], (double)af[t + 2], s2);
+        s3 = fma((double)af[t + 3], (double)af[t + 3], s3);
+    }
+    double sum = (s0 + s1) + (s2 + s3);
+    sum += __shfl_xor(sum, 32);
+    const float n = (float)sum;
+    if (h == 0) nh[col] = c0 + col < a.C ? -0.5f * n : -kInf;
+    if (blockIdx.y == 0) {
+        float m = n;
+        for (int o = 16; o > 0; o >>= 1) {
+            const float up = __shfl_xor(m, o);
+            m = up > m || up != up ? up : m;  // a NaN stays
+        }
+        if (lane == 0) a.mc2_part[blockIdx.x] = m;
+    }
+    __syncthreads();
+    f32x16 init;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) init[r] = nh[8 * (r >> 2) + 4 * h + (r & 3)];
+    for (int64_t q0 = (int64_t)blockIdx.y * 32; q0 < a.nq; q0 += (int64_t)gridDim.y * 32) {
+        float b[KH];
+        load_row<DP>(a.queries, q0 + col, q0 + col < a.nq, a.D, h, b);
+        f32x16 acc = init;
+#pragma unroll
+        for (int t = 0; t < KH; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[t], b[t], acc, 0, 0, 0);
+        if (q0 + col < a.nq) {
+            float *row = a.keys + (q0 + col) * a.stride;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int64_t c = c0 + 8 * g + 4 * h;
+                if (c + 4 <= a.stride)  // keys past C are +inf
+                    *reinterpret_cast<float4 *>(row + c) = make_float4(-2.0f * acc[4 * g], -2.0f * acc[4 * g + 1],
+                                                                       -2.0f * acc[4 * g + 2], -2.0f * acc[4 * g + 3]);
+                else if (c < a.C)  // a row of fewer than 4 keys: C == 1
+                    row[c] = -2.0f * acc[4 * g];
+            }
+        }
+    }
+}
+
+template <int DP>
+hipError_t launch_direct_dp(const DirectArgs &a, hipStream_t s)
+{
+    const int64_t nb = (a.C + 31) / 32, nt = (a.nq + 31) / 32;
+    // at least four waves per SIMD where there are that many (block, tile) pairs
+    const int64_t ny = std::max<int64_t>(1, std::min<int64_t>(nt, 4096 / nb));
+    hipLaunchKernelGGL((direct_keys_kernel<DP>), dim3((unsigned)nb, (unsigned)ny), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_direct_keys(int DP, const DirectArgs &a, hipStream_t s)
+{
+    switch (DP) {
+    case 32: return launch_direct_dp<32>(a, s);
+    case 64: return launch_direct_dp<64>(a, s);
+    case 96: return launch_direct_dp<96>(a, s);
+    case 128: return launch_direct_dp<128>(a, s);
+    case 192: return launch_direct_dp<192>(a, s);
+    case 256: return launch_direct_dp<256>(a, s);
+    default: return hipErrorInvalidValue;
+    }
+}
 
 hipError_t launch_screen(int mode, int rowtype, int DP, const ScreenArgs &a, int waves, int num_cus,
                          hipStream_t s)

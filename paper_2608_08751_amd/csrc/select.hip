@@ -174,7 +174,7 @@ __device__ uint32_t block_select(const uint32_t (&v)[V], int nv, int k, uint32_t
 // Routing threshold from the Cs sample keys of one query: the keys are cut
 // into groups of 16 consecutive sample centroids, tau = the rank_j-th smallest group
 // minimum (so about rank_j sample keys lie at or below tau), and every sample
-// key <= tau is emitted as a candidate. With Cs == 0, tau = +inf.
+// key <= tau is emitted as a candidate. Cs is at most 65,536.
 constexpr int kMaxGroups = 4096;
 constexpr int kGroupsPerThread = kMaxGroups / 256;
 
@@ -187,122 +187,6 @@ __device__ __forceinline__ uint32_t sample_id(const RouteArgs &a, int64_t s)
 {
     const int64_t st = a.sstride > 1 ? a.sstride : 1;
     return (uint32_t)((s / kChunk) * st * kChunk + s % kChunk);
-}
-
-__global__ __launch_bounds__(256) void route_threshold_kernel(RouteArgs a)
-{
-    if (plane_keys(a)) return;
-    const int64_t q = blockIdx.x;
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t sh[2];
-    __shared__ uint32_t s_cnt;
-    if (a.Cs == 0) {
-        if (threadIdx.x == 0) {
-            a.tau[q] = kInfF;
-            a.cand_cnt[q] = 0;
-        }
-        return;
-    }
-    const int G = (int)(a.Cs / 16);
-    const float *kr = a.keys + q * a.Cs;
-    uint32_t v[kGroupsPerThread];
-    int nv = 0;
-#pragma unroll
-    for (int e = 0; e < kGroupsPerThread; ++e) {
-        const int g = threadIdx.x + 256 * e;
-        v[e] = 0xFFFFFFFFu;
-        if (g < G) {
-            const float4 *p = reinterpret_cast<const float4 *>(kr + 16 * (int64_t)g);
-            float m = kInfF;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float4 w = p[i];
-                m = fminf(m, fminf(fminf(w.x, w.y), fminf(w.z, w.w)));
-            }
-            v[e] = f2o(m);
-            nv = e + 1;
-        }
-    }
-    if (threadIdx.x == 0) s_cnt = 0;
-    const float th = o2f(block_select(v, nv, min(a.rank_j, G), hist, sh));
-    const float4 *k4 = reinterpret_cast<const float4 *>(kr);
-    for (int64_t i = threadIdx.x; i < a.Cs / 4; i += blockDim.x) {
-        const float4 w = k4[i];
-        const float kk[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (kk[e] <= th) {
-                const uint32_t slot = atomicAdd(&s_cnt, 1u);
-                if (slot < (uint32_t)a.L)
-                    a.cand[q * a.L + slot] = make_uint2(__float_as_uint(kk[e]), sample_id(a, 4 * i + e));
-            }
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        a.tau[q] = th;
-        a.cand_cnt[q] = s_cnt;
-    }
-}
-
-// The same threshold with the query's sample keys read once: thread t keeps
-// groups t, t + 256, ... (GPT of them, 16 keys each) in registers, takes
-// their minima for the selection and then emits its own keys <= tau. Used
-// when the sample has at most 256 * GPT groups.
-template <int GPT>
-__global__ __launch_bounds__(256) void route_threshold_reg_kernel(RouteArgs a)
-{
-    if (plane_keys(a)) return;
-    const int64_t q = blockIdx.x;
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t sh[2];
-    __shared__ uint32_t s_cnt;
-    const int G = (int)(a.Cs / 16);
-    const float4 *k4 = reinterpret_cast<const float4 *>(a.keys + q * a.Cs);
-    float4 w[GPT][4];
-    uint32_t v[GPT];
-    int nv = 0;
-#pragma unroll
-    for (int e = 0; e < GPT; ++e) {
-        const int g = threadIdx.x + 256 * e;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w[e][i] = g < G ? k4[4 * (int64_t)g + i] : make_float4(kInfF, kInfF, kInfF, kInfF);
-    }
-#pragma unroll
-    for (int e = 0; e < GPT; ++e) {
-        float m = kInfF;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) m = fminf(m, fminf(fminf(w[e][i].x, w[e][i].y), fminf(w[e][i].z, w[e][i].w)));
-        v[e] = 0xFFFFFFFFu;
-        if (threadIdx.x + 256 * e < G) {
-            v[e] = f2o(m);
-            nv = e + 1;
-        }
-    }
-    if (threadIdx.x == 0) s_cnt = 0;
-    const float th = o2f(block_select(v, nv, min(a.rank_j, G), hist, sh));
-#pragma unroll
-    for (int e = 0; e < GPT; ++e) {
-        const int g = threadIdx.x + 256 * e;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float kk[4] = {w[e][i].x, w[e][i].y, w[e][i].z, w[e][i].w};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (g < G && kk[c] <= th) {
-                    const uint32_t slot = atomicAdd(&s_cnt, 1u);
-                    if (slot < (uint32_t)a.L)
-                        a.cand[q * a.L + slot] = make_uint2(__float_as_uint(kk[c]), sample_id(a, 16 * g + 4 * i + c));
-                }
-            }
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        a.tau[q] = th;
-        a.cand_cnt[q] = s_cnt;
-    }
 }
 
 // The threshold from the group minima the fp32 keys pass wrote: tau = the
@@ -517,9 +401,55 @@ __global__ __launch_bounds__(256) void route_select_kernel(RouteArgs a)
     }
 }
 
-// Exact fp64 scan of all centroids for the queries on the worklist: a running
-// best list of K2 entries plus a buffer of new entries that beat its k-th
-// element; the union is re-sorted whenever the buffer fills.
+// Exact fp64 scan of all centroids for one query (its row staged in LDS): a
+// running best list of K2 entries plus a buffer of new entries that beat its
+// k-th element; the union is re-sorted whenever the buffer fills. bd, bi:
+// 2 K2 entries, K2 the first power of two from max(k, workgroup) on.
+__device__ void exact_topk(const float *__restrict__ cent, int64_t C, int D, int k, const float *qrow, double *bd,
+                           int *bi, uint32_t &s_cnt, int32_t *out_ids, float *out_dist)
+{
+    int K2 = blockDim.x;
+    while (K2 < k) K2 <<= 1;
+    for (int i = threadIdx.x; i < 2 * K2; i += blockDim.x) {
+        bd[i] = kInfD;
+        bi[i] = 0x7fffffff;
+    }
+    if (threadIdx.x == 0) s_cnt = 0;
+    __syncthreads();
+    double wd = kInfD;
+    int wi = 0x7fffffff;
+    for (int64_t base = 0; base < C; base += blockDim.x) {
+        const int64_t c = base + threadIdx.x;
+        if (c < C) {
+            const double d = exact_dist(qrow, cent + c * D, D);
+            if (dist_lt(d, (int)c, wd, wi)) {
+                const uint32_t slot = atomicAdd(&s_cnt, 1u);
+                bd[K2 + slot] = d;
+                bi[K2 + slot] = (int)c;
+            }
+        }
+        __syncthreads();
+        const bool last = base + blockDim.x >= C;
+        if (s_cnt > (uint32_t)(K2 - blockDim.x) || last) {
+            bitonic_sort(bd, bi, 2 * K2, dist_lt);
+            for (int i = K2 + threadIdx.x; i < 2 * K2; i += blockDim.x) {
+                bd[i] = kInfD;
+                bi[i] = 0x7fffffff;
+            }
+            if (threadIdx.x == 0) s_cnt = 0;
+            __syncthreads();
+            wd = bd[k - 1];
+            wi = bi[k - 1];
+        }
+        __syncthreads();
+    }
+    for (int i = threadIdx.x; i < k; i += blockDim.x) {
+        out_ids[i] = bi[i];
+        if (out_dist) out_dist[i] = (float)bd[i];
+    }
+}
+
+// The queries on the worklist.
 __global__ __launch_bounds__(256) void route_fallback_kernel(RouteArgs a)
 {
     __shared__ double bd[2048];
@@ -542,49 +472,152 @@ __global__ __launch_bounds__(256) void route_fallback_kernel(RouteArgs a)
         }
     }
     const uint32_t total = *a.wl_cnt;
-    int K2 = 256;
-    while (K2 < a.k) K2 <<= 1;
     for (uint32_t w = blockIdx.x; w < total; w += gridDim.x) {
         const int64_t q = a.wl[w];
-        for (int i = threadIdx.x; i < 2 * K2; i += blockDim.x) {
-            bd[i] = kInfD;
-            bi[i] = 0x7fffffff;
-        }
         for (int d = threadIdx.x; d < a.D; d += blockDim.x) qrow[d] = a.queries[q * a.D + d];
-        if (threadIdx.x == 0) s_cnt = 0;
+        exact_topk(a.cent, a.C, a.D, a.k, qrow, bd, bi, s_cnt, a.out_ids + q * a.k,
+                   a.out_dist ? a.out_dist + q * a.k : nullptr);
         __syncthreads();
-        double wd = kInfD;
-        int wi = 0x7fffffff;
-        for (int64_t base = 0; base < a.C; base += blockDim.x) {
-            const int64_t c = base + threadIdx.x;
-            if (c < a.C) {
-                const double d = exact_dist(qrow, a.cent + c * a.D, a.D);
-                if (dist_lt(d, (int)c, wd, wi)) {
-                    const uint32_t slot = atomicAdd(&s_cnt, 1u);
-                    bd[K2 + slot] = d;
-                    bi[K2 + slot] = (int)c;
+    }
+}
+
+// Direct route: one workgroup of T threads selects a query's k nearest from
+// its row of keys, V of them per thread in registers. tau = the k-th smallest
+// of the threads' minima (k of the keys are no larger, so it is no smaller than
+// the k-th key, and with many keys per thread only a few more lie below it), or
+// the k-th key itself where k is over half the threads or the minima let too
+// many keys through; every centroid that can be among the k nearest has a key
+// of at most tau + 2B and is re-evaluated in fp64. A query whose window holds
+// more than kDirectCand, or whose bound is not finite, is scanned here in
+// fp64: no worklist and no further launch.
+// Rounds of latency bound this kernel (a selection of four passes, a gather,
+// a count), not bytes: 12 us for 1,000 queries on 1,024 x 128 with k = 16, 28
+// for 8 queries on 65,536 x 128 with k = 64.
+constexpr int kDirectCand = 2048;
+
+template <int T, int V>
+constexpr int direct_cand()  // also the scan's 2 K2 entries with k <= T V
+{
+    return 2 * T * V < kDirectCand ? 2 * T * V : kDirectCand;
+}
+
+template <int T, int V>
+__global__ __launch_bounds__(T) void direct_select_kernel(DirectArgs a)
+{
+    static_assert(V % 4 == 0, "keys are read in fours");
+    constexpr int kCand = direct_cand<T, V>();
+    __shared__ double bd[kCand];
+    __shared__ int bi[kCand];
+    __shared__ __attribute__((aligned(16))) float qrow[256];
+    __shared__ uint32_t hist[256];
+    __shared__ uint32_t sh[2];
+    __shared__ uint32_t s_cnt;
+    __shared__ double s_x2;
+    __shared__ uint32_t s_m[T / 64];
+    const int64_t q = blockIdx.x;
+    const int t = threadIdx.x;
+    const float *kr = a.keys + q * a.stride;
+    uint32_t v[V];
+    uint32_t mn = 0xFFFFFFFFu;
+#pragma unroll
+    for (int e = 0; e < V / 4; ++e) {
+        const int i = 4 * (t + T * e);
+        float4 w = make_float4(kInfF, kInfF, kInfF, kInfF);
+        if (i + 4 <= a.stride && i < a.C)
+            w = *reinterpret_cast<const float4 *>(kr + i);
+        else if (i < a.C)
+            w.x = kr[i];
+        v[4 * e] = f2o(w.x);
+        v[4 * e + 1] = f2o(w.y);
+        v[4 * e + 2] = f2o(w.z);
+        v[4 * e + 3] = f2o(w.w);
+        mn = min(min(mn, min(v[4 * e], v[4 * e + 1])), min(v[4 * e + 2], v[4 * e + 3]));
+    }
+    // the largest norm; NaN and infinities order above the finite ones
+    uint32_t m = 0;
+    for (int i = t; i < (int)((a.C + 31) / 32); i += T)
+        m = max(m, __float_as_uint(a.mc2_part[i]) & 0x7FFFFFFFu);
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+    if ((t & 63) == 0) s_m[t >> 6] = m;
+    for (int d = t; d < a.D; d += T) qrow[d] = a.queries[q * a.D + d];
+    if (t < 64) {
+        double s = 0.0;
+        for (int d = t; d < a.D; d += 64) {
+            const double x = (double)a.queries[q * a.D + d];
+            s = fma(x, x, s);
+        }
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (t == 0) {
+            s_x2 = s;
+            s_cnt = 0;
+        }
+    }
+    __syncthreads();
+    for (int i = 0; i < T / 64; ++i) m = max(m, s_m[i]);
+    const double x2 = s_x2, B2 = 2.0 * key_bound(a.bound_coef, m, x2);
+    const double M = (double)__uint_as_float(m);
+    bool exact = a.force_fallback || !(M + 2.0 * sqrt(x2) * sqrt(M) < 1e37);  // sums of finite keys
+    bool over = false;
+    int nr = 0;
+    if (!exact) {
+        const bool by_min = a.k <= T / 2 && V > 4;
+#pragma unroll 1
+        for (int pass = by_min ? 0 : 1; pass < 2; ++pass) {
+            uint32_t tau;
+            if (pass == 0) {
+                const uint32_t vm[1] = {mn};
+                tau = block_select(vm, 1, a.k, hist, sh);
+            } else {
+                tau = block_select(v, V, a.k, hist, sh);
+            }
+            const double thr = (double)o2f(tau) + B2;
+            // the keys are compared as floats no smaller than thr
+            float tf = (float)thr;
+            if ((double)tf < thr) tf = nextafterf(tf, kInfF);
+            const uint32_t to = f2o(tf);
+            if (mn <= to) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const int id = 4 * (t + T * (e / 4)) + e % 4;
+                    if (v[e] <= to && id < a.C) {
+                        const uint32_t slot = atomicAdd(&s_cnt, 1u);
+                        if (slot < kCand) bi[slot] = id;
+                    }
                 }
             }
             __syncthreads();
-            const bool last = base + blockDim.x >= a.C;
-            if (s_cnt > (uint32_t)(K2 - blockDim.x) || last) {
-                bitonic_sort(bd, bi, 2 * K2, dist_lt);
-                for (int i = K2 + threadIdx.x; i < 2 * K2; i += blockDim.x) {
-                    bd[i] = kInfD;
-                    bi[i] = 0x7fffffff;
-                }
-                if (threadIdx.x == 0) s_cnt = 0;
-                __syncthreads();
-                wd = bd[a.k - 1];
-                wi = bi[a.k - 1];
-            }
+            nr = (int)s_cnt;
+            over = nr > kCand;
+            if (!over) break;
+            __syncthreads();
+            if (t == 0) s_cnt = 0;
             __syncthreads();
         }
-        for (int i = threadIdx.x; i < a.k; i += blockDim.x) {
-            a.out_ids[q * a.k + i] = bi[i];
-            if (a.out_dist) a.out_dist[q * a.k + i] = (float)bd[i];
+        exact = over;
+    }
+    if (exact) {
+        if (t == 0) {
+            atomicAdd(a.stats + kStatFallback, 1ull);
+            if (over) atomicAdd(a.stats + kStatOverflow, 1ull);
         }
         __syncthreads();
+        exact_topk(a.cent, a.C, a.D, a.k, qrow, bd, bi, s_cnt, a.out_ids + q * a.k,
+                   a.out_dist ? a.out_dist + q * a.k : nullptr);
+        return;
+    }
+    for (int i = t; i < nr; i += T) bd[i] = exact_dist_lds4(qrow, a.cent + (int64_t)bi[i] * a.D, a.D);
+    __syncthreads();
+    // rank of each re-evaluated candidate in (distance, id) order
+    for (int i = t; i < nr; i += T) {
+        const double di = bd[i];
+        const int ii = bi[i];
+        int rank = 0;
+#pragma unroll 4
+        for (int j = 0; j < nr; ++j) rank += dist_lt(bd[j], bi[j], di, ii) ? 1 : 0;
+        if (rank < a.k) {
+            a.out_ids[q * a.k + rank] = ii;
+            if (a.out_dist) a.out_dist[q * a.k + rank] = (float)di;
+        }
     }
 }
 
@@ -615,17 +648,7 @@ hipError_t launch_centroid_norms(const float *cent, int64_t C, int D, float *cno
 
 hipError_t launch_route_threshold(const RouteArgs &a, hipStream_t s)
 {
-    const int64_t G = a.Cs / 16;
-    if (a.Cs > 0 && a.kmin && G <= kMaxGroups)
-        hipLaunchKernelGGL(route_threshold_gmin_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a);
-    else if (a.Cs > 0 && G <= 256)
-        hipLaunchKernelGGL(route_threshold_reg_kernel<1>, dim3((unsigned)a.nq), dim3(256), 0, s, a);
-    else if (a.Cs > 0 && G <= 512)
-        hipLaunchKernelGGL(route_threshold_reg_kernel<2>, dim3((unsigned)a.nq), dim3(256), 0, s, a);
-    else if (a.Cs > 0 && G <= 1024)
-        hipLaunchKernelGGL(route_threshold_reg_kernel<4>, dim3((unsigned)a.nq), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(route_threshold_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(route_threshold_gmin_kernel, dim3((unsigned)a.nq), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -639,6 +662,27 @@ hipError_t launch_route_select(const RouteArgs &a, hipStream_t s)
 {
     const size_t lds = (size_t)a.L * (sizeof(double) + sizeof(int));
     hipLaunchKernelGGL(route_select_kernel, dim3((unsigned)a.nq), dim3(256), lds, s, a);
+    return hipGetLastError();
+}
+
+// Threads by table size: up to 256 centroids one wave holds the row and needs
+// no barrier (a call of 16,384 queries on 256 x 256: 162 us, 291 with four
+// waves);
+// a workgroup of 256 keeps up to 2,048 keys, eight per thread, and several
+// share a CU; past that 1,024 threads read the row.
+hipError_t launch_direct_select(const DirectArgs &a, hipStream_t s)
+{
+    const dim3 grid((unsigned)a.nq);
+    if (a.C <= 64 * 4)
+        hipLaunchKernelGGL((direct_select_kernel<64, 4>), grid, dim3(64), 0, s, a);
+    else if (a.C <= 256 * 4)
+        hipLaunchKernelGGL((direct_select_kernel<256, 4>), grid, dim3(256), 0, s, a);
+    else if (a.C <= 256 * 8)
+        hipLaunchKernelGGL((direct_select_kernel<256, 8>), grid, dim3(256), 0, s, a);
+    else if (a.C <= 1024 * 16)
+        hipLaunchKernelGGL((direct_select_kernel<1024, 16>), grid, dim3(1024), 0, s, a);
+    else
+        hipLaunchKernelGGL((direct_select_kernel<1024, 64>), grid, dim3(1024), 0, s, a);
     return hipGetLastError();
 }
 
