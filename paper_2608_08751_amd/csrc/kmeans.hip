@@ -226,6 +226,122 @@ __global__ __launch_bounds__(256) void update_small_kernel(const XT *__restrict_
     if (lane == 0) jpart[j] = jp;
 }
 
+// The same sums with a list per group of DS lanes: lane (q, d) walks the
+// members of list q of the wave's 64 / DS lists by itself, so every lane adds
+// its own dimension (in the kernel above one lane in 64 / DS does) and nothing
+// is shuffled. A lane's loads run two batches of K members ahead of its
+// chain: ids of batch b + 2 and values of batch b + 1 are in flight while
+// batch b is added. The lists of all groups advance through the rows together
+// (members ascend within a list), so a row's subspaces are read at about one
+// time and partly come from the caches after the first. Bound by the serial
+// chain of the longest list and by 32-byte gathers of 128-byte lines: 2^20
+// rows of 16 subspaces of 8, lists of 4,096 on average, 778 -> 600 us; 2^20
+// rows of 8 in 65,536 lists 340 -> 47 us.
+template <typename XT, int DS, int K>
+__global__ __launch_bounds__(64) void update_lanes_kernel(const XT *__restrict__ X, int64_t N, int D, int64_t ld,
+                                                          const float *__restrict__ cin, int64_t C,
+                                                          const int64_t *__restrict__ counts,
+                                                          const int64_t *__restrict__ offsets,
+                                                          const uint32_t *__restrict__ perm, uint64_t seed,
+                                                          int32_t iter, float *__restrict__ cout,
+                                                          double *__restrict__ jpart, int64_t x_group)
+{
+    typedef typename SumType<XT>::type S;
+    constexpr int R = 64 / DS;  // lists per wave
+    const int lane = threadIdx.x;
+    const int d = lane % DS;
+    int64_t g = blockIdx.y, bx = blockIdx.x;
+    if (gridDim.y % 8 == 0) {  // neighbouring groups, which share cache lines, on one XCD
+        const int64_t id = g * gridDim.x + bx, r = id >> 3;
+        g = (id & 7) * (gridDim.y / 8) + r / gridDim.x;
+        bx = r % gridDim.x;
+    }
+    const int64_t j = bx * R + lane / DS;
+    const bool mine = j < C;
+    {
+        X += g * x_group;
+        cin += g * C * D;
+        cout += g * C * D;
+        counts += g * C;
+        offsets += g * (C + 1);
+        perm += g * N;
+        jpart += g * C;
+        seed += (uint64_t)g;
+    }
+    const int64_t n = mine ? counts[j] : 0;
+    const uint32_t *pl = n > 0 ? perm + offsets[j] : perm;  // an empty list reads row perm[0]
+    const int64_t last = n > 0 ? n - 1 : 0;
+    int64_t nmin = n, nmax = n;
+    for (int o = 32; o > 0; o >>= 1) {
+        nmin = min(nmin, (int64_t)__shfl_xor((long long)nmin, o));
+        nmax = max(nmax, (int64_t)__shfl_xor((long long)nmax, o));
+    }
+    const XT *xd = X + d;
+    const double cj = mine ? (double)cin[j * D + d] : 0.0;
+    S sum = 0;
+    double jp = 0.0;
+    uint32_t id[K];
+    XT va[K], vb[K];
+    auto ids = [&](int64_t t0) {
+        if (t0 + K <= nmin) {
+#pragma unroll
+            for (int m = 0; m < K; ++m) id[m] = pl[t0 + m];
+        } else {  // past the list's end its last member again
+            const int64_t base = min(t0, last);
+            const int left = (int)min(last - base, (int64_t)K);
+#pragma unroll
+            for (int m = 0; m < K; ++m) id[m] = pl[base + min(m, left)];
+        }
+    };
+    auto rows = [&](XT(&v)[K]) {
+#pragma unroll
+        for (int m = 0; m < K; ++m) v[m] = xd[(int64_t)id[m] * ld];
+    };
+    auto add = [&](const XT(&v)[K], int64_t t0) {
+        if (t0 + K <= nmin) {
+#pragma unroll
+            for (int m = 0; m < K; ++m) {
+                sum += (S)v[m];
+                const double t = (double)v[m] - cj;
+                jp = fma(t, t, jp);
+            }
+        } else {
+            const int left = (int)min(max(n - t0, (int64_t)0), (int64_t)K);
+#pragma unroll
+            for (int m = 0; m < K; ++m) {
+                if (m < left) {
+                    sum += (S)v[m];
+                    const double t = (double)v[m] - cj;
+                    jp = fma(t, t, jp);
+                }
+            }
+        }
+    };
+    if (nmax > 0) {
+        ids(0);
+        rows(va);
+        ids(K);
+        for (int64_t t0 = 0; t0 < nmax; t0 += 2 * K) {
+            rows(vb);
+            ids(t0 + 2 * K);
+            add(va, t0);
+            rows(va);
+            ids(t0 + 3 * K);
+            add(vb, t0 + K);
+        }
+    }
+    for (int off = DS / 2; off > 0; off >>= 1) jp += __shfl_xor(jp, off);
+    if (mine) {
+        float r;
+        if (n > 0)
+            r = (float)((double)sum / (double)n);
+        else
+            r = (float)X[reseed_row(seed, iter, j, N) * ld + d];
+        cout[j * D + d] = r;
+        if (d == 0) jpart[j] = jp;
+    }
+}
+
 // uint8 rows with D = 16 U (U = 1, 2, 4, 8 or 16 lanes per row) and 16-byte
 // aligned rows: lane l reads the 16 bytes of dimensions 16 (l % U) .. + 15 of
 // member l / U of each group of 64 / U members (one 16-byte load per lane,
@@ -331,6 +447,11 @@ __global__ __launch_bounds__(1024) void sum_parts_kernel(const double *__restric
     if (threadIdx.x == 0) *out = s[0];
 }
 
+// A list per group of lanes from this many waves on: below, the chip is idle
+// and a wave per list shortens the chains (1M rows, 256 x 8, 32 waves: 582 us
+// there).
+constexpr int64_t kLanesWaves = 128;
+
 }  // namespace
 
 hipError_t launch_kmeans_update(const void *rows, int rowtype, int64_t N, int D, int64_t ld,
@@ -352,23 +473,39 @@ hipError_t launch_kmeans_update(const void *rows, int rowtype, int64_t N, int D,
         // dims per lane: 1, 2 or 4 (D <= 64, 128, 256), member rows in flight 32, 16, 8
         const int K = D <= 64 ? 1 : D <= 128 ? 2 : 4;
         const bool small = D == 1 || D == 2 || D == 4 || D == 8 || D == 16 || D == 32;
+        const bool lanes = (int64_t)groups * C * D / 64 >= kLanesWaves;
+#define IVF_UPDATE_LANES(XT, DS_, K_)                                                                          \
+    hipLaunchKernelGGL((update_lanes_kernel<XT, DS_, K_>), dim3((unsigned)((C + 64 / DS_ - 1) / (64 / DS_)),    \
+                                                                (unsigned)groups),                             \
+                       dim3(64), 0, s, (const XT *)rows, N, D, ld, cent_in, C, counts, offsets, perm, seed,     \
+                       iter, cent_out, jpart, x_group)
+// Batches of 64 members hide the gathers' latency where lists are long (2^20
+// rows in 1,000 lists of 32 dims: 347 us, 439 with 32); lists of 16 members
+// would mostly load their last one again (65,536 lists of 32: 96 us with 16,
+// 160 with 32, 343 with 64).
 #define IVF_UPDATE_SMALL(XT, DS_)                                                                              \
-    hipLaunchKernelGGL((update_small_kernel<XT, DS_>), grid, dim3(256), 0, s, (const XT *)rows, N, D, ld, cent_in, \
-                       C, counts, offsets, perm, seed, iter, cent_out, jpart, x_group)
+    if (lanes && N / C >= 256)                                                                                 \
+        IVF_UPDATE_LANES(XT, DS_, 64);                                                                         \
+    else if (lanes)                                                                                            \
+        IVF_UPDATE_LANES(XT, DS_, 16);                                                                         \
+    else                                                                                                       \
+        hipLaunchKernelGGL((update_small_kernel<XT, DS_>), grid, dim3(256), 0, s, (const XT *)rows, N, D, ld,   \
+                           cent_in, C, counts, offsets, perm, seed, iter, cent_out, jpart, x_group)
 #define IVF_UPDATE_SMALL_ALL(XT)         \
     do {                                 \
-        if (D == 1)                      \
+        if (D == 1) {                    \
             IVF_UPDATE_SMALL(XT, 1);     \
-        else if (D == 2)                 \
+        } else if (D == 2) {             \
             IVF_UPDATE_SMALL(XT, 2);     \
-        else if (D == 4)                 \
+        } else if (D == 4) {             \
             IVF_UPDATE_SMALL(XT, 4);     \
-        else if (D == 8)                 \
+        } else if (D == 8) {             \
             IVF_UPDATE_SMALL(XT, 8);     \
-        else if (D == 16)                \
+        } else if (D == 16) {            \
             IVF_UPDATE_SMALL(XT, 16);    \
-        else                             \
+        } else {                         \
             IVF_UPDATE_SMALL(XT, 32);    \
+        }                                \
     } while (0)
 #define IVF_UPDATE_LAUNCH(XT, K_)                                                                              \
     hipLaunchKernelGGL((update_kernel<XT, K_>), grid, dim3(256), 0, s, (const XT *)rows, N, D, ld, cent_in, C, \
@@ -396,6 +533,7 @@ hipError_t launch_kmeans_update(const void *rows, int rowtype, int64_t N, int D,
 #undef IVF_UPDATE_LAUNCH
 #undef IVF_UPDATE_SMALL_ALL
 #undef IVF_UPDATE_SMALL
+#undef IVF_UPDATE_LANES
     }
     if (objective)
         hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)groups), dim3(1024), 0, s, jpart, C, objective);
