@@ -45,6 +45,7 @@
 #include "ivf_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ivf {
 namespace {
@@ -292,6 +293,12 @@ struct Desc {
     int32_t list;       // -1: none
 };
 
+// A wave's SL slices lie in whole subspaces, or in a known number of slices of one
+constexpr bool whole_slices(int SL) { return SL == 1 || SL == 2 || SL == 4 || SL == 8; }
+// and cover this many dims: so many lanes hold a list's residuals, 64 of them
+// those of a step's lists
+constexpr int slice_dims(int DS, int SL) { return SL == 10 ? 16 : (SL == 8 || !whole_slices(SL) ? 2 : 1) * DS; }
+
 // Part s of query b (grid B * S): its groups s, s + S, ..., `lists` of them at a
 // time. DS, SL: dims of a subspace and codeword slices per wave held in
 // registers (slice 4 m + q is codewords 64 q .. 64 q + 63 of subspace m, one per
@@ -319,18 +326,20 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     // dims of the subspaces a wave's slices lie in, from dim wd on (subspaces of
     // SL consecutive slices: one or two, three for SL = 10); lane W u + d holds
     // dim d of list u of a step
-    constexpr bool WHOLE = SL == 1 || SL == 2 || SL == 4 || SL == 8;
-    constexpr int W = SL == 10 ? 16 : (SL == 8 || !WHOLE ? 2 : 1) * DS;
+    constexpr bool WHOLE = whole_slices(SL);
+    constexpr int W = slice_dims(DS, SL);
     const int m_lo = wave * NS >> 2;
     const int wd = m_lo * DS + lane % W;
-    double w[NS][DS];
+    // three slices of 16 dims leave no room for fp64: converted at each use (exact)
+    typedef typename std::conditional<DS * SL <= 40, double, float>::type WT;
+    WT w[NS][DS];
     if constexpr (SL > 0) {
 #pragma unroll
         for (int i = 0; i < SL; ++i) {
             const int sl = wave * SL + i;
 #pragma unroll
             for (int d = 0; d < DS; ++d)
-                w[i][d] = sl < 4 * M ? (double)codebooks[((int64_t)(sl >> 2) * kPqK + 64 * (sl & 3) + lane) * DS + d] : 0.0;
+                w[i][d] = sl < 4 * M ? (WT)codebooks[((int64_t)(sl >> 2) * kPqK + 64 * (sl & 3) + lane) * DS + d] : (WT)0;
         }
     }
     const float ql = wd < D ? qb[wd] : 0.0f;
@@ -384,7 +393,7 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
                         double acc = 0.0;
 #pragma unroll
                         for (int d = 0; d < DS; ++d) {
-                            const double v = r[d] - w[i][d];
+                            const double v = r[d] - (double)w[i][d];
                             acc = fma(v, v, acc);
                         }
                         lt[sl * 64 + lane] = (float)acc;
@@ -548,7 +557,7 @@ __global__ __launch_bounds__(kAdcThreads) void adc_merge_kernel(const uint64_t *
 using ScanKernel = decltype(&adc_scan_kernel<8, 4>);
 
 // The kernel that holds the codebooks in registers for the usual subspaces:
-// slices per wave = ceil(M / 4), at most 40 doubles a thread.
+// slices per wave = ceil(M / 4), at most 40 doubles (or 48 floats) a thread.
 ScanKernel scan_kernel(int dsub, int M)
 {
     const int sl = (M + 3) / 4;
@@ -572,23 +581,33 @@ ScanKernel scan_kernel(int dsub, int M)
         switch (sl) {
         case 1: return adc_scan_kernel<16, 1>;
         case 2: return adc_scan_kernel<16, 2>;
+        case 3: return adc_scan_kernel<16, 3>;
         }
     }
     return adc_scan_kernel<1, 0>;
 }
 
-// Parts per query: one when the queries alone fill the chip several times over
-// (each part loads the codebooks and trims its own pool), else enough for four
-// rounds of workgroups, or for one when the batch is tiny (8 queries x 64
-// lists: 32 parts of two lists).
-int adc_parts(int64_t B, int P, int num_cus)
+// Parts per query: the number for which the rounds of workgroups (one per CU)
+// end soonest. A part costs about 29 us whatever it holds (codebooks, pool, final
+// trim) and 1.2 us per list of ordinary length, that is 24 lists (more where a
+// step holds fewer than four), and lists of thousands of codes cost their scan; several parts cost the merge, about five
+// lists. 8 queries x 64 lists: 32 parts of two lists, 58 us; 149 queries x 7:
+// one part (seven took 119 us against 59 with a workgroup per group of a list).
+int adc_parts(int64_t B, int P, int64_t codes_per_list, int held, int num_cus)
 {
-    int64_t s = 1;
-    if (B <= num_cus / 4)
-        s = (num_cus + B - 1) / std::max<int64_t>(B, 1);
-    else if (B < 4 * (int64_t)num_cus)
-        s = (4 * (int64_t)num_cus + B - 1) / B;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(s, P));
+    const double list = std::max(1.0, 4.0 / held) + (double)codes_per_list / 2048.0;
+    int best = 1;
+    double cost = 0.0;
+    for (int s = 1; s <= P; ++s) {
+        const double rounds = (double)((B * s + num_cus - 1) / num_cus);
+        const double t = rounds * (24.0 + ((P + s - 1) / s) * list) + (s > 1 ? 5.0 : 0.0);
+        if (s == 1 || t < cost) {
+            best = s;
+            cost = t;
+        }
+        if (B * s > 4 * (int64_t)num_cus) break;  // more rounds of less only add the fixed cost
+    }
+    return best;
 }
 
 }  // namespace
@@ -603,12 +622,14 @@ hipError_t launch_adc_scan(const float *Q, int64_t B, int D, const float *cent, 
                        w.gcnt, w.dl, w.dpos);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int S = adc_parts(B, P, num_cus);
-    // lists whose tables are built at a time
-    // (and four at most for subspaces of 16 dims: 64 lanes hold a step's residuals)
-    const int lists = std::max(1, std::min(D / M == 16 ? 4 : kAdcMaxLists, kAdcLutBytes / (M * kPqK * 4)));
+    // lists whose tables are built at a time: as many as fit LDS, and whose
+    // residuals a wave's lanes hold
+    const ScanKernel scan = scan_kernel(D / M, M);
+    const int held = scan == &adc_scan_kernel<1, 0> ? kAdcMaxLists : 64 / slice_dims(D / M, (M + 3) / 4);
+    const int S = adc_parts(B, P, N / C, held, num_cus);
+    const int lists = std::max(1, std::min(std::min(held, kAdcMaxLists), kAdcLutBytes / (M * kPqK * 4)));
     if ((size_t)lists * M * kPqK * 4 > (size_t)kAdcLutBytes) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(scan_kernel(D / M, M), dim3((unsigned)(B * S)), dim3(kAdcThreads), 0, s, Q, D, cent, P, perm,
+    hipLaunchKernelGGL(scan, dim3((unsigned)(B * S)), dim3(kAdcThreads), 0, s, Q, D, cent, P, perm,
                        codes, M, codebooks, k, S, lists, w.gcnt, w.dl, w.dpos, w.handoff, w.hcnt, ids, dist);
     if ((e = hipGetLastError()) != hipSuccess || S == 1) return e;
     hipLaunchKernelGGL(adc_merge_kernel, dim3((unsigned)B), dim3(kAdcThreads), 0, s, w.handoff, w.hcnt, S, k, ids, dist);

@@ -17,7 +17,9 @@ pytestmark = pytest.mark.gpu
     (5, 20, 32, 8, 5000, 6, 64), (5, 20, 64, 16, 5000, 6, 64), (5, 20, 96, 24, 5000, 6, 64),
     (5, 20, 128, 32, 5000, 6, 64), (5, 20, 160, 40, 5000, 6, 64), (5, 20, 64, 4, 5000, 6, 64),
     (5, 20, 128, 8, 5000, 6, 64), (4, 20, 240, 60, 4000, 6, 64), (4, 20, 256, 32, 4000, 6, 64),
-    (4, 20, 120, 15, 4000, 6, 64), (4, 20, 12, 3, 4000, 6, 1), (4, 300, 64, 8, 300, 256, 1000),
+    (300, 60, 96, 12, 6000, 30, 100), (300, 60, 160, 10, 6000, 20, 31), (2, 60, 160, 10, 6000, 20, 31),
+    (300, 60, 64, 4, 6000, 20, 31), (300, 60, 160, 40, 6000, 20, 31), (300, 60, 160, 20, 6000, 20, 31),
+    (300, 60, 96, 24, 6000, 20, 31), (300, 60, 64, 8, 6000, 20, 31), (4, 20, 120, 15, 4000, 6, 64), (4, 20, 12, 3, 4000, 6, 1), (4, 300, 64, 8, 300, 256, 1000),
 ])
 def test_branches_equal_the_oracle(ivf_ctx, oracle_mod, B, C, D, M, N, P, k):  # noqa: F811
     q, c, probes, off, perm, codes, cb = setup(B + C + D + M, B, C, D, M, N, P, 0.6)
