@@ -302,6 +302,12 @@ bool direct_route(const RoutePlan &p, int64_t Q, int64_t C, int k)
     return C <= kDirectMaxC && k <= 512 && Q <= p.QB && Q <= kDirectMaxQ && 2 * Q <= p.qdp;
 }
 
+// The f16 plane takes the queries that are not uint8-valued from 10 GFLOP per
+// call on: building the plane and the filter's flushes cost 40-80 us however small the call,
+// against 8 us per GFLOP on fp32 MFMA (1,656 queries on 20,438 x 64: 242 us in f16,
+// 181 in fp32; 1,280 on 83,435 x 64: 157 and 214).
+bool f16_route(int64_t Q, int64_t C, int D) { return 2.0 * (double)Q * (double)C * (double)D >= 1e10; }
+
 int64_t worklist_cap(int64_t N) { return std::min<int64_t>(N, 4096 + N / 64); }
 // Rows a one-pass screen may list before the next screen takes every row: a
 // quarter of a call of ordinary size (a 131,072 x 100 table of close centroids
@@ -1038,18 +1044,19 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
     // synchronisation) when a centroid does not fit the int8 planes or the f16
     // window is too wide.
     const bool planes = p.qdp > 0 && !ctx->fp32_screen;
+    const bool f16 = planes && f16_route(Q, C, D);
     uint32_t *w = l.sc.mc2_bits;
     if (planes) {
         TIMED("route_i8_check", launch_route_i8_check(queries, Q, D, w + kWordNotI8, s));
         TIMED("quantize", launch_quantize_centroids(centroids, C, D, p.qdp, l.qc, l.negb, w + kWordQBad, s,
-                                                    w + kWordNotI8, w));
+                                                    w + kWordNotI8, f16 ? w : nullptr));
     }
     for (int64_t q0 = 0; q0 < Q; q0 += p.QB) {
         const int64_t nb = std::min(p.QB, Q - q0);
         const float *qrows = queries + q0 * D;
         TIMED("route_bound", launch_route_i8_bound(qrows, nb, D, planes ? w + kWordQBad : nullptr,
                                                    planes ? w + kWordNotI8 : nullptr, planes ? l.qbound : nullptr, s,
-                                                   w, f16_acc_coef(DP), l.qn2));
+                                                   w, f16 || !planes ? f16_acc_coef(DP) : -1.0, l.qn2));
         ScreenArgs a{};
         a.rows = qrows;
         a.nrows = nb;
@@ -1104,6 +1111,7 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
         r.stats = l.sc.stats;
         r.w = planes ? w : nullptr;
         r.qbound = l.qbound;
+        r.f16 = f16;
         if (planes) {
             // the planes' sample minima (in the keys buffer), threshold and
             // filter over every centroid
@@ -1116,7 +1124,7 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
             rf.nsub = p.Cs / kQuantChunk;
             rf.cstride = p.Ss;
             rf.kmin = l.keys;
-            TIMED("route_f16_keys", launch_route_f16(kRouteKeys, p.qdp, rf, ctx->num_cus, s));
+            if (f16) TIMED("route_f16_keys", launch_route_f16(kRouteKeys, p.qdp, rf, ctx->num_cus, s));
             TIMED("route_threshold_min", launch_route_threshold_min(r, s));
             ra.c_end = C;
             ra.nchunks = (C + kQuantChunk - 1) / kQuantChunk;
@@ -1134,7 +1142,7 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
             rf.cand_cnt = l.cand_cnt;
             rf.cand = l.cand;
             rf.L = p.L;
-            TIMED("route_f16_filter", launch_route_f16(kRouteFilter, p.qdp, rf, ctx->num_cus, s));
+            if (f16) TIMED("route_f16_filter", launch_route_f16(kRouteFilter, p.qdp, rf, ctx->num_cus, s));
         }
         a.c_begin = 0;
         a.c_end = C;

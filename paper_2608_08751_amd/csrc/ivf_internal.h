@@ -248,6 +248,7 @@ struct RouteArgs {
     // smallest group minimum, and the batch goes to the fp32 kernels when that
     // lies above the rank_max-th
     int rank_safe, rank_max;
+    bool f16;  // the f16 plane is in use for what the int8 planes do not take
 };
 
 // Direct route: every key of the batch kept, then one workgroup per query

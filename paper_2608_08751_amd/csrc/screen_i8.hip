@@ -716,7 +716,7 @@ __global__ __launch_bounds__(256) void route_i8_check_kernel(const float *__rest
 // null). Raises *off when *q_bad (a centroid outside the two planes' range) is
 // set (the f16 plane was not built then: the fp32 kernels take the call). In a
 // library call, w are the scalar words: the batch's worklist counter and f16
-// flag start here.
+// flag start here (acc < 0: no f16 plane in this call).
 __global__ __launch_bounds__(256) void route_i8_bound_kernel(const float *__restrict__ Q, int64_t nq, int D,
                                                              const uint32_t *__restrict__ q_bad,
                                                              uint32_t *__restrict__ off, float *__restrict__ qbound,
@@ -732,7 +732,7 @@ __global__ __launch_bounds__(256) void route_i8_bound_kernel(const float *__rest
         if (off && *q_bad) atomicOr(off, 1u);
         if (w) {
             w[kWordWorklist] = 0u;
-            w[kWordF16Off] = off && *q_bad ? 1u : 0u;
+            w[kWordF16Off] = (off && *q_bad) || acc < 0.0 ? 1u : 0u;
         }
     }
     const uint32_t mc2 = w ? w[kWordMc2] : 0u, rc = w ? w[kWordF16Rc] : 0u;

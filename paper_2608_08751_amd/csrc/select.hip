@@ -258,6 +258,7 @@ __global__ __launch_bounds__(256) void route_threshold_min_kernel(RouteArgs a)
 {
     // (kWordF16Off, zero before this kernel, is raised by it and not read)
     const bool i8 = a.w[kWordNotI8] == 0u;
+    if (!i8 && !a.f16) return;
     const int64_t q = blockIdx.x;
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sh[2];

@@ -80,6 +80,27 @@ def test_route_equals_the_oracle(ivf_ctx, oracle_mod, kind, Q, C, D, k):  # noqa
     assert (ids.cpu().numpy() == oids).all() and (dist.cpu().numpy() == odist).all()
 
 
+@pytest.mark.parametrize("kind,Q,C,D,k", [
+    ("plain", 20000, 70000, 4, 128), ("plain", 2000, 20011, 128, 64), ("plain", 6000, 4097, 256, 5),
+    ("ties", 9000, 9001, 64, 40), ("offset", 3000, 20000, 96, 32), ("range", 2500, 20000, 128, 16),
+    ("tiny", 4000, 15000, 96, 8), ("huge", 4000, 15000, 96, 8), ("plain", 20000, 8300, 32, 8),
+])
+def test_large_route_equals_the_oracle(ivf_ctx, oracle_mod, kind, Q, C, D, k):  # noqa: F811
+    """Calls of at least 10 GFLOP, which take the f16 plane; 120 queries compared."""
+    import torch
+
+    import paper_2608_08751_amd as ivf
+
+    assert 2 * Q * C * D >= 1e10
+    q, c = data(kind, Q, C, D, seed=Q + D)
+    ids, dist = ivf.ivf_route(ivf_ctx, to_dev(q), to_dev(c), k)
+    torch.cuda.synchronize()
+    print(kind, Q, C, D, k, ivf_ctx.last_stats(), flush=True)
+    pick = np.r_[0:60, Q - 60:Q]
+    oids, odist = oracle_mod.route(q[pick], c, k)
+    assert (ids.cpu().numpy()[pick] == oids).all() and (dist.cpu().numpy()[pick] == odist).all()
+
+
 def test_route_batches_and_odd_queries(ivf_ctx, oracle_mod):  # noqa: F811
     """Two internal batches: one query of the second has no f16 bound, so that
     batch alone goes to the fp32 kernels."""
