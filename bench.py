@@ -157,6 +157,11 @@ def bench_route(ctx, name, d, k, oracle_s, full_oracle=False):
         out["int8_mfma_frac"] = tf / PEAK_INT8_MFMA_TOPS
         out["int8_mfma_executed_frac"] = 2.0 * tf / PEAK_INT8_MFMA_TOPS
         out["vs_fp32_mfma_peak_ratio"] = tf / PEAK_FP32_MFMA_TFLOPS
+    elif out["kernels_ms"].get("route_f16_filter", 0.0) > out["kernels_ms"].get("screen_filter", 0.0):
+        # the kernels that do not take the call return at once
+        out["screen"] = "f16 MFMA"
+        out["tflops"] = tf
+        out["vs_fp32_mfma_peak_ratio"] = tf / PEAK_FP32_MFMA_TFLOPS
     else:
         out["screen"] = "fp32 MFMA"
         out["tflops"] = tf
@@ -436,8 +441,8 @@ def main():
                             "64M-row chunks) assigned to 65,536 fp32 centroids (the mixture means) by top-1 "
                             "squared L2, then counts, offsets and the stable list permutation",
                 "rows": N, "centroids": C, "dim": D,
-                "screen": "int8 MFMA (one plane per centroid; two planes for the rows it leaves); exact fp64 "
-                          "re-evaluation of near-ties",
+                "screen": "int8 MFMA (one plane per centroid, a second pass collects the candidates of the "
+                          "rows it leaves); exact fp64 re-evaluation of near-ties",
             },
             "roofline": roofline,
             "kernels": kernels,

@@ -49,6 +49,8 @@
  *     planes' key units; any other value in the call sends it to the f16, a
  *     centroid that does not quantise to the fp32 kernels (device flag, no
  *     host synchronisation). IVF_OPT_FP32_SCREEN forces the fp32 kernels.
+ *     A call of less than 10 GFLOP (2 Q C D) takes the fp32 kernels in place of
+ *     the f16 ones.
  *   - tables of at most 2,048 centroids, and batches of at most
  *     min(32, padded D / 2) queries with nprobe <= 512 on tables of at most
  *     65,536, are routed from the whole fp32 key matrix in two launches.

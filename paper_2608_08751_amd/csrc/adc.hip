@@ -589,10 +589,10 @@ ScanKernel scan_kernel(int dsub, int M)
 
 // Parts per query: the number for which the rounds of workgroups (one per CU)
 // end soonest. A part costs about 29 us whatever it holds (codebooks, pool, final
-// trim) and 1.2 us per list of ordinary length, that is 24 lists (more where a
-// step holds fewer than four), and lists of thousands of codes cost their scan; several parts cost the merge, about five
-// lists. 8 queries x 64 lists: 32 parts of two lists, 58 us; 149 queries x 7:
-// one part (seven took 119 us against 59 with a workgroup per group of a list).
+// trim) and 1.2 us per list of ordinary length (more where a step holds fewer
+// than four), that is 24 lists; lists of thousands of codes cost their scan;
+// several parts cost the merge, about five lists. 8 queries x 64 lists: 32 parts
+// of two lists, 58 us; 149 queries x 7: one part (seven took 119 us against 59 with a workgroup per group of a list).
 int adc_parts(int64_t B, int P, int64_t codes_per_list, int held, int num_cus)
 {
     const double list = std::max(1.0, 4.0 / held) + (double)codes_per_list / 2048.0;
