@@ -10,6 +10,7 @@
 #include "ivf_internal.h"
 #include "exact.h"
 
+#include <float.h>
 #include <math.h>
 
 namespace ivf {
@@ -251,7 +252,10 @@ __global__ __launch_bounds__(256) void route_threshold_gmin_kernel(RouteArgs a)
 // rank_safe-th minimum (the k-th smallest key lies below that minimum but for
 // a five-sigma draw of the sample); a query for which that lies above the
 // rank_max-th minimum would keep too many candidates, and its batch goes to
-// the fp32 kernels.
+// the fp32 kernels. A rank above rank_max (IVF_OPT_SAMPLE_RANK) is selected
+// from all minima. tau stays below infinity: the filter keeps v >= -tau, and
+// what lies outside the table (padding rows, the scan's start block) scores
+// -infinity.
 constexpr int kRankMax = 64;
 
 __global__ __launch_bounds__(256) void route_threshold_min_kernel(RouteArgs a)
@@ -312,10 +316,11 @@ __global__ __launch_bounds__(256) void route_threshold_min_kernel(RouteArgs a)
         if (less < rs && rs <= less + same) s_rank[1] = o2f(m);
     }
     __syncthreads();
+    const float th = rank <= rmax ? s_rank[0] : o2f(block_select(v, nv, rank, hist, sh));
     if (threadIdx.x == 0) {
         const float cover = __double2float_ru((double)s_rank[1] + 2.0 * (double)a.qbound[q]);
         const bool wide = !(cover <= o2f(top));
-        a.tau[q] = fmaxf(s_rank[0], cover);
+        a.tau[q] = fminf(fmaxf(th, cover), FLT_MAX);
         a.cand_cnt[q] = 0;
         if (wide) a.w[kWordF16Off] = 1u;
     }

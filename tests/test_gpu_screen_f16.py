@@ -101,6 +101,34 @@ def test_large_route_equals_the_oracle(ivf_ctx, oracle_mod, kind, Q, C, D, k):  
     assert (ids.cpu().numpy()[pick] == oids).all() and (dist.cpu().numpy()[pick] == odist).all()
 
 
+@pytest.mark.parametrize("rank", [1, 60, 65, 100, 400])
+def test_threshold_ranks_on_the_f16_plane(ivf_ctx, oracle_mod, rank):  # noqa: F811
+    """Ranks below and above the 64 minima the threshold keeps: the same
+    candidates at every run, more of them at a higher rank, the same results."""
+    import torch
+
+    import paper_2608_08751_amd as ivf
+
+    q, c = data("plain", 2000, 20011, 128, seed=31)
+    qd, cd = to_dev(q), to_dev(c)
+    ivf_ctx.set_option(ivf.IVF_OPT_SAMPLE_RANK, rank)
+    try:
+        runs = []
+        for _ in range(2):
+            ids, dist = ivf.ivf_route(ivf_ctx, qd, cd, 16)
+            torch.cuda.synchronize()
+            runs.append(ivf_ctx.last_stats())
+            print(rank, runs[-1], flush=True)
+    finally:
+        ivf_ctx.set_option(ivf.IVF_OPT_SAMPLE_RANK, 0)
+    assert runs[0] == runs[1]
+    if rank > 1:  # a sample of 2,496 in 156 groups: eight centroids per sample key
+        assert runs[0]["candidates"] > 2000 * min(rank, 156) * 6
+    pick = np.r_[0:40, 1960:2000]
+    oids, odist = oracle_mod.route(q[pick], c, 16)
+    assert (ids.cpu().numpy()[pick] == oids).all() and (dist.cpu().numpy()[pick] == odist).all()
+
+
 def test_route_batches_and_odd_queries(ivf_ctx, oracle_mod):  # noqa: F811
     """Two internal batches: one query of the second has no f16 bound, so that
     batch alone goes to the fp32 kernels."""

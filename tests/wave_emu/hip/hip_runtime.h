@@ -183,6 +183,18 @@ inline T __shfl(T v, int src)
     return r;
 }
 
+template <typename T>
+inline T __shfl_up(T v, int d)
+{
+    emu::Wave &w = emu::wave();
+    memcpy(w.buf[emu::lane()], &v, sizeof(T));
+    w.bar->arrive_and_wait();
+    T r;
+    memcpy(&r, w.buf[emu::lane() >= d ? emu::lane() - d : emu::lane()], sizeof(T));
+    w.bar->arrive_and_wait();
+    return r;
+}
+
 inline int __ffsll(unsigned long long m) { return __builtin_ffsll((long long)m); }
 inline int __popcll(unsigned long long m) { return __builtin_popcountll(m); }
 
