@@ -59,10 +59,18 @@ struct RowAcc {
     }
 };
 
+// M >= the largest scaled centroid norm: 2^-20 covers the rounding of the
+// squared norm to fp32 and of the sums and roots, 2^-149 that of a subnormal
+// one.
+__device__ __forceinline__ double f16_max_norm(uint32_t mc2_bits)
+{
+    return sqrt((double)__uint_as_float(mc2_bits) * (1.0 + 0x1p-20) + 0x1p-149) * (double)f16_scale(mc2_bits);
+}
+
 // B for a row, in the scaled units, as a double.
 __device__ __forceinline__ double f16_bound(const RowNorms &r, uint32_t mc2_bits, uint32_t rc_bits, double acc)
 {
-    const double M = sqrt((double)__uint_as_float(mc2_bits) * (1.0 + 0x1p-20)) * (double)f16_scale(mc2_bits);
+    const double M = f16_max_norm(mc2_bits);
     const double rc = (double)__uint_as_float(rc_bits);
     return (double)r.rx * M + (double)r.xh * rc + acc * (0.5 * M * M + (double)r.xh * (M + rc)) + 0x1p-60;
 }
@@ -71,7 +79,7 @@ __device__ __forceinline__ double f16_bound(const RowNorms &r, uint32_t mc2_bits
 // fp32 loses in (value - window).
 __device__ __forceinline__ float f16_window(const RowNorms &r, uint32_t mc2_bits, uint32_t rc_bits, double acc)
 {
-    const double M = sqrt((double)__uint_as_float(mc2_bits) * (1.0 + 0x1p-20)) * (double)f16_scale(mc2_bits);
+    const double M = f16_max_norm(mc2_bits);
     return __double2float_ru(2.0 * f16_bound(r, mc2_bits, rc_bits, acc) + 0x1p-21 * (M * M + (double)r.xh * M));
 }
 
