@@ -32,6 +32,8 @@ __global__ __launch_bounds__(256) void resolve_kernel(ResolveArgs a)
     const int lane = threadIdx.x & 63;
     const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t nt = (int64_t)gridDim.x * 256;
+    const int64_t nl = *a.list_cnt;
+    if (nl > a.list_cap) return;  // another screen takes every row
     const int64_t nd = min((int64_t)*a.rs.duel_cnt, a.rs.duel_cap);
     // whole waves stay in step (nt and the wave's first item are multiples of
     // 64 lanes), so the shuffles always find their partners
@@ -45,8 +47,7 @@ __global__ __launch_bounds__(256) void resolve_kernel(ResolveArgs a)
         const int oc = __shfl_xor(c, 1);
         if (on && !(t & 1)) a.labels[rc.x] = dist_lt(od, oc, d, c) ? oc : c;
     }
-    const int64_t nl = *a.list_cnt;
-    if (!a.rs.list_thr || nl > a.list_cap) return;  // another screen takes the rows
+    if (!a.rs.list_thr) return;  // another screen takes the listed rows
     for (int64_t w = t0 - lane; w < kResolveCand * nl; w += nt) {
         const int64_t t = w + lane;
         const int64_t i = t / kResolveCand;

@@ -511,7 +511,7 @@ __global__ __launch_bounds__(512, 2) void screen_f16_kernel(ScreenF16Args a)
     __shared__ __attribute__((aligned(16))) char lds[G::LDS];
     __shared__ TileLists tl;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, jl = lane & 31;
-    if (threadIdx.x == 0) tl.cnt[0] = tl.cnt[1] = 0;  // (a tile's barriers come before their first use)
+    if (threadIdx.x == 0) tl.cnt[0] = tl.cnt[1] = tl.base[1] = 0;  // (a tile's barriers come before their first use)
     const uint32_t mc2 = *a.mc2_bits, rc = *a.rc_bits;
     const float sc = f16_scale(mc2);
     const int64_t ntiles = (a.nrows + G::ROWS - 1) / G::ROWS;
@@ -531,7 +531,12 @@ __global__ __launch_bounds__(512, 2) void screen_f16_kernel(ScreenF16Args a)
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) v[rb] = f16_finish(a, row[rb], row[rb] < a.nrows, h, st[rb], tl);
         list_tile<float, RB>(a, row, v, tl);
+        // a list past its capacity hands every row to the fp32 screen: the
+        // tiles that are left would be screened for nothing (500,000 x 96 rows
+        // that f16 cannot tell apart, 16,384 centroids: 14.3 -> 13.3 ms)
+        const bool full = (int64_t)tl.base[1] >= a.list_cap && !a.force_list;
         __syncthreads();
+        if (full) break;
     }
 }
 

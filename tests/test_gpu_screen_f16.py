@@ -60,6 +60,25 @@ def test_assign_equals_the_oracle(ivf_ctx, oracle_mod, kind, N, C, D):  # noqa: 
         assert bad.size == 0, "labels differ at rows %s" % bad[:10]
 
 
+def test_assign_stops_when_the_list_overflows(ivf_ctx, oracle_mod):  # noqa: F811
+    """Rows far from the origin: every one is left undecided, and once a quarter
+    of them is listed the f16 pass ends and the fp32 screen takes all of them."""
+    import torch
+
+    import paper_2608_08751_amd as ivf
+
+    N, C = 700_000, 600
+    x, c = data("plain", N, C, 32, seed=3)
+    x, c = x + np.float32(30.0), c + np.float32(30.0)
+    lab = ivf.ivf_assign_build(ivf_ctx, to_dev(x), to_dev(c))[0]
+    torch.cuda.synchronize()
+    st = ivf_ctx.last_stats()
+    print(st, flush=True)
+    assert N // 4 < st["rescreen"] < N // 2
+    pick = np.r_[0:2000, np.random.default_rng(0).integers(0, N, 4000), N - 2000:N]
+    assert (lab.cpu().numpy()[pick] == oracle_mod.assign(x[pick], c)).all()
+
+
 @pytest.mark.parametrize("kind,Q,C,D,k", [
     ("plain", 513, 4096, 96, 16), ("plain", 1, 3000, 128, 5), ("plain", 40, 9001, 4, 128), ("plain", 300, 2049, 256, 64),
     ("plain", 65, 5000, 100, 1000), ("plain", 200, 2113, 160, 1), ("ties", 500, 4100, 64, 40),
