@@ -50,6 +50,8 @@
 namespace ivf {
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int kSetupThreads = 256;
 constexpr int kAdcThreads = 1024;
 constexpr int kAdcWaves = kAdcThreads / 64;
@@ -334,12 +336,18 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     typedef typename std::conditional<DS * SL <= 40, double, float>::type WT;
     WT w[NS][DS];
     if constexpr (SL > 0) {
+        // (16 bytes at a time: single floats, 4 DS bytes apart between lanes, took
+        // each line of the codebooks out of L2 once per dim, 14 of a part's 29 us)
 #pragma unroll
         for (int i = 0; i < SL; ++i) {
             const int sl = wave * SL + i;
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(codebooks + ((int64_t)min(sl, 4 * M - 1) * 64 + lane) * DS);
 #pragma unroll
-            for (int d = 0; d < DS; ++d)
-                w[i][d] = sl < 4 * M ? (WT)codebooks[((int64_t)(sl >> 2) * kPqK + 64 * (sl & 3) + lane) * DS + d] : (WT)0;
+            for (int q = 0; q < DS / 4; ++q) {
+                const f32x4 v = src[q];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[i][4 * q + e] = (WT)v[e];
+            }
         }
     }
     const float ql = wd < D ? qb[wd] : 0.0f;
