@@ -36,16 +36,15 @@
 // probed list, whatever its length. With one workgroup per group every group
 // read the 1,024 D bytes of codebooks from L2 and converted them, and handed
 // all its codes to the merge; here a thread holds its codewords of the usual
-// subspaces (D <= 160) in registers in fp64 for all the groups of its part, and
-// one threshold serves a whole query. 2,048 queries x 96 probed lists of 152
-// codes, M = 16, k = 512: 1.96 -> 1.21 ms (0.23 of it per workgroup, 9.9 us per
-// list of all queries); 8 queries x 64 lists: 158 -> 58 us.
+// widths (see scan_kernel) in registers in fp64 for all the groups of its part,
+// the other widths are read once for the lists of a step, and one threshold serves
+// a whole query. 2,048 queries x 96 probed lists of 122 codes, M = 16, k = 512:
+// 1.86 -> 1.12 ms; 8 queries x 64 lists: 98 -> 45 us.
 // Ids are unique within a query (lists are disjoint), so "the k smallest
 // keys" is exact whatever the grouping.
 #include "ivf_internal.h"
 
 #include <algorithm>
-#include <type_traits>
 
 namespace ivf {
 namespace {
@@ -60,6 +59,7 @@ constexpr int kAdcMinGroup = 8;      // chunks per group at least
 constexpr int kAdcPool = 4096;       // LDS pool capacity (keys): trimmed when fewer than kAdcThreads places are left
 constexpr int kAdcMaxLists = 8;      // lists whose LUTs are built at a time, as many as fit
 constexpr int kAdcLutBytes = 73728;  // LUTs
+constexpr int kAdcPadD = 512;        // dims of a list's residual, its subspaces padded to 4, 8 or 16 dims
 constexpr int kAdcBins = 2048;       // 11-bit digits
 constexpr uint64_t kNoKey = ~0ull;
 static_assert(kAdcMaxK + kAdcThreads <= kAdcPool, "a trimmed pool takes another round of keys");
@@ -295,17 +295,16 @@ struct Desc {
     int32_t list;       // -1: none
 };
 
-// A wave's SL slices lie in whole subspaces, or in a known number of slices of one
-constexpr bool whole_slices(int SL) { return SL == 1 || SL == 2 || SL == 4 || SL == 8; }
-// and cover this many dims: so many lanes hold a list's residuals, 64 of them
-// those of a step's lists
-constexpr int slice_dims(int DS, int SL) { return SL == 10 ? 16 : (SL == 8 || !whole_slices(SL) ? 2 : 1) * DS; }
+// A wave's SL slices lie in one subspace or, from six on, in two; they cover
+// this many dims: so many lanes hold a list's residuals, 64 of them those of a
+// step's lists
+constexpr int slice_dims(int DS, int SL) { return (SL >= 6 ? 2 : 1) * DS; }
 
 // Part s of query b (grid B * S): its groups s, s + S, ..., `lists` of them at a
 // time. DS, SL: dims of a subspace and codeword slices per wave held in
 // registers (slice 4 m + q is codewords 64 q .. 64 q + 63 of subspace m, one per
-// lane; wave w holds slices SL w .. SL w + SL - 1); SL = 0: codewords of any
-// width are read from memory.
+// lane; wave w holds slices SL w .. SL w + SL - 1). SL = 0: codewords of DS dims
+// (of 9 to 16 with DS = 16) are read from memory, SL = -1: of more than 16.
 template <int DS, int SL>
 __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     const float *__restrict__ Q, int D, const float *__restrict__ cent, int P, const uint32_t *__restrict__ perm,
@@ -316,6 +315,7 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     __shared__ __attribute__((aligned(16))) float lut[kAdcLutBytes / 4];  // [lists][M][256]
     __shared__ PoolLds pool;
     __shared__ Desc ring[4][kAdcMaxLists];  // descriptors of the steps around the current one
+    __shared__ __attribute__((aligned(16))) double res[SL > 0 ? 1 : kAdcMaxLists * kAdcPadD];  // [lists][M][pd]
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int64_t b = blockIdx.x / S;
@@ -325,16 +325,13 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     const int64_t g_first = b * 2 * (int64_t)P + part;
     const float *qb = Q + b * D;
     constexpr int NS = SL > 0 ? SL : 1;
-    // dims of the subspaces a wave's slices lie in, from dim wd on (subspaces of
-    // SL consecutive slices: one or two, three for SL = 10); lane W u + d holds
-    // dim d of list u of a step
-    constexpr bool WHOLE = whole_slices(SL);
+    const int dsub = SL == 0 && DS <= 8 ? DS : D / M;
+    const int pd = (dsub + DS - 1) / DS * DS;  // (SL <= 0, from 9 dims on: padded with zeros)
+    // dims of the subspaces a wave's slices lie in, from dim wd on
     constexpr int W = slice_dims(DS, SL);
     const int m_lo = wave * NS >> 2;
     const int wd = m_lo * DS + lane % W;
-    // three slices of 16 dims leave no room for fp64: converted at each use (exact)
-    typedef typename std::conditional<DS * SL <= 40, double, float>::type WT;
-    WT w[NS][DS];
+    double w[NS][DS];
     if constexpr (SL > 0) {
         // (16 bytes at a time: single floats, 4 DS bytes apart between lanes, took
         // each line of the codebooks out of L2 once per dim, 14 of a part's 29 us)
@@ -346,11 +343,26 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
             for (int q = 0; q < DS / 4; ++q) {
                 const f32x4 v = src[q];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[i][4 * q + e] = (WT)v[e];
+                for (int e = 0; e < 4; ++e) w[i][4 * q + e] = (double)v[e];
             }
         }
     }
-    const float ql = wd < D ? qb[wd] : 0.0f;
+    // the residual dims this thread forms for a step's lists: lane W u + d holds
+    // dim wd of list u, or (SL = 0) dims of the lists' rows laid end to end
+    constexpr int NR = SL > 0 ? 1 : kAdcMaxLists * 256 / kAdcThreads;
+    int ru[NR], rd[NR];
+    float ql[NR];
+#pragma unroll
+    for (int e = 0; e < NR; ++e) {
+        const int i = t + e * kAdcThreads;
+        ru[e] = SL > 0 ? lane / W : i / D;
+        rd[e] = SL > 0 ? wd : i % D;
+        if (ru[e] >= lists || rd[e] >= D) ru[e] = -1;
+        ql[e] = ru[e] >= 0 ? qb[rd[e]] : 0.0f;
+    }
+    if constexpr (SL <= 0) {
+        for (int i = t; i < lists * M * pd; i += kAdcThreads) res[i] = 0.0;
+    }
     pool_init(pool);
     auto load_desc = [&](int step) __attribute__((always_inline)) {
         Desc v{0, 0, -1};
@@ -361,13 +373,16 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
         }
         return v;
     };
-    // this lane's centroid dim of a step's list (its descriptors are in the ring)
+    // this thread's centroid dims of a step's lists (their descriptors are in the ring)
+    struct Dims {
+        float v[NR];
+    };
     auto load_cent = [&](int step) __attribute__((always_inline)) {
-        float c = 0.0f;
-        if constexpr (SL > 0) {
-            const int u = lane / W;
-            const int32_t l = u < lists ? ring[step & 3][u].list : -1;
-            if (l >= 0 && wd < D) c = cent[(int64_t)l * D + wd];
+        Dims c;
+#pragma unroll
+        for (int e = 0; e < NR; ++e) {
+            const int32_t l = ru[e] >= 0 ? ring[step & 3][ru[e]].list : -1;
+            c.v[e] = l >= 0 ? cent[(int64_t)l * D + rd[e]] : 0.0f;
         }
         return c;
     };
@@ -375,9 +390,9 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     // c (fp32, as defined) is the same for every lane: it is formed once per
     // list and dim, in the lane that holds the dim, and read from there into
     // scalar registers (LDS broadcasts of it took the whole LDS bandwidth).
-    auto build = [&](int step, float cl, float *buf) __attribute__((always_inline)) {
+    auto build = [&](int step, const Dims &cl, float *buf) __attribute__((always_inline)) {
         const int nl = min(lists, ng - step * lists);
-        const double rl = (double)(ql - cl);
+        const double rl = (double)(ql[0] - cl.v[0]);
         const int rlo = (int)(uint32_t)__double_as_longlong(rl), rhi = (int)(uint32_t)(__double_as_longlong(rl) >> 32);
         for (int u = 0; u < nl; ++u) {
             float *lt = buf + (size_t)u * M * kPqK;
@@ -389,7 +404,7 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
                     const int sl = wave * SL + i;
                     if (sl < 4 * M) {
                         const int m = (sl >> 2) - m_lo;
-                        if (WHOLE ? i % 4 == 0 : m != m_of) {  // (uniform) the slice's subspace
+                        if (SL != 6 ? i % 4 == 0 : m != m_of) {  // (uniform) the slice's subspace
                             m_of = m;
 #pragma unroll
                             for (int d = 0; d < DS; ++d) {
@@ -401,29 +416,105 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
                         double acc = 0.0;
 #pragma unroll
                         for (int d = 0; d < DS; ++d) {
-                            const double v = r[d] - (double)w[i][d];
+                            const double v = r[d] - w[i][d];
                             acc = fma(v, v, acc);
                         }
                         lt[sl * 64 + lane] = (float)acc;
                     }
                 }
-            } else {
-                const float *c = cent + (int64_t)__builtin_amdgcn_readfirstlane(ring[step & 3][u].list) * D;
-                const int dsub = D / M;
-                for (int sl = wave; sl < 4 * M; sl += kAdcWaves) {
-                    const float *wr = codebooks + ((int64_t)sl * 64 + lane) * dsub;
-                    const int d0 = (sl >> 2) * dsub;
-                    double acc = 0.0;
-                    for (int d = 0; d < dsub; ++d) {
-                        const double v = (double)(qb[d0 + d] - c[d0 + d]) - (double)wr[d];
-                        acc = fma(v, v, acc);
-                    }
-                    lt[sl * 64 + lane] = (float)acc;
-                }
             }
         }
     };
-    const bool words = SL > 0 && M == 4 * SL;  // a code is SL words
+    // The same from memory, for the widths without a register layout: the
+    // residuals of the step's lists lie in LDS in fp64, padded to DS dims a
+    // subspace, and a wave reads U slices' codewords (the next ones while these
+    // are in use) and converts them once for all of the lists. Bound by the LDS
+    // broadcasts of the residuals, which U slices share. 512 queries x 32 lists
+    // of 244 codes, 32 subspaces of 8: 1.93 -> 0.34 ms (a
+    // float a load, the residual formed anew by every lane).
+    auto build_memory = [&](int step, const Dims &cl) __attribute__((always_inline)) {
+        constexpr int U = DS <= 4 ? 4 : DS <= 8 ? 2 : 1;
+        constexpr bool BLOCKS = SL < 0;  // subspaces of more than 16 dims go through in blocks of 16
+        const int nl = min(lists, ng - step * lists);
+#pragma unroll
+        for (int e = 0; e < NR; ++e)
+            if (ru[e] >= 0) res[(ru[e] * M + rd[e] / dsub) * pd + rd[e] % dsub] = (double)(ql[e] - cl.v[e]);
+        __syncthreads();
+        auto load = [&](int un, int blk, float(&c)[U][DS]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const float *w0 = codebooks + ((int64_t)(un * U + j) * 64 + lane) * dsub;
+#pragma unroll
+                for (int q = 0; q < (DS + 3) / 4; ++q) {
+                    const int d0 = blk * DS + 4 * q;
+                    if (DS % 4 == 0 && (DS <= 8 || (dsub & 3) == 0)) {
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(w0 + min(d0, dsub - 4));
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) c[j][4 * q + e] = d0 < dsub ? v[e] : 0.0f;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (4 * q + e < DS) {
+                                const float v = w0[min(d0 + e, dsub - 1)];
+                                c[j][4 * q + e] = d0 + e < dsub ? v : 0.0f;
+                            }
+                        }
+                    }
+                }
+            }
+        };
+        const int nu = 4 * M / U, nb = pd / DS;
+        float c[U][DS];
+        if (wave < nu) load(wave, 0, c);
+        double acc[BLOCKS ? kAdcMaxLists : 1];
+        for (int un = wave, blk = 0; un < nu;) {
+            double w[U][DS];
+#pragma unroll
+            for (int j = 0; j < U; ++j)
+#pragma unroll
+                for (int d = 0; d < DS; ++d) w[j][d] = (double)c[j][d];
+            const bool last = !BLOCKS || blk + 1 == nb;
+            const int nun = last ? un + kAdcWaves : un, nblk = last ? 0 : blk + 1;
+            if (nun < nu) load(nun, nblk, c);
+            const int m = un * U >> 2;
+            const double *r0 = res + m * pd + blk * DS;
+            float *l0 = lut + m * kPqK + (un * U & 3) * 64 + lane;
+            auto one = [&](int u, double &a) __attribute__((always_inline)) {
+                double r[DS];
+#pragma unroll
+                for (int d = 0; d < DS; ++d) r[d] = r0[u * M * pd + d];
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    double s = BLOCKS && blk > 0 ? a : 0.0;
+#pragma unroll
+                    for (int d = 0; d < DS; ++d) {  // (the padding adds exact zeros)
+                        const double v = r[d] - w[j][d];
+                        s = fma(v, v, s);
+                    }
+                    if (BLOCKS) a = s;
+                    if (last) l0[u * M * kPqK + 64 * j] = (float)s;
+                }
+            };
+            if constexpr (BLOCKS) {
+#pragma unroll
+                for (int u = 0; u < kAdcMaxLists; ++u)
+                    if (u < nl) one(u, acc[u]);
+            } else {
+#pragma unroll 1
+                for (int u = 0; u < nl; ++u) one(u, acc[0]);
+            }
+            un = nun;
+            blk = nblk;
+        }
+    };
+    // a code is SL words, or whole words of which NW are loaded at a time
+    constexpr int NW = SL > 0 ? SL : 8;
+    const bool words = SL > 0 ? M == 4 * SL : (M & 3) == 0;
+    auto load_code = [&](int64_t pos, uint32_t(&cw)[NW]) __attribute__((always_inline)) {
+        const uint32_t *a = reinterpret_cast<const uint32_t *>(codes + pos * M);
+#pragma unroll
+        for (int e = 0; e < NW; ++e) cw[e] = a[SL > 0 || 4 * e < M ? e : 0];
+    };
     // Loads are issued a table build ahead of their use: a step's descriptors
     // three steps, its centroid dims one step, its codes one build. (Two table
     // buffers of half as many lists, a build beside the scan before it, were
@@ -434,7 +525,7 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     }
     Desc ahead = load_desc(3);
     __syncthreads();
-    float cl = load_cent(0);
+    Dims cl = load_cent(0);
     int room = kAdcPool;  // places the pool has at least
     for (int step = 0; step < steps; ++step) {
         const Desc *ds = ring[step & 3];
@@ -452,21 +543,20 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
             }
         };
         int cu = 0;
-        uint32_t cw[NS], id = 0;
+        uint32_t cw[NW], id = 0;
         if (t < total) {
             const int64_t pos = locate(t, cu);
             id = perm[pos];
             // (the number of words is known at compile time: a branch per word
             // would wait for each load before the next)
-            const uint32_t *a = reinterpret_cast<const uint32_t *>(codes + pos * M);
-            if (words) {
-#pragma unroll
-                for (int e = 0; e < SL; ++e) cw[e] = a[e];
-            }
+            if (words) load_code(pos, cw);
         }
-        const float cc = cl;
+        const Dims cc = cl;
         cl = load_cent(step + 1);
-        build(step, cc, lut);
+        if constexpr (SL > 0)
+            build(step, cc, lut);
+        else
+            build_memory(step, cc);
         __syncthreads();
         for (int64_t c0 = 0; c0 < total; c0 += kAdcThreads) {
             if (room < kAdcThreads) {  // (uniform)
@@ -481,21 +571,32 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
                 const float *lt;
                 float acc = 0.0f;
                 if (words) {
+                    int64_t pos = 0;
+                    if (c0 > 0 || SL <= 0) pos = locate(c0 + t, cu);
                     if (c0 > 0) {
-                        const int64_t pos = locate(c0 + t, cu);
-                        const uint32_t *a = reinterpret_cast<const uint32_t *>(codes + pos * M);
                         id = perm[pos];
-#pragma unroll
-                        for (int e = 0; e < SL; ++e) cw[e] = a[e];
+                        load_code(pos, cw);
                     }
                     lt = lut + (size_t)cu * M * kPqK;
 #pragma unroll
-                    for (int e = 0; e < SL; ++e) {
-                        const float *l4 = lt + 4 * e * kPqK;
-                        acc = acc + l4[0 * kPqK + (cw[e] & 0xFFu)];
-                        acc = acc + l4[1 * kPqK + ((cw[e] >> 8) & 0xFFu)];
-                        acc = acc + l4[2 * kPqK + ((cw[e] >> 16) & 0xFFu)];
-                        acc = acc + l4[3 * kPqK + (cw[e] >> 24)];
+                    for (int e = 0; e < NW; ++e) {
+                        if (SL > 0 || 4 * e < M) {
+                            const float *l4 = lt + 4 * e * kPqK;
+                            acc = acc + l4[0 * kPqK + (cw[e] & 0xFFu)];
+                            acc = acc + l4[1 * kPqK + ((cw[e] >> 8) & 0xFFu)];
+                            acc = acc + l4[2 * kPqK + ((cw[e] >> 16) & 0xFFu)];
+                            acc = acc + l4[3 * kPqK + (cw[e] >> 24)];
+                        }
+                    }
+                    if constexpr (SL <= 0) {
+                        const uint32_t *a = reinterpret_cast<const uint32_t *>(codes + pos * M);
+                        for (int m = 4 * NW; m < M; m += 4) {
+                            const uint32_t x = a[m / 4];
+                            acc = acc + lt[(m + 0) * kPqK + (x & 0xFFu)];
+                            acc = acc + lt[(m + 1) * kPqK + ((x >> 8) & 0xFFu)];
+                            acc = acc + lt[(m + 2) * kPqK + ((x >> 16) & 0xFFu)];
+                            acc = acc + lt[(m + 3) * kPqK + (x >> 24)];
+                        }
                     }
                 } else {
                     const int64_t pos = locate(c0 + t, cu);
@@ -564,18 +665,21 @@ __global__ __launch_bounds__(kAdcThreads) void adc_merge_kernel(const uint64_t *
 
 using ScanKernel = decltype(&adc_scan_kernel<8, 4>);
 
-// The kernel that holds the codebooks in registers for the usual subspaces:
-// slices per wave = ceil(M / 4), at most 40 doubles (or 48 floats) a thread.
-ScanKernel scan_kernel(int dsub, int M)
+// The kernel for a width: codebooks in registers where a wave's slices are at
+// most 32 doubles a thread (more spill) and share their subspaces evenly, from memory
+// otherwise. 2,048 queries x 96 lists of 122 codes, registers against memory:
+// 16 subspaces of 8 dims 1.12 and 1.46 ms, 32 of 4 1.41 and 2.30, 24 of 4 1.16 and
+// 1.41; 12 of 8 (slices in threes) 1.24 and 1.05, 20 of 8 (fives) 1.92 and 1.73, 10
+// of 16 (48 floats) 2.98 and 1.78.
+ScanKernel scan_kernel(int dsub, int M, int &held)
 {
     const int sl = (M + 3) / 4;
+    held = 64 / slice_dims(dsub, sl);
     if (dsub == 8) {
         switch (sl) {
         case 1: return adc_scan_kernel<8, 1>;
         case 2: return adc_scan_kernel<8, 2>;
-        case 3: return adc_scan_kernel<8, 3>;
         case 4: return adc_scan_kernel<8, 4>;
-        case 5: return adc_scan_kernel<8, 5>;
         }
     } else if (dsub == 4) {
         switch (sl) {
@@ -583,24 +687,34 @@ ScanKernel scan_kernel(int dsub, int M)
         case 4: return adc_scan_kernel<4, 4>;
         case 6: return adc_scan_kernel<4, 6>;
         case 8: return adc_scan_kernel<4, 8>;
-        case 10: return adc_scan_kernel<4, 10>;
         }
     } else if (dsub == 16) {
         switch (sl) {
         case 1: return adc_scan_kernel<16, 1>;
         case 2: return adc_scan_kernel<16, 2>;
-        case 3: return adc_scan_kernel<16, 3>;
         }
     }
-    return adc_scan_kernel<1, 0>;
+    held = kAdcMaxLists;
+    switch (dsub) {
+    case 1: return adc_scan_kernel<1, 0>;
+    case 2: return adc_scan_kernel<2, 0>;
+    case 3: return adc_scan_kernel<3, 0>;
+    case 4: return adc_scan_kernel<4, 0>;
+    case 5: return adc_scan_kernel<5, 0>;
+    case 6: return adc_scan_kernel<6, 0>;
+    case 7: return adc_scan_kernel<7, 0>;
+    case 8: return adc_scan_kernel<8, 0>;
+    }
+    return dsub <= 16 ? adc_scan_kernel<16, 0> : adc_scan_kernel<16, -1>;
 }
 
 // Parts per query: the number for which the rounds of workgroups (one per CU)
-// end soonest. A part costs about 29 us whatever it holds (codebooks, pool, final
+// end soonest. A part costs about 15 us whatever it holds (codebooks, pool, final
 // trim) and 1.2 us per list of ordinary length (more where a step holds fewer
-// than four), that is 24 lists; lists of thousands of codes cost their scan;
+// than four), that is 12 lists; lists of thousands of codes cost their scan;
 // several parts cost the merge, about five lists. 8 queries x 64 lists: 32 parts
-// of two lists, 58 us; 149 queries x 7: one part (seven took 119 us against 59 with a workgroup per group of a list).
+// of two lists, 45 us (98 with a workgroup per group of a list); 149 queries x 7:
+// one part, 28 us (49).
 int adc_parts(int64_t B, int P, int64_t codes_per_list, int held, int num_cus)
 {
     const double list = std::max(1.0, 4.0 / held) + (double)codes_per_list / 2048.0;
@@ -608,7 +722,7 @@ int adc_parts(int64_t B, int P, int64_t codes_per_list, int held, int num_cus)
     double cost = 0.0;
     for (int s = 1; s <= P; ++s) {
         const double rounds = (double)((B * s + num_cus - 1) / num_cus);
-        const double t = rounds * (24.0 + ((P + s - 1) / s) * list) + (s > 1 ? 5.0 : 0.0);
+        const double t = rounds * (12.0 + ((P + s - 1) / s) * list) + (s > 1 ? 5.0 : 0.0);
         if (s == 1 || t < cost) {
             best = s;
             cost = t;
@@ -632,8 +746,8 @@ hipError_t launch_adc_scan(const float *Q, int64_t B, int D, const float *cent, 
     if (e != hipSuccess) return e;
     // lists whose tables are built at a time: as many as fit LDS, and whose
     // residuals a wave's lanes hold
-    const ScanKernel scan = scan_kernel(D / M, M);
-    const int held = scan == &adc_scan_kernel<1, 0> ? kAdcMaxLists : 64 / slice_dims(D / M, (M + 3) / 4);
+    int held = 0;
+    const ScanKernel scan = scan_kernel(D / M, M, held);
     const int S = adc_parts(B, P, N / C, held, num_cus);
     const int lists = std::max(1, std::min(std::min(held, kAdcMaxLists), kAdcLutBytes / (M * kPqK * 4)));
     if ((size_t)lists * M * kPqK * 4 > (size_t)kAdcLutBytes) return hipErrorInvalidValue;

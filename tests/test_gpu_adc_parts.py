@@ -1,5 +1,6 @@
 """The ADC scan's branches: every register layout of the codebooks (subspaces of
-4, 8 and 16 dims, whole and straddling waves) and the memory one, codes of one
+4, 8 and 16 dims) and every width read from memory (1 to 8 dims, up to 16, in
+blocks of 16, whole and part last blocks), codes of one
 to sixty bytes, batches cut into many parts, a few and one, lists of one code
 and of many rounds, ties (equal codes, ids decide), and k from 1 to 1,024.
 Bit for bit the oracle's."""
@@ -17,6 +18,13 @@ pytestmark = pytest.mark.gpu
     (5, 20, 32, 8, 5000, 6, 64), (5, 20, 64, 16, 5000, 6, 64), (5, 20, 96, 24, 5000, 6, 64),
     (5, 20, 128, 32, 5000, 6, 64), (5, 20, 160, 40, 5000, 6, 64), (5, 20, 64, 4, 5000, 6, 64),
     (5, 20, 128, 8, 5000, 6, 64), (4, 20, 240, 60, 4000, 6, 64), (4, 20, 256, 32, 4000, 6, 64),
+    (5, 20, 48, 12, 5000, 6, 64), (5, 20, 80, 20, 5000, 6, 64), (5, 20, 112, 28, 5000, 6, 64),
+    (5, 20, 144, 36, 5000, 6, 64), (5, 20, 64, 32, 5000, 6, 64), (5, 20, 60, 60, 5000, 6, 64),
+    (5, 20, 36, 12, 5000, 6, 64), (5, 20, 100, 20, 5000, 6, 64), (5, 20, 120, 20, 5000, 11, 64),
+    (5, 20, 28, 4, 5000, 9, 64), (5, 20, 120, 10, 5000, 9, 64), (5, 20, 36, 4, 5000, 9, 64), (5, 20, 240, 12, 5000, 9, 64),
+    (5, 20, 256, 8, 5000, 9, 64), (5, 20, 256, 1, 5000, 20, 64), (5, 20, 68, 2, 5000, 9, 64), (5, 20, 252, 28, 5000, 6, 64),
+    (5, 20, 224, 28, 5000, 6, 64), (300, 60, 256, 16, 6000, 20, 31), (300, 60, 208, 13, 6000, 20, 31),
+    (300, 60, 192, 24, 6000, 20, 31), (300, 60, 12, 12, 6000, 20, 31),
     (300, 60, 96, 12, 6000, 30, 100), (300, 60, 160, 10, 6000, 20, 31), (2, 60, 160, 10, 6000, 20, 31),
     (300, 60, 64, 4, 6000, 20, 31), (300, 60, 160, 40, 6000, 20, 31), (300, 60, 160, 20, 6000, 20, 31),
     (300, 60, 96, 24, 6000, 20, 31), (300, 60, 64, 8, 6000, 20, 31), (4, 20, 120, 15, 4000, 6, 64), (4, 20, 12, 3, 4000, 6, 1), (4, 300, 64, 8, 300, 256, 1000),
