@@ -15,13 +15,16 @@
 // codes (the last one partial); the chunks of a list are taken in runs of
 // G_b (the group size of query b, max(kAdcMinGroup, ceil(chunks_b / P))), so a
 // short list is one group and a long one is spread over several groups, and a
-// query has at most 2P groups. The groups of a query are dealt to S parts
-// (part s takes groups s, s + S, ...): one part per query when the batch fills
-// the chip, several when it does not.
+// query has at most 2P groups. The groups of a query are dealt to S_b parts
+// (part s takes groups s, s + S_b, ...): one part per query when the batch fills
+// the chip, several when it does not, more for a query far heavier than the
+// others.
 //   adc_setup_kernel   one workgroup per query: the chunk counts of its
 //                      probed lists, G_b, the groups of every list and their
 //                      exclusive scan over the probes (each group's slot),
 //                      and one descriptor per group (list, code range);
+//   adc_extra_kernel   one workgroup, where lists may be skewed: the parts of
+//                      the heavy queries beyond those every query has;
 //   adc_scan_kernel    one workgroup of 16 waves per part: a few groups at a
 //                      time it builds their lists' LUTs in LDS, scans their
 //                      codes and keeps the k smallest keys of the part in an
@@ -43,6 +46,8 @@
 // Ids are unique within a query (lists are disjoint), so "the k smallest
 // keys" is exact whatever the grouping.
 #include "ivf_internal.h"
+
+#include <math.h>
 
 #include <algorithm>
 
@@ -222,17 +227,88 @@ __device__ __forceinline__ void list_range(const int64_t *__restrict__ offsets, 
     o1 = min(max(offsets[l + 1], o0), N);
 }
 
+// What the parts of a query are decided by, in units of one ordinary list
+// (1.2 us): a table, a chunk of codes, the work a part is meant to have; parts:
+// per query where lists are of about the same length.
+struct AdcCost {
+    float list, chunk, part;
+    int parts;
+};
+
+// gcnt[b]: groups (at most 2P <= 8,192) and parts (at most P) of query b.
+__device__ __forceinline__ int32_t pack_groups(int groups, int parts) { return groups | parts << 14; }
+__device__ __forceinline__ int groups_of(int32_t g) { return g & 0x3FFF; }
+__device__ __forceinline__ int parts_of(int32_t g) { return g >> 14; }
+static_assert(2 * kMaxAdcProbes < 1 << 14 && kMaxAdcProbes < 1 << 16, "both fit a word");
+
+// Parts beyond the `S` that every query has, for queries that cost more than
+// twice the usual (skewed lists): x.list[e] = (query, part) of extra part e,
+// *x.n of them; x.split[i] = query of which some are, *x.nsplit of them. One
+// workgroup; the extra parts are scaled down to x.cap where more are asked for.
+struct AdcExtra {
+    uint64_t *list;
+    int32_t *n;
+    int32_t *split;
+    int32_t *nsplit;
+    int cap;  // 0: no extra parts
+};
+
+__global__ __launch_bounds__(kAdcThreads) void adc_extra_kernel(int64_t B, int S, int32_t *__restrict__ gcnt,
+                                                               AdcExtra x)
+{
+    __shared__ int64_t wsum[kAdcWaves];
+    __shared__ int32_t s_split;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    int64_t sum = 0;
+    for (int64_t b = t; b < B; b += kAdcThreads) sum += parts_of(gcnt[b]) - S;
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor((long long)sum, o);
+    if (lane == 0) wsum[wave] = sum;
+    if (t == 0) s_split = 0;
+    __syncthreads();
+    int64_t total = 0;
+    for (int w = 0; w < kAdcWaves; ++w) total += wsum[w];
+    __syncthreads();
+    int64_t first = 0;  // extra parts of the queries before this round's
+    for (int64_t b0 = 0; b0 < B; b0 += kAdcThreads) {
+        const int64_t b = b0 + t;
+        const int32_t g = b < B ? gcnt[b] : 0;
+        int64_t ex = b < B ? parts_of(g) - S : 0;
+        if (total > x.cap) ex = ex * x.cap / total;
+        int64_t incl = ex;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t up = __shfl_up((long long)incl, o);
+            if (lane >= o) incl += up;
+        }
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        int64_t at = first + incl - ex;
+        for (int w = 0; w < kAdcWaves; ++w) {
+            if (w < wave) at += wsum[w];
+            first += wsum[w];
+        }
+        if (b < B) gcnt[b] = pack_groups(groups_of(g), S + (int)ex);
+        for (int e = 0; e < (int)ex; ++e) x.list[at + e] = (uint64_t)b << 32 | (uint32_t)(S + e);
+        if (ex > 0) x.split[atomicAdd(&s_split, 1)] = (int32_t)b;
+        __syncthreads();
+    }
+    if (t == 0) {
+        *x.n = (int32_t)first;
+        *x.nsplit = s_split;
+    }
+}
+
 // Task setup of query b: the group size, the groups of each probed list
 // (prefix over the probes gives each group's slot j < 2P), and for every
-// group its list and code range: dl[b][j], dpos[b][j] = (first, end).
+// group its list and code range: dl[b][j], dpos[b][j] = (first, end). gcnt[b]
+// holds the groups and the parts that the query's cost asks for (see AdcCost).
 __global__ __launch_bounds__(kSetupThreads) void adc_setup_kernel(const int32_t *__restrict__ probes, int P,
                                                                 const int64_t *__restrict__ offsets, int64_t C,
-                                                                int64_t N, int32_t *__restrict__ gcnt,
+                                                                int64_t N, AdcCost cost, int32_t *__restrict__ gcnt,
                                                                 int32_t *__restrict__ dl,
                                                                 longlong2 *__restrict__ dpos)
 {
     __shared__ int32_t wsum[kSetupThreads / 64];
-    __shared__ int32_t s_g;
+    __shared__ int32_t s_g, s_n;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int64_t b = blockIdx.x;
     // thread t takes the contiguous probes [t * per, (t + 1) * per)
@@ -259,6 +335,7 @@ __global__ __launch_bounds__(kSetupThreads) void adc_setup_kernel(const int32_t 
     if (t == 0) {
         int32_t n = 0;
         for (int w = 0; w < kSetupThreads / 64; ++w) n += wsum[w];
+        s_n = n;
         s_g = max(kAdcMinGroup, (n + P - 1) / P);
     }
     __syncthreads();
@@ -287,7 +364,11 @@ __global__ __launch_bounds__(kSetupThreads) void adc_setup_kernel(const int32_t 
             dpos[base + j] = make_longlong2(f, min(o1s[e], f + (int64_t)G * kAdcChunk));
         }
     }
-    if (t == kSetupThreads - 1) gcnt[b] = j;  // the last thread ends past every group
+    if (t == kSetupThreads - 1) {  // the last thread ends past every group
+        const float c = (float)j * cost.list + (float)s_n * cost.chunk;
+        const float want = fminf(ceilf(c / cost.part), (float)min(P, j));
+        gcnt[b] = pack_groups(j, c > 2.0f * (float)cost.parts * cost.part ? max(cost.parts, (int)want) : cost.parts);
+    }
 }
 
 struct Desc {
@@ -300,16 +381,16 @@ struct Desc {
 // step's lists
 constexpr int slice_dims(int DS, int SL) { return (SL >= 6 ? 2 : 1) * DS; }
 
-// Part s of query b (grid B * S): its groups s, s + S, ..., `lists` of them at a
-// time. DS, SL: dims of a subspace and codeword slices per wave held in
+// Part s of the S_b of query b (grid: B * S, then the extra parts): its groups
+// s, s + S_b, ..., `lists` of them at a time. DS, SL: dims of a subspace and codeword slices per wave held in
 // registers (slice 4 m + q is codewords 64 q .. 64 q + 63 of subspace m, one per
 // lane; wave w holds slices SL w .. SL w + SL - 1). SL = 0: codewords of DS dims
 // (of 9 to 16 with DS = 16) are read from memory, SL = -1: of more than 16.
 template <int DS, int SL>
 __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     const float *__restrict__ Q, int D, const float *__restrict__ cent, int P, const uint32_t *__restrict__ perm,
-    const uint8_t *__restrict__ codes, int M, const float *__restrict__ codebooks, int k, int S, int lists,
-    const int32_t *__restrict__ gcnt, const int32_t *__restrict__ dl, const longlong2 *__restrict__ dpos,
+    const uint8_t *__restrict__ codes, int M, const float *__restrict__ codebooks, int k, int64_t B, int S0, int lists,
+    AdcExtra extra, const int32_t *__restrict__ gcnt, const int32_t *__restrict__ dl, const longlong2 *__restrict__ dpos,
     uint64_t *__restrict__ handoff, int32_t *__restrict__ hcnt, uint32_t *__restrict__ ids, float *__restrict__ dist)
 {
     __shared__ __attribute__((aligned(16))) float lut[kAdcLutBytes / 4];  // [lists][M][256]
@@ -318,9 +399,16 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
     __shared__ __attribute__((aligned(16))) double res[SL > 0 ? 1 : kAdcMaxLists * kAdcPadD];  // [lists][M][pd]
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int64_t b = blockIdx.x / S;
-    const int part = (int)(blockIdx.x - b * S);
-    const int ng = (gcnt[b] - part + S - 1) / S;  // groups of this part
+    int64_t b = blockIdx.x / S0;
+    int part = (int)(blockIdx.x - b * S0);
+    if (b >= B) {
+        const int64_t e = blockIdx.x - B * S0;
+        if (e >= *extra.n) return;
+        b = (int64_t)(extra.list[e] >> 32);
+        part = (int)(uint32_t)extra.list[e];
+    }
+    const int S = parts_of(gcnt[b]);
+    const int ng = (groups_of(gcnt[b]) - part + S - 1) / S;  // groups of this part
     const int steps = (ng + lists - 1) / lists;
     const int64_t g_first = b * 2 * (int64_t)P + part;
     const float *qb = Q + b * D;
@@ -628,27 +716,33 @@ __global__ __launch_bounds__(kAdcThreads) void adc_scan_kernel(
         pool_finish(pool, k, b, ids, dist);
         return;
     }
-    const int64_t slot = b * S + part;
+    const int64_t slot = b * P + part;
     const int m = min(n, k);
     if (t < m) handoff[slot * k + t] = pool.key[t];
     if (t == 0) hcnt[slot] = m;
 }
 
-// Query b's parts, 16 at a time: wave w takes the keys of part p0 + w.
+// Query b's parts, 16 at a time: wave w takes the keys of part p0 + w. Every
+// query, or (split given) those that have extra parts.
 __global__ __launch_bounds__(kAdcThreads) void adc_merge_kernel(const uint64_t *__restrict__ handoff,
-                                                               const int32_t *__restrict__ hcnt, int S, int k,
+                                                               const int32_t *__restrict__ hcnt,
+                                                               const int32_t *__restrict__ gcnt, int P,
+                                                               const int32_t *__restrict__ split,
+                                                               const int32_t *__restrict__ nsplit, int k,
                                                                uint32_t *__restrict__ ids, float *__restrict__ dist)
 {
     __shared__ PoolLds pool;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t b = blockIdx.x;
+    if (split && (int)blockIdx.x >= *nsplit) return;
+    const int64_t b = split ? split[blockIdx.x] : blockIdx.x;
+    const int S = parts_of(gcnt[b]);
     pool_init(pool);
     for (int p0 = 0; p0 < S; p0 += kAdcWaves) {
         int most = 0;
-        for (int p = p0; p < min(S, p0 + kAdcWaves); ++p) most = max(most, hcnt[b * S + p]);
+        for (int p = p0; p < min(S, p0 + kAdcWaves); ++p) most = max(most, hcnt[b * P + p]);
         const int p = p0 + wave;
-        const int n = p < S ? hcnt[b * S + p] : 0;
-        const uint64_t *in = handoff + (b * S + min(p, S - 1)) * (int64_t)k;
+        const int n = p < S ? hcnt[b * P + p] : 0;
+        const uint64_t *in = handoff + (b * P + min(p, S - 1)) * (int64_t)k;
         for (int i0 = 0; i0 < most; i0 += 64) {
             const int i = i0 + lane;
             const uint64_t key = i < n ? in[i] : kNoKey;
@@ -715,14 +809,16 @@ ScanKernel scan_kernel(int dsub, int M, int &held)
 // several parts cost the merge, about five lists. 8 queries x 64 lists: 32 parts
 // of two lists, 45 us (98 with a workgroup per group of a list); 149 queries x 7:
 // one part, 28 us (49).
-int adc_parts(int64_t B, int P, int64_t codes_per_list, int held, int num_cus)
+constexpr double kPartCost = 12.0;     // lists
+constexpr double kCodesCost = 2048.0;  // codes scanned in the time of a list's table
+
+int adc_parts(int64_t B, int P, double list, int num_cus)
 {
-    const double list = std::max(1.0, 4.0 / held) + (double)codes_per_list / 2048.0;
     int best = 1;
     double cost = 0.0;
     for (int s = 1; s <= P; ++s) {
         const double rounds = (double)((B * s + num_cus - 1) / num_cus);
-        const double t = rounds * (12.0 + ((P + s - 1) / s) * list) + (s > 1 ? 5.0 : 0.0);
+        const double t = rounds * (kPartCost + ((P + s - 1) / s) * list) + (s > 1 ? 5.0 : 0.0);
         if (s == 1 || t < cost) {
             best = s;
             cost = t;
@@ -740,21 +836,46 @@ hipError_t launch_adc_scan(const float *Q, int64_t B, int D, const float *cent, 
                            const AdcScratch &w, uint32_t *ids, float *dist, int num_cus, hipStream_t s)
 {
     if (B <= 0) return hipSuccess;
-    hipLaunchKernelGGL(adc_setup_kernel, dim3((unsigned)B), dim3(kSetupThreads), 0, s, probes, P, offsets, C, N,
-                       w.gcnt, w.dl, w.dpos);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     // lists whose tables are built at a time: as many as fit LDS, and whose
     // residuals a wave's lanes hold
     int held = 0;
     const ScanKernel scan = scan_kernel(D / M, M, held);
-    const int S = adc_parts(B, P, N / C, held, num_cus);
     const int lists = std::max(1, std::min(std::min(held, kAdcMaxLists), kAdcLutBytes / (M * kPqK * 4)));
     if ((size_t)lists * M * kPqK * 4 > (size_t)kAdcLutBytes) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(scan, dim3((unsigned)(B * S)), dim3(kAdcThreads), 0, s, Q, D, cent, P, perm,
-                       codes, M, codebooks, k, S, lists, w.gcnt, w.dl, w.dpos, w.handoff, w.hcnt, ids, dist);
-    if ((e = hipGetLastError()) != hipSuccess || S == 1) return e;
-    hipLaunchKernelGGL(adc_merge_kernel, dim3((unsigned)B), dim3(kAdcThreads), 0, s, w.handoff, w.hcnt, S, k, ids, dist);
+    const double table = std::max(1.0, 4.0 / held), chunk = kAdcChunk / kCodesCost;
+    const double list = table + (double)(N / C) / kCodesCost;
+    const int S = adc_parts(B, P, list, num_cus);
+    // Extra parts: where lists are skewed, one query may hold many times the
+    // others' codes, and the workgroup that scans them ends long after the rest
+    // (256 queries x 64 of 16,384 Zipf lists of 10M codes: 1.48 ms, 0.73 with a
+    // workgroup per group of a list, 0.37 with extra parts). The lengths are on
+    // the device, so the extra parts are decided there, wherever the codes are
+    // enough to make a query twice as heavy as its parts are meant for; the two
+    // launches take 5 us where no query is.
+    const double part = std::max(kPartCost, (double)P / S * list);
+    AdcExtra x{};
+    if (S < P && (double)N / kCodesCost > 2.0 * S * part) {
+        x.cap = (int)std::min<int64_t>(2 * (int64_t)num_cus, B * (P - S));
+        x.list = w.handoff + B * P * k;  // parts hand over below B * P slots of the 2 B * P
+        x.split = (int32_t *)(x.list + x.cap);  // at most B, after at most B (P - 1) of B P k entries
+        x.n = w.hcnt + B * P;                   // (P >= 2 here)
+        x.nsplit = w.hcnt + B * P + 1;
+    }
+    const AdcCost cost{(float)table, (float)chunk, x.cap > 0 ? (float)part : INFINITY, S};
+    hipLaunchKernelGGL(adc_setup_kernel, dim3((unsigned)B), dim3(kSetupThreads), 0, s, probes, P, offsets, C, N, cost,
+                       w.gcnt, w.dl, w.dpos);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (x.cap > 0) {
+        hipLaunchKernelGGL(adc_extra_kernel, dim3(1), dim3(kAdcThreads), 0, s, B, S, w.gcnt, x);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(scan, dim3((unsigned)(B * S + x.cap)), dim3(kAdcThreads), 0, s, Q, D, cent, P, perm,
+                       codes, M, codebooks, k, B, S, lists, x, w.gcnt, w.dl, w.dpos, w.handoff, w.hcnt, ids, dist);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (S > 1 || x.cap > 0)
+        hipLaunchKernelGGL(adc_merge_kernel, dim3((unsigned)(S > 1 ? B : std::min<int64_t>(B, x.cap))), dim3(kAdcThreads),
+                           0, s, w.handoff, w.hcnt, w.gcnt, P, S > 1 ? nullptr : x.split, x.nsplit, k, ids, dist);
     return hipGetLastError();
 }
 

@@ -478,11 +478,11 @@ constexpr int kMaxAdcProbes = 4096;
 // (list id, code range), each query's group count, and, when a query is cut
 // into several parts (at most P), a handoff of k keys per part.
 struct AdcScratch {
-    uint64_t *handoff;  // [B * 2P * k], used up to B * parts * k
-    int32_t *hcnt;      // [B * 2P] keys the part handed over (<= k)
+    uint64_t *handoff;  // [B * 2P * k]: keys of part s of query b from (b P + s) k on; past B P k the extra parts' list
+    int32_t *hcnt;      // [B * 2P] keys the part handed over (<= k); past B P the extra parts' counts
     int32_t *dl;        // [B * 2P] list of the group
     longlong2 *dpos;    // [B * 2P] first and end code position of the group
-    int32_t *gcnt;      // [B] groups of the query
+    int32_t *gcnt;      // [B] groups and parts of the query
 };
 // ids/dist [B, k].
 hipError_t launch_adc_scan(const float *Q, int64_t B, int D, const float *cent, int64_t C,

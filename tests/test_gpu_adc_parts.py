@@ -36,6 +36,30 @@ def test_branches_equal_the_oracle(ivf_ctx, oracle_mod, B, C, D, M, N, P, k):  #
     assert (ids == oids).all() and (dist.view(np.uint32) == odist.view(np.uint32)).all()
 
 
+@pytest.mark.parametrize("B,C,D,M,N,P,k", [
+    (300, 40, 64, 8, 400_000, 4, 300),   # a few heavy queries of many
+    (700, 12, 32, 4, 300_000, 6, 1024),  # more extra parts wanted than there are: scaled down
+    (1500, 30, 32, 4, 300_000, 2, 10),   # two probes, more queries than a round of the extra kernel takes
+    (20, 200, 32, 8, 2_000_000, 40, 64),  # several parts each, more for some
+    (260, 300, 32, 4, 200_000, 2, 1),
+])
+def test_skewed_lists_get_more_parts(ivf_ctx, oracle_mod, B, C, D, M, N, P, k):
+    """Lists of very different lengths, so that some queries are cut into more
+    parts than the others; the heaviest and the lightest queries are compared."""
+    q, c, probes, off, perm, codes, cb = setup(B + N, B, C, D, M, N, P, 2.0)
+    ids, dist = gpu_adc(ivf_ctx, q, c, probes, off, perm, codes, cb, k)
+    n = (off[probes + 1] - off[probes]).sum(1)
+    assert n.max() > 2 * 12 * 2048 and n.max() > 8 * n.min()  # (a part's least work: 12 lists, 2,048 codes each)
+    order = np.argsort(n, kind="stable")
+    pick = np.r_[order[:4], order[B // 2:B // 2 + 3], order[-5:]]
+    oids, odist = oracle_mod.adc_scan(q[pick], c, probes[pick], off, perm, codes, cb, k)
+    assert (ids[pick] == oids).all() and (dist[pick].view(np.uint32) == odist.view(np.uint32)).all()
+    # a query's result does not depend on the others: alone it takes other parts
+    one = order[-1:]
+    ids1, dist1 = gpu_adc(ivf_ctx, q[one], c, probes[one], off, perm, codes, cb, k)
+    assert (ids1 == ids[one]).all() and (dist1.view(np.uint32) == dist[one].view(np.uint32)).all()
+
+
 @pytest.mark.parametrize("B", [2, 1100])
 def test_equal_codes_rank_by_id(ivf_ctx, oracle_mod, B):  # noqa: F811
     q, c, probes, off, perm, codes, cb = setup(3, B, 6, 64, 8, 20000, 3)
