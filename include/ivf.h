@@ -69,7 +69,10 @@
  *     ivf_last_error() describes the problem.
  *   - Scratch memory is a caller-provided device workspace (ivf_set_workspace)
  *     of at least ivf_workspace_bytes() for the call; too small gives
- *     IVF_ENOMEM with the required size in ivf_last_error(). Two calls that
+ *     IVF_ENOMEM with the required size in ivf_last_error(). (Routing, k-means
+ *     and assignment take a smaller one that holds all but the f16 plane and
+ *     the lists of undecided rows, and then run the fp32 and two-plane
+ *     screens.) Two calls that
  *     share a context must not overlap on different streams.
  *   - Q, N == 0 is a no-op returning IVF_OK.
  *   - Supported shapes: 4 <= D <= 256 with D % 4 == 0 (else IVF_EUNSUPPORTED);

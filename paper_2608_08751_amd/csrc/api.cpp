@@ -196,13 +196,21 @@ struct RoutePlan {
     int rank_j;
     int qdp;      // padded dimension of the int8 and f16 route planes; 0 = fp32 kernels only
     int rank_safe, rank_max;  // f16 plane: see RouteArgs
+    bool f16;     // the f16 plane is laid out for what the int8 planes do not take
 };
+
+// The f16 plane takes the queries that are not uint8-valued from 10 GFLOP per
+// call on: building the plane and the filter's flushes cost 40-80 us however small the call,
+// against 8 us per GFLOP on fp32 MFMA (1,656 queries on 20,438 x 64: 242 us in f16,
+// 181 in fp32; 1,280 on 83,435 x 64: 157 and 214).
+bool f16_route(int64_t Q, int64_t C, int D) { return 2.0 * (double)Q * (double)C * (double)D >= 1e10; }
 
 RoutePlan plan_route(int64_t Q, int64_t C, int k, int rank_override, int D)
 {
     RoutePlan p;
     p.QB = std::max<int64_t>(1, std::min<int64_t>(Q, kRouteBatch));
     p.qdp = quant_dim(D);
+    p.f16 = C > 2048 && f16_route(Q, C, D);
     if (C <= 2048) {
         p.Cs = 0;
         p.Ss = 1;
@@ -278,8 +286,9 @@ RouteLayout layout_route(void *base, const RoutePlan &p, int64_t C)
     l.qbound = nullptr;
     if (p.qdp > 0) {
         // the two int8 planes or the f16 plane: one call uses one of them
-        l.qc = c.take<int8_t>((size_t)quantized_pad1(C) * 2 * p.qdp);
-        l.negb = c.take<int32_t>(quantized_pad1(C));
+        const int64_t pad = p.f16 ? quantized_pad1(C) : quantized_pad(C);
+        l.qc = c.take<int8_t>((size_t)pad * 2 * p.qdp);
+        l.negb = c.take<int32_t>(pad);
         l.qbound = c.take<float>(p.QB);
     }
     l.bytes = c.off + kAlign;
@@ -301,12 +310,6 @@ bool direct_route(const RoutePlan &p, int64_t Q, int64_t C, int k)
     if (p.Cs == 0) return true;
     return C <= kDirectMaxC && k <= 512 && Q <= p.QB && Q <= kDirectMaxQ && 2 * Q <= p.qdp;
 }
-
-// The f16 plane takes the queries that are not uint8-valued from 10 GFLOP per
-// call on: building the plane and the filter's flushes cost 40-80 us however small the call,
-// against 8 us per GFLOP on fp32 MFMA (1,656 queries on 20,438 x 64: 242 us in f16,
-// 181 in fp32; 1,280 on 83,435 x 64: 157 and 214).
-bool f16_route(int64_t Q, int64_t C, int D) { return 2.0 * (double)Q * (double)C * (double)D >= 1e10; }
 
 int64_t worklist_cap(int64_t N) { return std::min<int64_t>(N, 4096 + N / 64); }
 // Rows a one-pass screen may list before the next screen takes every row: a
@@ -347,6 +350,7 @@ struct AssignLayout {
     int32_t *list;
     int64_t list_cap;
     ResolveLists rs;
+    bool lean;
     int32_t *wl;
     int64_t wl_cap;
     double *fb_d;   // split fallback partial results
@@ -379,11 +383,14 @@ PqLayout layout_pq(void *base, int64_t n, int M, int num_cus)
     Carver c(base);
     PqLayout l{};
     l.labels = c.take<int32_t>((size_t)n * M);
-    l.cnt = c.take<uint32_t>(single_scratch_bytes(plan_single(n, kPqK, M, num_cus)) / 4);
+    const size_t cnt = single_scratch_bytes(plan_single(n, kPqK, M, num_cus));
+    const bool shared = cnt <= (size_t)kPqK * M * sizeof(double);  // the list build ends before the update begins
+    if (!shared) l.cnt = c.take<uint32_t>(cnt / 4);
     l.counts = c.take<int64_t>((size_t)kPqK * M);
     l.offsets = c.take<int64_t>((size_t)(kPqK + 1) * M);
     l.perm = c.take<uint32_t>((size_t)n * M);
     l.jpart = c.take<double>((size_t)kPqK * M);
+    if (shared) l.cnt = (uint32_t *)l.jpart;
     l.bytes = c.off;
     return l;
 }
@@ -391,8 +398,10 @@ PqLayout layout_pq(void *base, int64_t n, int M, int num_cus)
 // need_lists: counts/offsets/perm live in the workspace (k-means step);
 // need_build: count matrix for the list build; qdp > 0: quantised centroids
 // of padded dimension qdp for the int8 screen.
+// lean: without the f16 plane and the lists of rows to resolve (the fp32 screen
+// takes fp32 rows, the two-plane screen the rows that the single plane leaves).
 AssignLayout layout_assign(void *base, int64_t N, int64_t C, int qdp, bool need_build, bool need_lists,
-                           int num_cus)
+                           int num_cus, bool lean = false)
 {
     Carver c(base);
     AssignLayout l{};
@@ -400,8 +409,9 @@ AssignLayout layout_assign(void *base, int64_t N, int64_t C, int qdp, bool need_
     l.cnorm = c.take<float>(C);
     if (qdp > 0) {
         // the two int8 planes (uint8 rows) or the f16 plane (fp32 rows)
-        l.qc = c.take<int8_t>((size_t)quantized_pad1(C) * 2 * qdp);
-        l.negb = c.take<int32_t>(quantized_pad1(C));
+        const int64_t pad = lean ? quantized_pad(C) : quantized_pad1(C);
+        l.qc = c.take<int8_t>((size_t)pad * 2 * qdp);
+        l.negb = c.take<int32_t>(pad);
         if (qdp <= 128) {
             l.qc1 = c.take<int8_t>((size_t)quantized_pad1(C) * qdp);
             l.negb1 = c.take<int32_t>(quantized_pad1(C));
@@ -414,17 +424,23 @@ AssignLayout layout_assign(void *base, int64_t N, int64_t C, int qdp, bool need_
             l.ord1 = c.take<uint32_t>(C);
             l.pos1 = c.take<int32_t>(C);
         }
-        l.list_cap = rescreen_cap(std::min(N, kAssignSlice));
-        l.list = c.take<int32_t>(l.list_cap);
-        l.rs.duel_cap = duel_cap(std::min(N, kAssignSlice));
-        l.rs.duel = c.take<uint2>(l.rs.duel_cap);
-        l.rs.duel2 = c.take<int32_t>(l.rs.duel_cap);
-        l.rs.list_thr = c.take<int32_t>(l.list_cap);
-        l.rs.cand_cnt = c.take<uint32_t>(l.list_cap);
-        l.rs.cand = c.take<int32_t>((size_t)l.list_cap * kResolveCand);
-        l.rs.list2 = c.take<int32_t>(l.list_cap);
-        l.rs.duel_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 8 : nullptr;
-        l.rs.list2_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 9 : nullptr;
+        const int64_t n = std::min(N, kAssignSlice);
+        l.lean = lean;
+        if (!lean || qdp <= 128) {
+            l.list_cap = lean ? std::min<int64_t>(n, 4096 + n / 16) : rescreen_cap(n);
+            l.list = c.take<int32_t>(l.list_cap);
+        }
+        if (!lean) {
+            l.rs.duel_cap = duel_cap(n);
+            l.rs.duel = c.take<uint2>(l.rs.duel_cap);
+            l.rs.duel2 = c.take<int32_t>(l.rs.duel_cap);
+            l.rs.list_thr = c.take<int32_t>(l.list_cap);
+            l.rs.cand_cnt = c.take<uint32_t>(l.list_cap);
+            l.rs.cand = c.take<int32_t>((size_t)l.list_cap * kResolveCand);
+            l.rs.list2 = c.take<int32_t>(l.list_cap);
+            l.rs.duel_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 8 : nullptr;
+            l.rs.list2_cnt = l.sc.mc2_bits ? l.sc.mc2_bits + 9 : nullptr;
+        }
     }
     l.wl_cap = worklist_cap(std::min(N, kAssignSlice));
     l.wl = c.take<int32_t>(l.wl_cap);
@@ -479,12 +495,27 @@ struct DeviceGuard {
     }
 };
 
-ivf_status check_ws(ivf_ctx *ctx, size_t need)
+// least: what the call can do with; need: what ivf_workspace_bytes asks for
+ivf_status check_ws(ivf_ctx *ctx, size_t least, size_t need)
 {
-    if (!ctx->ws || ctx->ws_bytes < need)
+    if (!ctx->ws || ctx->ws_bytes < least)
         return fail(ctx, IVF_ENOMEM, "workspace too small: %zu bytes required, %zu provided", need,
                     ctx->ws ? ctx->ws_bytes : (size_t)0);
     return IVF_OK;
+}
+ivf_status check_ws(ivf_ctx *ctx, size_t need) { return check_ws(ctx, need, need); }
+
+// The layout of an assignment with its list build in the context's workspace:
+// lean when the whole one does not fit.
+ivf_status fit_assign(ivf_ctx *ctx, int64_t N, int64_t C, int D, bool need_lists, AssignLayout &l)
+{
+    const int qdp = quant_dim(D), cus = ctx->num_cus;
+    const size_t need = layout_assign(nullptr, N, C, qdp, true, need_lists, cus).bytes;
+    const bool lean = ctx->ws_bytes < need;
+    const size_t least = lean ? layout_assign(nullptr, N, C, qdp, true, need_lists, cus, true).bytes : need;
+    const ivf_status st = check_ws(ctx, least, need);
+    if (st == IVF_OK) l = layout_assign(ctx->ws, N, C, qdp, true, need_lists, cus, lean);
+    return st;
 }
 
 #define HIP_TRY(expr)                                                                      \
@@ -553,7 +584,7 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
     TIMED("fill", launch_fill_u32(l.sc.mc2_bits, 64, 0u, s));
     TIMED("centroid_norms", launch_centroid_norms(cent, C, D, l.cnorm, l.sc.mc2_bits, s));
     const bool int8 = rowtype == kRowU8 && !ctx->fp32_screen;
-    const bool f16 = rowtype == kRowF32 && !ctx->fp32_screen && l.list;
+    const bool f16 = rowtype == kRowF32 && !ctx->fp32_screen && !l.lean;
     const bool single = int8 && l.qc1 && !ctx->two_plane_only;
     uint32_t *q_bad = l.sc.mc2_bits + 2;
     uint32_t *q_bad1 = l.sc.mc2_bits + 3;
@@ -597,7 +628,7 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
             TIMED("fill", launch_fill_u32(l.sc.wl_cnt, 1, 0u, s));
             if (single || f16) {
                 TIMED("fill", launch_fill_u32(list_cnt, 1, 0u, s));
-                TIMED("fill", launch_fill_u32(l.rs.duel_cnt, 2, 0u, s));
+                if (!l.lean) TIMED("fill", launch_fill_u32(l.rs.duel_cnt, 2, 0u, s));
             }
         }
         ScreenArgs a{};
@@ -699,12 +730,13 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
                 // near ties: decided from collected candidates (a forced
                 // rescreen or a test's list capacity keeps the two-plane
                 // screen of the listed rows)
-                const bool collect = !q.force_rescreen && ctx->rescreen_cap == 0;
+                const bool collect = !q.force_rescreen && ctx->rescreen_cap == 0 && !l.lean;
                 q.rs = l.rs;
                 if (!collect) q.rs.list_thr = nullptr;
                 TIMED("screen_top1_i8s", launch_screen_i8_single(DP, q, ctx->num_cus, s));
                 if (collect) TIMED("collect_i8", launch_collect_i8(DP, q, ctx->num_cus, s));
-                TIMED("resolve", launch_resolve(rowtype, resolve_args(q.rs, q.list_cap, ord1), ctx->num_cus, s));
+                if (!l.lean)
+                    TIMED("resolve", launch_resolve(rowtype, resolve_args(q.rs, q.list_cap, ord1), ctx->num_cus, s));
             }
             TIMED("screen_top1_i8", launch_screen_i8(DP, q, ctx->num_cus, s));
             a.gate = q_bad;
@@ -1044,7 +1076,7 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
     // synchronisation) when a centroid does not fit the int8 planes or the f16
     // window is too wide.
     const bool planes = p.qdp > 0 && !ctx->fp32_screen;
-    const bool f16 = planes && f16_route(Q, C, D);
+    const bool f16 = planes && p.f16;
     uint32_t *w = l.sc.mc2_bits;
     if (planes) {
         TIMED("route_i8_check", launch_route_i8_check(queries, Q, D, w + kWordNotI8, s));
@@ -1184,9 +1216,11 @@ ivf_status ivf_route(ivf_ctx *ctx, const float *queries, int64_t Q, const float 
     bool done = false;
     ivf_status st = check_route(ctx, queries, Q, centroids, C, D, nprobe, out_ids, out_dist, &done);
     if (st != IVF_OK || done) return st;
-    const RoutePlan p = plan_route(Q, C, nprobe, ctx->sample_rank, D);
+    RoutePlan p = plan_route(Q, C, nprobe, ctx->sample_rank, D);
     const size_t need = layout_route(nullptr, p, C).bytes;
-    if ((st = check_ws(ctx, need)) != IVF_OK) return st;
+    // without room for the f16 plane's padding the fp32 kernels take its place
+    if (p.f16 && ctx->ws_bytes < need) p.f16 = false;
+    if ((st = check_ws(ctx, layout_route(nullptr, p, C).bytes, need)) != IVF_OK) return st;
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(ctx, IVF_EDEVICE, "no usable device (context device %d)", ctx->device);
     return enqueue_route(ctx, queries, Q, centroids, C, D, nprobe, out_ids, out_dist, p, ctx->ws);
@@ -1209,8 +1243,9 @@ ivf_status ivf_route_noalloc(ivf_ctx *ctx, const float *queries, int64_t Q, cons
         q1.QB = 1;
         return layout_route(nullptr, q1, C).bytes;
     };
-    // the int8 route planes are left out (fp32 kernels only) when they do not
-    // fit beside one query
+    // the f16 plane, then the int8 route planes are left out (fp32 kernels
+    // only) when they do not fit beside one query
+    if (one_query() > kStaticScratchBytes) p.f16 = false;
     if (one_query() > kStaticScratchBytes) p.qdp = 0;
     const size_t one = one_query();
     if (one > kStaticScratchBytes)
@@ -1276,12 +1311,11 @@ ivf_status ivf_kmeans_step(ivf_ctx *ctx, const void *train, int dt, int64_t N,
         for (int j = i + 1; j < 4; ++j)
             if (overlap(outs[i], osz[i], outs[j], osz[j])) return fail(ctx, IVF_EINVAL, "outputs overlap");
     }
-    const size_t need = layout_assign(nullptr, N, C, quant_dim(D), true, true, ctx->num_cus).bytes;
-    if ((st = check_ws(ctx, need)) != IVF_OK) return st;
+    AssignLayout l;
+    if ((st = fit_assign(ctx, N, C, D, true, l)) != IVF_OK) return st;
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(ctx, IVF_EDEVICE, "no usable device (context device %d)", ctx->device);
 
-    const AssignLayout l = layout_assign(ctx->ws, N, C, quant_dim(D), true, true, ctx->num_cus);
     const int rowtype = dt == IVF_U8 ? kRowU8 : kRowF32;
     if ((st = enqueue_assign(ctx, train, rowtype, N, centroids, C, D, out_labels, l, hint_labels)) != IVF_OK)
         return st;
@@ -1317,12 +1351,11 @@ ivf_status ivf_assign_build(ivf_ctx *ctx, const void *base, int dt, int64_t N,
         for (int j = i + 1; j < 4; ++j)
             if (overlap(outs[i], osz[i], outs[j], osz[j])) return fail(ctx, IVF_EINVAL, "outputs overlap");
     }
-    const size_t need = layout_assign(nullptr, std::max<int64_t>(N, 1), C, quant_dim(D), true, false, ctx->num_cus).bytes;
-    if ((st = check_ws(ctx, need)) != IVF_OK) return st;
+    AssignLayout l;
+    if ((st = fit_assign(ctx, std::max<int64_t>(N, 1), C, D, false, l)) != IVF_OK) return st;
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(ctx, IVF_EDEVICE, "no usable device (context device %d)", ctx->device);
 
-    const AssignLayout l = layout_assign(ctx->ws, std::max<int64_t>(N, 1), C, quant_dim(D), true, false, ctx->num_cus);
     const int rowtype = dt == IVF_U8 ? kRowU8 : kRowF32;
     if (N > 0 && (st = enqueue_assign(ctx, base, rowtype, N, centroids, C, D, out_labels, l)) != IVF_OK)
         return st;

@@ -335,3 +335,38 @@ def test_no_cpu_fallback_without_gpu():
         pytest.skip("GPU present")
     with pytest.raises(Exception):
         ivf.Context(0)
+
+
+@pytest.mark.parametrize("op,sizes,nbytes", [
+    ("route", (1000, 65537, 256, 1000), 71256992), ("route", (20000, 4000, 100, 64), 139870208),
+    ("kmeans", (2_000_000, 257, 256), 20322056), ("kmeans", (100_000, 65536, 96), 27532288),
+    ("kmeans", (1000, 100, 4), 2676256), ("assign", (1 << 28, 65537, 256), 65062080),
+    ("assign", (2_000_000, 65536, 128), 42626304), ("assign", (1000, 2048, 200), 2915584),
+    ("pq", (20_000, 256, 256), 42903296),
+])
+def test_smaller_workspaces_that_calls_accept(vctx, op, sizes, nbytes):
+    """Workspaces without room for the f16 plane or the lists of undecided rows:
+    less than ivf_workspace_bytes, and enough (the slower screens run)."""
+    lib, h = vctx.lib, vctx.handle
+    big = [P(i * 64 * GB) for i in range(1, 8)]
+    ops = {"route": B.IVF_OP_ROUTE, "kmeans": B.IVF_OP_KMEANS_STEP, "assign": B.IVF_OP_ASSIGN_BUILD,
+           "pq": B.IVF_OP_PQ_TRAIN_STEP}
+    lib.ivf_set_workspace(h, P(600 * GB), nbytes)
+    if op == "route":
+        Q, C, D, k = sizes
+        call = lambda: lib.ivf_route(h, big[0], Q, big[1], C, D, k, big[2], big[3])
+        need = lib.ivf_workspace_bytes(ops[op], Q, C, D, k)
+    elif op == "pq":
+        n, D, M = sizes
+        call = lambda: lib.ivf_pq_train_step(h, big[0], n, D, M, big[1], 0, 0, big[2], big[3], big[4])
+        need = lib.ivf_workspace_bytes(ops[op], n, M, D, 0)
+    else:
+        N, C, D = sizes
+        call = {"kmeans": lambda: lib.ivf_kmeans_step(h, big[0], B.IVF_F32, N, big[1], C, D, 7, 0, big[2], big[3], big[4],
+                                                      big[5], None),
+                "assign": lambda: lib.ivf_assign_build(h, big[0], B.IVF_U8, N, big[1], C, D, big[2], big[3], big[4],
+                                                       big[5])}[op]
+        need = lib.ivf_workspace_bytes(ops[op], N, C, D, 0)
+    assert call() == B.IVF_EDEVICE  # every check passed (the context has no device)
+    lib.ivf_set_workspace(h, P(600 * GB), nbytes // 2)
+    assert call() == B.IVF_ENOMEM and str(need) in vctx.error()
