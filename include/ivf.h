@@ -231,10 +231,10 @@ ivf_status ivf_build_lists(ivf_ctx *ctx, const int32_t *labels, int64_t N, int64
  *          where the whole key matrix is kept)
  *   out[3] route: queries whose candidate list overflowed
  *   out[4] route: centroids in the threshold sample
- *   out[5] assignment of uint8 rows: 1 when screened on int8 MFMA
+ *   out[5] assignment of uint8 rows, route: 1 when screened on int8 MFMA
  *   out[6] assignment: rows the first screen (one int8 plane, or f16 for
  *          fp32 rows) left with more than two possible centroids
- *   out[7] reserved (0) */
+ *   out[7] route: internal batches of queries screened on the f16 plane */
 ivf_status ivf_last_stats(ivf_ctx *ctx, int64_t out[8]);
 
 /* Test, tuning and profiling knobs (values persist on the context):

@@ -177,7 +177,7 @@ class Context:
     def last_stats(self):
         out = (ctypes.c_int64 * 8)()
         self.check(self.lib.ivf_last_stats(self.handle, out), "ivf_last_stats")
-        keys = ("fallback", "refine2", "candidates", "overflow", "sample", "screen_i8", "rescreen")
+        keys = ("fallback", "refine2", "candidates", "overflow", "sample", "screen_i8", "rescreen", "screen_f16")
         return {k: int(out[i]) for i, k in enumerate(keys)}
 
 

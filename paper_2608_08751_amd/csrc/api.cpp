@@ -1114,6 +1114,7 @@ ivf_status enqueue_route(ivf_ctx *ctx, const float *queries, int64_t Q, const fl
         rf.mc2_bits = l.sc.mc2_bits;
         rf.w = w;
         rf.cpad = quantized_pad1(C);
+        rf.stats = l.sc.stats;
         RouteArgs r{};
         r.queries = qrows;
         r.nq = nb;

@@ -42,6 +42,7 @@ enum StatSlot {
     kStatSample = 4,
     kStatScreenI8 = 5,  // 1 when the uint8 rows were screened on int8 MFMA
     kStatRescreen = 6,  // rows the single-plane int8 screen left with more than two candidates
+    kStatScreenF16 = 7,  // routing batches whose filter ran on the f16 plane
     kNumStats = 8
 };
 
@@ -358,6 +359,7 @@ struct RouteF16Args {
     uint32_t *cand_cnt;
     uint2 *cand;
     int L;
+    unsigned long long *stats;  // [kStatScreenF16]
 };
 hipError_t launch_route_f16(int mode, int DP, const RouteF16Args &a, int num_cus, hipStream_t s);
 // Exact fp64 scan of the rows on the assignment worklist (labels -1). The

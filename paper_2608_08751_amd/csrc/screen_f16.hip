@@ -607,6 +607,7 @@ __global__ __launch_bounds__(512, 2) void route_f16_kernel(RouteF16Args a)
     __shared__ uint2 qm[KEYS ? 1 : G::W * kWaveQueue];
     __shared__ float tvs[KEYS ? 1 : G::ROWS];
     if (route_mode(a.w) != kModeF16) return;
+    if (!KEYS && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(a.stats + kStatScreenF16, 1ull);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, jl = lane & 31;
     const float sc = f16_scale(*a.mc2_bits);
     const int64_t nchunks = (a.nsub + G::SUB - 1) / G::SUB;

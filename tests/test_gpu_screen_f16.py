@@ -114,7 +114,9 @@ def test_large_route_equals_the_oracle(ivf_ctx, oracle_mod, kind, Q, C, D, k):  
     q, c = data(kind, Q, C, D, seed=Q + D)
     ids, dist = ivf.ivf_route(ivf_ctx, to_dev(q), to_dev(c), k)
     torch.cuda.synchronize()
-    print(kind, Q, C, D, k, ivf_ctx.last_stats(), flush=True)
+    st = ivf_ctx.last_stats()
+    print(kind, Q, C, D, k, st, flush=True)
+    assert st["screen_f16"] == (0 if kind in ("offset", "range") else (Q + 16383) // 16384)
     pick = np.r_[0:60, Q - 60:Q]
     oids, odist = oracle_mod.route(q[pick], c, k)
     assert (ids.cpu().numpy()[pick] == oids).all() and (dist.cpu().numpy()[pick] == odist).all()
@@ -148,17 +150,49 @@ def test_threshold_ranks_on_the_f16_plane(ivf_ctx, oracle_mod, rank):  # noqa: F
     assert (ids.cpu().numpy()[pick] == oids).all() and (dist.cpu().numpy()[pick] == odist).all()
 
 
-def test_route_batches_and_odd_queries(ivf_ctx, oracle_mod):  # noqa: F811
-    """Two internal batches: one query of the second has no f16 bound, so that
-    batch alone goes to the fp32 kernels."""
+@pytest.mark.parametrize("odd,batches", [(None, 2), (5, 1), (16384 + 5, 1), ("both", 0)])
+def test_route_batches_and_odd_queries(ivf_ctx, oracle_mod, odd, batches):  # noqa: F811
+    """Two internal batches: where a query of one has no f16 bound, that batch
+    alone goes to the fp32 kernels."""
     import torch
 
     import paper_2608_08751_amd as ivf
 
-    q, c = data("plain", 16384 + 700, 2300, 32, seed=9)
-    q[16384 + 5] *= np.float32(1e6)
+    Q, C, D = 16384 + 700, 9300, 32
+    assert 2 * Q * C * D >= 1e10  # a call the f16 plane takes
+    q, c = data("plain", Q, C, D, seed=9)
+    for i in () if odd is None else (5, 16384 + 5) if odd == "both" else (odd,):
+        q[i] *= np.float32(1e6)
     ids, dist = ivf.ivf_route(ivf_ctx, to_dev(q), to_dev(c), 8)
     torch.cuda.synchronize()
+    st = ivf_ctx.last_stats()
+    assert st["screen_f16"] == batches and st["screen_i8"] == 0
+    pick = np.r_[0:64, 16384 - 8:16384 + 64, 16384 + 636:16384 + 700]
+    oids, odist = oracle_mod.route(q[pick], c, 8)
+    assert (ids.cpu().numpy()[pick] == oids).all() and (dist.cpu().numpy()[pick] == odist).all()
+
+
+@pytest.mark.parametrize("kind", ["int8", "centroid", "query"])
+def test_integer_queries_and_what_does_not_quantise(ivf_ctx, oracle_mod, kind):  # noqa: F811
+    """uint8-valued queries in two batches: the int8 planes take them; one centroid
+    outside their range sends both batches to the fp32 kernels (no f16 plane
+    was built), one other query value both to the f16 plane."""
+    import torch
+
+    import paper_2608_08751_amd as ivf
+
+    Q, C, D = 16384 + 700, 9300, 32
+    r = np.random.default_rng(4)
+    c = (255 * r.random((C, D))).astype(np.float32)
+    q = r.integers(0, 256, (Q, D)).astype(np.float32)
+    if kind == "centroid":
+        c[77, 3] = 300.0
+    elif kind == "query":
+        q[16384 + 9, 1] = 17.5
+    ids, dist = ivf.ivf_route(ivf_ctx, to_dev(q), to_dev(c), 8)
+    torch.cuda.synchronize()
+    st = ivf_ctx.last_stats()
+    assert (st["screen_i8"], st["screen_f16"]) == {"int8": (1, 0), "centroid": (0, 0), "query": (0, 2)}[kind]
     pick = np.r_[0:64, 16384 - 8:16384 + 64, 16384 + 636:16384 + 700]
     oids, odist = oracle_mod.route(q[pick], c, 8)
     assert (ids.cpu().numpy()[pick] == oids).all() and (dist.cpu().numpy()[pick] == odist).all()
