@@ -326,6 +326,48 @@ __global__ __launch_bounds__(256) void route_threshold_min_kernel(RouteArgs a)
     }
 }
 
+// Ranks nr re-evaluated candidates (distances and ids in LDS) by (distance, id)
+// and writes the first k: every thread counts, for R of its candidates at a
+// time, the ones before them, so a pass over the list serves R (16,384 queries on
+// 2,048 x 32 centroids, k = 1,024: 5.6 -> 2.4 ms; every centroid a candidate: 20.6 ->
+// 8.4).
+template <int R>
+__device__ __forceinline__ void rank_some(const double *__restrict__ bd, const int *__restrict__ bi, int nr, int k, int i0,
+                                          int32_t *__restrict__ ids, float *__restrict__ dist)
+{
+    double d[R];
+    int id[R], rank[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = min(i0 + r * (int)blockDim.x, nr - 1);
+        d[r] = bd[i];
+        id[r] = bi[i];
+        rank[r] = 0;
+    }
+#pragma unroll 4
+    for (int j = 0; j < nr; ++j) {
+        const double dj = bd[j];
+        const int ij = bi[j];
+#pragma unroll
+        for (int r = 0; r < R; ++r) rank[r] += dist_lt(dj, ij, d[r], id[r]) ? 1 : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (i0 + r * (int)blockDim.x < nr && rank[r] < k) {
+            ids[rank[r]] = id[r];
+            if (dist) dist[rank[r]] = (float)d[r];
+        }
+    }
+}
+
+__device__ __forceinline__ void write_ranked(const double *__restrict__ bd, const int *__restrict__ bi, int nr, int k,
+                                             int32_t *__restrict__ ids, float *__restrict__ dist)
+{
+    int i = threadIdx.x;
+    for (; i + (int)blockDim.x < nr; i += 4 * (int)blockDim.x) rank_some<4>(bd, bi, nr, k, i, ids, dist);
+    if (i < nr) rank_some<1>(bd, bi, nr, k, i, ids, dist);
+}
+
 // Certified selection of one query's top-k from its screened candidates.
 // Candidates = every centroid with key <= tau. Let kth = the k-th smallest key
 // (radix select). If tau >= kth + 2B, every centroid outside
@@ -394,17 +436,7 @@ __global__ __launch_bounds__(256) void route_select_kernel(RouteArgs a)
     for (int i = threadIdx.x; i < nr; i += blockDim.x)
         rd[i] = exact_dist(qrow, a.cent + (int64_t)rid[i] * a.D, a.D);
     __syncthreads();
-    // rank of each re-evaluated candidate in (distance, id) order
-    for (int i = threadIdx.x; i < nr; i += blockDim.x) {
-        const double di = rd[i];
-        const int ii = rid[i];
-        int rank = 0;
-        for (int j = 0; j < nr; ++j) rank += dist_lt(rd[j], rid[j], di, ii) ? 1 : 0;
-        if (rank < a.k) {
-            a.out_ids[q * a.k + rank] = ii;
-            if (a.out_dist) a.out_dist[q * a.k + rank] = (float)di;
-        }
-    }
+    write_ranked(rd, rid, nr, a.k, a.out_ids + q * a.k, a.out_dist ? a.out_dist + q * a.k : nullptr);
 }
 
 // Exact fp64 scan of all centroids for one query (its row staged in LDS): a
@@ -613,18 +645,7 @@ __global__ __launch_bounds__(T) void direct_select_kernel(DirectArgs a)
     }
     for (int i = t; i < nr; i += T) bd[i] = exact_dist_lds4(qrow, a.cent + (int64_t)bi[i] * a.D, a.D);
     __syncthreads();
-    // rank of each re-evaluated candidate in (distance, id) order
-    for (int i = t; i < nr; i += T) {
-        const double di = bd[i];
-        const int ii = bi[i];
-        int rank = 0;
-#pragma unroll 4
-        for (int j = 0; j < nr; ++j) rank += dist_lt(bd[j], bi[j], di, ii) ? 1 : 0;
-        if (rank < a.k) {
-            a.out_ids[q * a.k + rank] = ii;
-            if (a.out_dist) a.out_dist[q * a.k + rank] = (float)di;
-        }
-    }
+    write_ranked(bd, bi, nr, a.k, a.out_ids + q * a.k, a.out_dist ? a.out_dist + q * a.k : nullptr);
 }
 
 int grid_for(int64_t n, int per_block, int cap)
@@ -671,9 +692,9 @@ hipError_t launch_route_select(const RouteArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// Threads by table size: up to 256 centroids one wave holds the row and needs
+// Threads by table size: up to 512 centroids one wave holds the row and needs
 // no barrier (a call of 16,384 queries on 256 x 256: 162 us, 291 with four
-// waves);
+// waves; on 300 x 256 162 and 264);
 // a workgroup of 256 keeps up to 2,048 keys, eight per thread, and several
 // share a CU; past that 1,024 threads read the row.
 hipError_t launch_direct_select(const DirectArgs &a, hipStream_t s)
@@ -681,6 +702,8 @@ hipError_t launch_direct_select(const DirectArgs &a, hipStream_t s)
     const dim3 grid((unsigned)a.nq);
     if (a.C <= 64 * 4)
         hipLaunchKernelGGL((direct_select_kernel<64, 4>), grid, dim3(64), 0, s, a);
+    else if (a.C <= 64 * 8)
+        hipLaunchKernelGGL((direct_select_kernel<64, 8>), grid, dim3(64), 0, s, a);
     else if (a.C <= 256 * 4)
         hipLaunchKernelGGL((direct_select_kernel<256, 4>), grid, dim3(256), 0, s, a);
     else if (a.C <= 256 * 8)

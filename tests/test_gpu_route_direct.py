@@ -26,7 +26,7 @@ def check(ctx, oracle_mod, q, c, k, pick=slice(None)):
 
 
 @pytest.mark.parametrize("Q,C,D,k", [
-    (1, 1, 4, 1), (3, 2, 8, 2), (33, 31, 12, 31), (5, 33, 100, 7), (90, 256, 256, 256), (90, 257, 256, 200), (300, 1024, 128, 16), (64, 1025, 96, 128),
+    (1, 1, 4, 1), (3, 2, 8, 2), (33, 31, 12, 31), (5, 33, 100, 7), (90, 256, 256, 256), (90, 257, 256, 200), (40, 300, 32, 300), (40, 512, 64, 400), (40, 513, 64, 100), (300, 1024, 128, 16), (64, 1025, 96, 128),
     (31, 1025, 64, 129), (70, 2048, 256, 1024), (32, 2048, 160, 1), (1, 2049, 128, 512), (32, 2049, 64, 513),
     (33, 2049, 64, 64), (16, 4000, 32, 9), (17, 4000, 32, 9), (32, 16384, 100, 64), (8, 16385, 96, 128),
     (4, 65536, 36, 100), (18, 65536, 36, 1), (3, 65537, 36, 100),
