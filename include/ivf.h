@@ -29,7 +29,8 @@
  *     What its window leaves undecided, and data f16 cannot hold, is screened
  *     on fp32 MFMA (v_mfma_f32_32x32x2_f32; the bound is the fp32 dot-product
  *     rounding bound for any summation order), as are routing tables of at
- *     most 2,048 centroids;
+ *     most 2,048 centroids, and assignments of less than 0.8 GFLOP (2 N C D) to
+ *     tables of less than 32,000 values;
  *   - uint8 rows (k-means and assignment): int8 MFMA
  *     (v_mfma_i32_32x32x32_i8) on rows x - 128 against quantised centroids,
  *     whose integer scores are exact; the bound is the quantisation error

@@ -311,6 +311,16 @@ bool direct_route(const RoutePlan &p, int64_t Q, int64_t C, int k)
     return C <= kDirectMaxC && k <= 512 && Q <= p.QB && Q <= kDirectMaxQ && 2 * Q <= p.qdp;
 }
 
+// fp32 rows are screened on f16 where the table is long enough that a tile's
+// scan of it, or the call large enough that the whole, outweighs the four more
+// launches (5 us each): 300 rows x 100 x 32 60 us in f16 and 45 on fp32 MFMA alone,
+// 3,000 x 300 x 96 102-121 and 98-104, 50,000 x 50 x 64 60-82 and 44-67; 5,000 x 500 x
+// 64 104 and 104, 1,000 x 1,000 x 64 108 and 132, 20,000 x 500 x 128 134 and 157.
+bool f16_assign(int64_t N, int64_t C, int D, int DP)
+{
+    return C * DP >= 32000 || 2.0 * (double)N * (double)C * (double)D >= 8e8;
+}
+
 int64_t worklist_cap(int64_t N) { return std::min<int64_t>(N, 4096 + N / 64); }
 // Rows a one-pass screen may list before the next screen takes every row: a
 // quarter of a call of ordinary size (a 131,072 x 100 table of close centroids
@@ -584,7 +594,7 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
     TIMED("fill", launch_fill_u32(l.sc.mc2_bits, 64, 0u, s));
     TIMED("centroid_norms", launch_centroid_norms(cent, C, D, l.cnorm, l.sc.mc2_bits, s));
     const bool int8 = rowtype == kRowU8 && !ctx->fp32_screen;
-    const bool f16 = rowtype == kRowF32 && !ctx->fp32_screen && !l.lean;
+    const bool f16 = rowtype == kRowF32 && !ctx->fp32_screen && !l.lean && f16_assign(N, C, D, DP);
     const bool single = int8 && l.qc1 && !ctx->two_plane_only;
     uint32_t *q_bad = l.sc.mc2_bits + 2;
     uint32_t *q_bad1 = l.sc.mc2_bits + 3;

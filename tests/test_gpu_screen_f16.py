@@ -1,4 +1,5 @@
-"""The f16 screen of fp32 rows and queries: labels, ids and distances equal the
+"""The f16 screen of fp32 rows and queries (and the small calls beside it that
+stay on fp32): labels, ids and distances equal the
 oracle's on ordinary data, among near ties (two candidates, a few, more than
 the collecting pass keeps), and where f16 cannot decide: data far from the
 origin (its window covers every centroid), values beyond its range or below
@@ -40,6 +41,9 @@ def data(kind, N, C, D, seed):
     ("plain", 900, 130, 256), ("plain", 600, 300, 160), ("plain", 520, 700, 64),
     ("ties", 4000, 900, 100), ("ties", 2500, 600, 200), ("offset", 2000, 500, 96), ("range", 1500, 400, 128),
     ("tiny", 800, 200, 96), ("huge", 800, 200, 96), ("zero", 100, 70, 32),
+    # small tables, which take f16 from 0.8 GFLOP on; the smallest calls above stay on fp32
+    ("plain", 200_000, 65, 36), ("plain", 45_000, 257, 96), ("plain", 1_100_000, 3, 128), ("ties", 120_000, 33, 128),
+    ("zero", 100_000, 70, 64), ("range", 60_000, 130, 64), ("tiny", 3000, 400, 96), ("huge", 3000, 400, 96),
 ])
 def test_assign_equals_the_oracle(ivf_ctx, oracle_mod, kind, N, C, D):  # noqa: F811
     import torch
