@@ -267,10 +267,10 @@ ivf_status ivf_last_stats(ivf_ctx *ctx, int64_t out[8]);
  *                           for fp32 rows; results must not change)
  *   IVF_OPT_RESCREEN_CAP    > 0: capacity of the first screen's list of rows
  *                           for the next one, which then takes them
- *                           (default 4,096 + N / 4, N / 16 from 2^26 rows on,
- *                           with the rows' candidates collected; past it the
- *                           next screen takes every row); speed only, never
- *                           results
+ *                           (default 4,096 + max(N / 16, min(N / 4, 2^22)) of a
+ *                           slice's N rows, with their candidates collected;
+ *                           past it the next screen takes every row); speed
+ *                           only, never results
  *   IVF_OPT_ASSIGN_SLICE    > 0: rows per assignment slice, below the
  *                           default 2^28 (each slice is screened with its own
  *                           worklists); speed only, never results
@@ -445,8 +445,8 @@ ivf_status ivf_pq_train_step(ivf_ctx *ctx, const float *x, int64_t n, int32_t D,
  *   codebooks  [M, 256, D/M] fp32
  *   k          handoff per query, 1 <= k <= 1024; P <= 4096
  *   out_ids    [B, k] uint32 row ids     out_dist [B, k] fp32
- * Workspace: ivf_workspace_bytes(IVF_OP_ADC_SCAN, B, P, D, k) = 8 B*P*k
- * bytes (+256): large batches can be scanned in slices of queries.
+ * Workspace: ivf_workspace_bytes(IVF_OP_ADC_SCAN, B, P, D, k), 16 B*P*k
+ * bytes and 56 B*P more: large batches can be scanned in slices of queries.
  * Errors: IVF_EINVAL, IVF_EUNSUPPORTED (D, M, N), IVF_ENOMEM, IVF_EDEVICE. */
 ivf_status ivf_adc_scan(ivf_ctx *ctx, const float *queries, int64_t B, int32_t D,
                         const float *centroids, int64_t C, const int32_t *probes, int32_t P,

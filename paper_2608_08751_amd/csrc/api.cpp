@@ -323,10 +323,10 @@ bool f16_assign(int64_t N, int64_t C, int D, int DP)
 
 int64_t worklist_cap(int64_t N) { return std::min<int64_t>(N, 4096 + N / 64); }
 // Rows a one-pass screen may list before the next screen takes every row: a
-// quarter of a call of ordinary size (a 131,072 x 100 table of close centroids
+// quarter of a call of up to 2^24 rows (a 131,072 x 100 table of close centroids
 // lists 16 %; past a quarter a full second screen costs about as much as
-// collecting), a sixteenth of a call of more than 2^26 rows, where the lists'
-// 48 bytes per entry would grow into gigabytes.
+// collecting), 2^22 rows up to 2^26, a sixteenth past that: the lists' 48 bytes
+// per entry would grow into gigabytes.
 int64_t rescreen_cap(int64_t N)
 {
     return std::min<int64_t>(N, 4096 + std::max<int64_t>(N / 16, std::min<int64_t>(N / 4, (int64_t)1 << 22)));
@@ -761,8 +761,8 @@ ivf_status enqueue_assign(ivf_ctx *ctx, const void *rows, int rowtype, int64_t N
 }
 
 // List build: one partition by the label for C <= 256 lists, the two-level
-// radix partition for C <= 65,536, the single-pass per-block build otherwise. `scratch` is the build area of the
-// workspace.
+// radix partition for C <= 65,536, the single-pass per-block build otherwise.
+// `scratch` is the build area of the workspace.
 ivf_status enqueue_build(ivf_ctx *ctx, int64_t N, int64_t C, const int32_t *labels, void *scratch,
                          int64_t *counts, int64_t *offsets, uint32_t *perm)
 {
