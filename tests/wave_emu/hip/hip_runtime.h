@@ -42,6 +42,7 @@ inline float4 make_float4(float x, float y, float z, float w) { return float4{x,
 struct longlong2 {
     long long x, y;
 };
+inline longlong2 make_longlong2(long long x, long long y) { return longlong2{x, y}; }
 struct double2 {
     double x, y;
 };
@@ -310,6 +311,17 @@ inline int __builtin_amdgcn_readfirstlane(int v)
     return r;
 }
 
+inline int __builtin_amdgcn_readlane(int v, int src)
+{
+    emu::Wave &w = emu::wave();
+    memcpy(w.buf[emu::lane()], &v, sizeof(int));
+    w.bar->arrive_and_wait();
+    int r;
+    memcpy(&r, w.buf[src & 63], sizeof(int));
+    w.bar->arrive_and_wait();
+    return r;
+}
+
 inline void __builtin_amdgcn_sched_barrier(int) {}
 // the wave's lanes meet (every lane of the wave must come)
 inline void __builtin_amdgcn_wave_barrier() { emu::wave().bar->arrive_and_wait(); }
@@ -327,6 +339,19 @@ inline float __uint_as_float(uint32_t u)
     float f;
     memcpy(&f, &u, 4);
     return f;
+}
+inline long long __double_as_longlong(double d)
+{
+    long long v;
+    memcpy(&v, &d, 8);
+    return v;
+}
+inline double __hiloint2double(int hi, int lo)
+{
+    const uint64_t u = (uint64_t)(uint32_t)hi << 32 | (uint32_t)lo;
+    double d;
+    memcpy(&d, &u, 8);
+    return d;
 }
 // double to float, rounded toward +infinity
 inline float __double2float_ru(double x)
