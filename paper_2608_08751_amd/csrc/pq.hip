@@ -187,7 +187,7 @@ __device__ __forceinline__ void pq_stage(const float *__restrict__ cb, int dsub,
         reinterpret_cast<float *>(img + G::BIAS)[(j >> 5) * 32 + 16 * hf + reg] = -(float)(0.5 * b);
     }
     r2 = wave_max(r2);
-    if (lane < 16) sub.mu[lane] = 0.0f;
+    if (lane >= DS && lane < 16) sub.mu[lane] = 0.0f;
 #pragma unroll
     for (int d = 0; d < DS; ++d)
         if (lane == 0) sub.mu[d] = mu[d];

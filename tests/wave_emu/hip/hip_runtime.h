@@ -197,6 +197,7 @@ inline T __shfl_up(T v, int d)
 }
 
 inline int __ffsll(unsigned long long m) { return __builtin_ffsll((long long)m); }
+inline int __popc(unsigned m) { return __builtin_popcount(m); }
 inline int __popcll(unsigned long long m) { return __builtin_popcountll(m); }
 
 // lanes below this one among the mask's low (lanes 0-31) and high (32-63) halves
@@ -239,6 +240,41 @@ inline emu_i32x16 __builtin_amdgcn_mfma_i32_32x32x32_i8(emu_i32x4 a, emu_i32x4 b
     }
     w.bar->arrive_and_wait();
     return d;
+}
+
+typedef _Float16 emu_f16x8 __attribute__((ext_vector_type(8)));
+typedef float emu_f32x16 __attribute__((ext_vector_type(16)));
+
+// v_mfma_f32_32x32x16_f16: lane l supplies A[l % 32][8 (l / 32) + 0..7] and
+// B[k][l % 32] for k = 8 (l / 32) + 0..7; the output layout is the int8 one's.
+// Products and sums in fp32, in order.
+inline emu_f32x16 __builtin_amdgcn_mfma_f32_32x32x16_f16(emu_f16x8 a, emu_f16x8 b, emu_f32x16 c, int, int, int)
+{
+    emu::Wave &w = emu::wave();
+    const int l = emu::lane();
+    memcpy(w.buf[l], &a, 16);
+    memcpy(w.buf[l] + 16, &b, 16);
+    w.bar->arrive_and_wait();
+    emu_f32x16 d;
+    for (int r = 0; r < 16; ++r) {
+        const int i = 8 * (r / 4) + 4 * (l / 32) + r % 4, j = l % 32;
+        float s = c[r];
+        for (int k = 0; k < 16; ++k) {
+            _Float16 av, bv;
+            memcpy(&av, w.buf[i + 32 * (k / 8)] + 2 * (k % 8), 2);
+            memcpy(&bv, w.buf[j + 32 * (k / 8)] + 16 + 2 * (k % 8), 2);
+            s += (float)av * (float)bv;
+        }
+        d[r] = s;
+    }
+    w.bar->arrive_and_wait();
+    return d;
+}
+
+// the middle of three
+inline float __builtin_amdgcn_fmed3f(float a, float b, float c)
+{
+    return fmaxf(fminf(a, b), fminf(fmaxf(a, b), c));
 }
 
 // v_dot4_i32_i8 without clamping: c + the dot of the four signed bytes
@@ -323,6 +359,7 @@ inline int __builtin_amdgcn_readlane(int v, int src)
 }
 
 inline void __builtin_amdgcn_sched_barrier(int) {}
+inline void __builtin_amdgcn_s_waitcnt(int) {}
 // the wave's lanes meet (every lane of the wave must come)
 inline void __builtin_amdgcn_wave_barrier() { emu::wave().bar->arrive_and_wait(); }
 // a compiler fence; the host's barriers already order the lanes' accesses
