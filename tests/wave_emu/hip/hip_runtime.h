@@ -37,6 +37,10 @@ struct uint2 {
 struct float4 {
     float x, y, z, w;
 };
+struct float2 {
+    float x, y;
+};
+inline float2 make_float2(float x, float y) { return float2{x, y}; }
 inline uint2 make_uint2(unsigned x, unsigned y) { return uint2{x, y}; }
 inline float4 make_float4(float x, float y, float z, float w) { return float4{x, y, z, w}; }
 struct longlong2 {
@@ -362,8 +366,9 @@ inline void __builtin_amdgcn_sched_barrier(int) {}
 inline void __builtin_amdgcn_s_waitcnt(int) {}
 // the wave's lanes meet (every lane of the wave must come)
 inline void __builtin_amdgcn_wave_barrier() { emu::wave().bar->arrive_and_wait(); }
-// a compiler fence; the host's barriers already order the lanes' accesses
-inline void __builtin_amdgcn_fence(int, const char *) {}
+// A wave's LDS accesses stay in order on the device; between the lanes' host
+// threads that takes a barrier (every lane of the wave must come).
+inline void __builtin_amdgcn_fence(int, const char *) { emu::wave().bar->arrive_and_wait(); }
 
 inline uint32_t __float_as_uint(float f)
 {
@@ -377,6 +382,8 @@ inline float __uint_as_float(uint32_t u)
     memcpy(&f, &u, 4);
     return f;
 }
+inline int __float_as_int(float f) { return (int)__float_as_uint(f); }
+inline float __int_as_float(int i) { return __uint_as_float((uint32_t)i); }
 inline long long __double_as_longlong(double d)
 {
     long long v;
