@@ -60,7 +60,7 @@ def setup(seed, B, C, D, M, N, P, skew):
     return q, c, probes, off, perm, codes, cb
 
 
-@pytest.mark.parametrize("D,M", [(32, 4), (64, 16), (96, 24), (32, 2), (8, 8), (12, 6), (36, 12), (112, 28), (20, 4),
+@pytest.mark.parametrize("D,M", [(32, 4), (64, 16), (96, 24), (32, 2), (8, 8), (12, 6), (36, 12), (20, 4),
                                  (24, 4), (28, 4), (192, 24), (36, 4), (208, 13), (68, 2), (256, 1), (60, 60)])
 def test_emulated_widths(emu_adc, oracle_mod, tmp_path, D, M):
     a = setup(D + M, 1, 9, D, M, 700, 5, 0.5)

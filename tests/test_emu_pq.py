@@ -35,9 +35,9 @@ def emu_pq(tmp_path_factory):
 
 
 @pytest.mark.parametrize("kind,n,D,M", [
-    ("plain", 1, 4, 1), ("plain", 65, 8, 1), ("plain", 130, 32, 4), ("plain", 100, 16, 1), ("plain", 64, 12, 4),
-    ("plain", 70, 20, 4), ("plain", 70, 24, 2), ("plain", 70, 120, 30), ("range", 150, 16, 2), ("far30", 130, 16, 2),
-    ("equal", 130, 32, 4), ("equal", 700, 16, 1), ("one", 1300, 8, 2), ("vanish", 70, 8, 1), ("vast", 70, 8, 8),
+    ("plain", 1, 4, 1), ("plain", 65, 8, 1), ("plain", 70, 32, 4), ("plain", 70, 16, 1), ("plain", 64, 12, 4),
+    ("plain", 70, 20, 4), ("plain", 20, 120, 30), ("range", 70, 16, 2), ("far30", 70, 16, 2),
+    ("equal", 70, 32, 4), ("equal", 600, 16, 1), ("one", 1300, 8, 2), ("vanish", 70, 8, 1), ("vast", 70, 8, 8),
     ("blocks", 8 * 64 * 37 + 5, 4, 1), ("blocks", 8 * 64 * 9 + 5, 8, 4),
 ])
 def test_emulated_codes(emu_pq, oracle_mod, tmp_path, kind, n, D, M):

@@ -59,10 +59,10 @@ def run(exe, tmp_path, x, c, tau, list_cap, duel_cap, collect, Cs, stride, L, cu
 
 
 @pytest.mark.parametrize("kind,N,C,D,cap,duels,collect,cus", [
-    ("plain", 70, 300, 36, 70, 70, 1, 1), ("plain", 600, 130, 64, 600, 600, 1, 2), ("plain", 40, 513, 100, 40, 40, 1, 3),
-    ("plain", 300, 90, 160, 300, 300, 1, 2), ("plain", 33, 70, 256, 33, 33, 1, 1), ("plain", 5, 1, 4, 5, 5, 1, 1),
-    ("ties", 560, 200, 96, 560, 560, 1, 2), ("ties", 300, 150, 128, 300, 20, 1, 2), ("ties", 300, 150, 32, 40, 300, 1, 1),
-    ("ties", 200, 150, 64, 200, 200, 0, 2), ("range", 200, 100, 64, 200, 200, 1, 1), ("zero", 60, 50, 32, 60, 60, 1, 2),
+    ("plain", 70, 300, 36, 70, 70, 1, 1), ("plain", 540, 70, 64, 540, 540, 1, 2),
+    ("plain", 40, 90, 160, 40, 40, 1, 2), ("plain", 33, 70, 256, 33, 33, 1, 1), ("plain", 5, 1, 4, 5, 5, 1, 1),
+    ("ties", 100, 200, 96, 100, 100, 1, 2), ("ties", 100, 150, 128, 100, 20, 1, 2), ("ties", 200, 150, 32, 40, 200, 1, 1),
+    ("ties", 60, 150, 64, 60, 60, 0, 1), ("range", 100, 100, 64, 100, 100, 1, 1), ("zero", 40, 50, 32, 40, 40, 1, 1),
 ])
 def test_emulated_f16(emu_f16, oracle_mod, tmp_path, kind, N, C, D, cap, duels, collect, cus):
     x, c = data(kind, N, C, D, seed=N + C + D)
