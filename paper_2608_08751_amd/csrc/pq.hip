@@ -22,7 +22,7 @@
 //   - a few undecided rows of a tile (0.07 % of the sub-vectors of Gaussian
 //     residuals) get the wave's four codewords per lane, one row after another;
 //   - a tile with more is left for the dense evaluation: one row per lane,
-//     four tiles at a time, every codeword read once for them. The window
+//     several tiles at a time, every codeword read once for them. The window
 //     follows the largest ||C||, so one codeword far from the others, equal
 //     codewords or narrow subspaces can leave most rows undecided; where two
 //     tiles in a row were left, the following ones skip the screen;
